@@ -273,8 +273,7 @@ struct alignas(16) StepTabs {
 static_assert(sizeof(StepTabs) % 16 == 0, "staged in 16-byte words");
 
 struct Dev {
-    const PairTab* pair;   // kMaxTypes x kMaxTypes
-    const StepTabs* tabs;  // the same constants for k_step
+    const StepTabs* tabs;  // per-type and per-type-pair constants
     float4* x[2];          // positions (xyz) + type bits (w), double-buffered
     float4* u;             // velocity before the closing half kick of the last step
     int32_t* img;          // image counters, 3 x n
@@ -299,8 +298,8 @@ struct Dev {
     unsigned long long* stepv;      // two step slots (parity of the step)
     unsigned long long* ke_fix;     // [2] sum m v^2 in 2^-32 fixed point (kinetic kT), one slot per sweep parity
     uint32_t* err;         // [0] flags, [1], [2] tags of the offending pair
-    float4* f4;            // forces + per-particle energy (evaluation kernels)
-    unsigned long long* red;        // reduction scratch (observables)
+    float4* f4;            // forces (evaluation kernels)
+    unsigned long long* red;        // sums of the observables (kObsSlots x kObsWords, zero between calls)
     uint32_t* scan;        // scan scratch (bond read-out)
     uint32_t* parent;      // union-find parents (cluster observable)
     uint32_t* nl;          // nlmax x n neighbour indices (slot-major)

@@ -40,8 +40,9 @@ thread_local std::string g_create_error;
 
 struct TypeCfg { uint32_t valence = 0; double sigma = 1.0, eps = 1.0, mass = 1.0; };
 struct BondCfg { int kind; double k, r0; double lmin = 0, lc1 = 0, lc0 = 0, lmax = 0; };
-constexpr uint32_t kAnaHist = 256;              // largest histogram of the network analyses
+constexpr uint32_t kAnaHist = kHistMax;         // largest histogram of the network analyses
 constexpr uint32_t kAnaWords = kAnaHist + 8;
+constexpr uint32_t kPinnedWords = kAnaWords > kObsOut ? kAnaWords : kObsOut;
 struct RxRes { double k_on, k_off, eps, p_on, p_off; };
 // rate modifier of one reaction: 0 none, 1 melting, 2 slip bond
 struct RxMod { int kind = 0; double lam = 0, tm = 0, k_on_m = 0, k_off_m = 0, a = 0; };
@@ -94,9 +95,10 @@ struct db_system {
     std::vector<void*> allocs;
     hipStream_t stream = nullptr, own_stream = nullptr;
     uint32_t* bsum = nullptr;       // block sums for the bond read-out (nb + 1)
-    float4* stage = nullptr;        // tag-ordered staging buffer
-    uint32_t* flag = nullptr;       // device flag for iterative kernels
-    uint32_t* err_h = nullptr;      // pinned host copy of the device error words
+    float* stage = nullptr;         // tag-ordered staging buffer (3 n words)
+    uint32_t* err_h = nullptr;      // pinned host memory: the device error words, then `obs_h`
+    unsigned long long* obs_h = nullptr;   // pinned answers of the observables and histograms
+    std::vector<double> val_sum;           // per type: valence x particles
     uint64_t step = 0;
     int cur_x = 0, cur_list = 0;
     std::vector<uint32_t> tag_h, rtag_h;   // host mirrors of tag / rtag
@@ -184,6 +186,12 @@ struct TimerScope {
     do {                                                                                     \
         if ((sys)->P.ext) LAUNCH_AS(sys, tname, (kern<true>), grid, block, __VA_ARGS__);     \
         else LAUNCH_AS(sys, tname, (kern<false>), grid, block, __VA_ARGS__);                 \
+    } while (0)
+#define LAUNCH_EVAL(sys, mode, xin, off, out3)                                                     \
+    do {                                                                                           \
+        const unsigned ge_ = grid_of((sys)->n);                                                    \
+        if ((sys)->P.ext) LAUNCH_AS(sys, "k_eval", (k_eval<true, mode>), ge_, kBlock, (sys)->P, (sys)->D, xin, off, out3); \
+        else LAUNCH_AS(sys, "k_eval", (k_eval<false, mode>), ge_, kBlock, (sys)->P, (sys)->D, xin, off, out3);             \
     } while (0)
 // the same, with the name the kernel is timed under given explicitly
 #define LAUNCH_AS(sys, tname, kern, grid, block, ...)                                            \
@@ -750,7 +758,7 @@ db_status upload_state(db_system* s, const float* pos3, const float* vel3, const
     for (int l = 0; l < 3; ++l) LAUNCH(s, k_clear_counts, std::min(grid_of(P.ncell), 65535u), kBlock, s->P, s->D, l);
     LAUNCH(s, k_binr, grid_of(n), kBlock, s->P, s->D, s->cur_x, (int)(s->step % 3));
     LAUNCH(s, k_nlist, ntiles(P), kTileThreads, s->P, s->D, (int)(s->step % 3));
-    LAUNCH(s, k_eval, grid_of(n), kBlock, s->P, s->D, s->cur_x, 0u);
+    LAUNCH_EVAL(s, 0, s->cur_x, 0u, (float*)nullptr);
     if (!vel_is_u) LAUNCH(s, k_init_u, grid_of(n), kBlock, s->P, s->D, s->cur_x, 0u);
     HIPCHK(s, hipGetLastError());
     HIPCHK(s, hipStreamSynchronize(s->stream));
@@ -786,6 +794,15 @@ db_status ensure_cell_capacity(db_system* s, const float* pos3) {
     return DB_OK;
 }
 
+// What the device's error words (read back by the caller) mean.
+db_status report_errors(db_system* s, const uint32_t* err) {
+    if (err[0] & kErrOverflow) { s->invalid = true; return fail(s, DB_EOVERFLOW, "cell capacity %u exceeded", s->P.cellcap); }
+    if (err[0] & kErrFene) { s->invalid = true; return fail(s, DB_EBOND, "bond %u-%u outside its range (FENE r >= R0, tether r outside (l_min, l_max))", err[1], err[2]); }
+    if (err[0] & kErrForce) { s->invalid = true; return fail(s, DB_EBOND, "force out of the representable range"); }
+    if (err[0] & kErrNlist) { s->invalid = true; return fail(s, DB_EOVERFLOW, "more than %u neighbours of one particle", s->P.nlmax); }
+    return DB_OK;
+}
+
 db_status check_errors(db_system* s) {
     HIPCHK(s, hipGetLastError());
     // the error words come back through a pinned buffer, behind the work on
@@ -795,11 +812,7 @@ db_status check_errors(db_system* s) {
     flush_timing(s);
     uint32_t err[4];
     std::memcpy(err, s->err_h, sizeof err);
-    if (err[0] & kErrOverflow) { s->invalid = true; return fail(s, DB_EOVERFLOW, "cell capacity %u exceeded", s->P.cellcap); }
-    if (err[0] & kErrFene) { s->invalid = true; return fail(s, DB_EBOND, "bond %u-%u outside its range (FENE r >= R0, tether r outside (l_min, l_max))", err[1], err[2]); }
-    if (err[0] & kErrForce) { s->invalid = true; return fail(s, DB_EBOND, "force out of the representable range"); }
-    if (err[0] & kErrNlist) { s->invalid = true; return fail(s, DB_EOVERFLOW, "more than %u neighbours of one particle", s->P.nlmax); }
-    return DB_OK;
+    return report_errors(s, err);
 }
 
 // Sweep at the current positions: buffers xcur / cell list lst, step key in slot sp.
@@ -1544,11 +1557,6 @@ static db_status commit_impl(db_system* s) {
     s->stream = s->own_stream;
     s->committed = true;   // from here on db_destroy frees device memory
     {
-        PairTab* pt = nullptr;
-        DALLOC(s, pt, (size_t)kMaxTypes * kMaxTypes);
-        HIPCHK(s, hipMemcpyAsync(pt, s->pair_h.data(), s->pair_h.size() * sizeof(PairTab),
-                                 hipMemcpyHostToDevice, s->stream));
-        D.pair = pt;
         // step tables: the same numbers k_step would read from the parameter
         // block, laid out for one 16-byte copy per thread into LDS
         StepTabs th{};
@@ -1587,7 +1595,8 @@ static db_status commit_impl(db_system* s) {
     DALLOC(s, D.ke_fix, 2);
     DALLOC(s, D.err, 4);
     DALLOC(s, D.f4, 2 * (size_t)n);
-    DALLOC(s, D.red, 4 + kMaxRx);
+    DALLOC(s, D.red, kObsSlots * kObsWords);
+    HIPCHK(s, hipMemsetAsync(D.red, 0, kObsSlots * kObsWords * sizeof(unsigned long long), s->stream));
     DALLOC(s, s->ana, kAnaWords);
     DALLOC(s, D.scan, (size_t)n + 1);
     DALLOC(s, D.parent, n);
@@ -1609,16 +1618,18 @@ static db_status commit_impl(db_system* s) {
     DALLOC(s, D.mol_alt, n);
     DALLOC(s, D.dyn_alt, (size_t)P.cap_max * n);
     DALLOC(s, D.stat_alt, (size_t)std::max(P.stat_max, 1u) * n);
-    DALLOC(s, s->stage, n);
-    DALLOC(s, s->flag, 1);
+    DALLOC(s, s->stage, 3 * (size_t)n);
     {
         void* h = nullptr;
-        if (hipHostMalloc(&h, 4 * sizeof(uint32_t), hipHostMallocDefault) != hipSuccess) {
+        if (hipHostMalloc(&h, 16 + kPinnedWords * sizeof(unsigned long long), hipHostMallocDefault) != hipSuccess) {
             (void)hipGetLastError();
             return fail(s, DB_ENOMEM, "pinned host allocation failed");
         }
         s->err_h = (uint32_t*)h;
+        s->obs_h = (unsigned long long*)((char*)h + 16);
     }
+    s->val_sum.assign(s->ntypes, 0.0);
+    for (uint32_t i = 0; i < n; ++i) s->val_sum[s->type[i]] += s->types[s->type[i]].valence;
     // static topology, molecule ids, tags
     std::vector<uint32_t> stat((size_t)std::max(P.stat_max, 1u) * n, kEmpty), fillc(n, 0);
     for (size_t k = 0; k < s->stat_bt.size(); ++k) {
@@ -2013,7 +2024,7 @@ db_status db_sweep_frozen(db_system* s, uint64_t step_key) {
     HIPCHK(s, hipSetDevice(s->device));
     const unsigned g = grid_of(s->n);
     const int xc = s->cur_x;
-    LAUNCH(s, k_eval, g, kBlock, s->P, s->D, xc, 0u);
+    LAUNCH_EVAL(s, 0, xc, 0u, (float*)nullptr);
     const unsigned long long sv[2] = {step_key, step_key};
     const unsigned long long sv_back[2] = {s->step, s->step};
     HIPCHK(s, hipMemcpyAsync(s->D.stepv, sv, sizeof sv, hipMemcpyHostToDevice, s->stream));
@@ -2024,7 +2035,7 @@ db_status db_sweep_frozen(db_system* s, uint64_t step_key) {
     launch_sweep(s, xc, (int)(step_key & 1));
     // both kinetic-energy slots start the next regular sweep cleared
     if (s->P.kt_kinetic) HIPCHK(s, hipMemsetAsync(s->D.ke_fix, 0, 16, s->stream));
-    LAUNCH(s, k_eval, g, kBlock, s->P, s->D, xc, s->n);
+    LAUNCH_EVAL(s, 0, xc, s->n, (float*)nullptr);
     LAUNCH(s, k_fix_u, g, kBlock, s->P, s->D, xc);
     HIPCHK(s, hipMemcpyAsync(s->D.stepv, sv_back, sizeof sv_back, hipMemcpyHostToDevice, s->stream));
     return check_errors(s);
@@ -2183,24 +2194,16 @@ db_status db_read_positions(db_system* s, float* pos3, int32_t* image3) {
     if (st != DB_OK) return st;
     if (!pos3) return fail(s, DB_EINVAL, "pos3 is NULL");
     HIPCHK(s, hipSetDevice(s->device));
-    LAUNCH(s, k_gather, grid_of(s->n), kBlock, s->P, s->D, s->stage, s->cur_x, 0);
-    std::vector<float4> h(s->n);
-    HIPCHK(s, hipMemcpyAsync(h.data(), s->stage, s->n * sizeof(float4), hipMemcpyDeviceToHost, s->stream));
-    std::vector<int32_t> im;
+    const size_t bytes = 3 * (size_t)s->n * sizeof(float);
+    LAUNCH(s, k_gather3, grid_of(s->n), kBlock, s->P, s->D, s->stage, s->cur_x);
+    HIPCHK(s, hipMemcpyAsync(pos3, s->stage, bytes, hipMemcpyDeviceToHost, s->stream));
     if (image3) {
-        // the staging buffer (16 n bytes) is reused for 12 n bytes of image counters;
-        // the position copy above is ordered before this kernel on the stream
+        // the staging buffer is reused; the position copy above is ordered
+        // before this kernel on the stream
         LAUNCH(s, k_gather_img, grid_of(s->n), kBlock, s->P, s->D, (int32_t*)s->stage);
-        im.resize(3 * (size_t)s->n);
-        HIPCHK(s, hipMemcpyAsync(im.data(), s->stage, im.size() * 4, hipMemcpyDeviceToHost, s->stream));
+        HIPCHK(s, hipMemcpyAsync(image3, s->stage, bytes, hipMemcpyDeviceToHost, s->stream));
     }
     HIPCHK(s, hipStreamSynchronize(s->stream));
-    for (uint32_t t = 0; t < s->n; ++t) {
-        pos3[3 * t] = h[t].x;
-        pos3[3 * t + 1] = h[t].y;
-        pos3[3 * t + 2] = h[t].z;
-    }
-    if (image3) std::memcpy(image3, im.data(), im.size() * 4);
     return DB_OK;
 }
 
@@ -2209,17 +2212,12 @@ static db_status read_vec(db_system* s, float* out3, int mode) {
     if (st != DB_OK) return st;
     if (!out3) return fail(s, DB_EINVAL, "output is NULL");
     HIPCHK(s, hipSetDevice(s->device));
-    LAUNCH(s, k_eval, grid_of(s->n), kBlock, s->P, s->D, s->cur_x, 0u);
-    LAUNCH(s, k_gather, grid_of(s->n), kBlock, s->P, s->D, s->stage, s->cur_x, mode);
-    std::vector<float4> h(s->n);
-    HIPCHK(s, hipMemcpyAsync(h.data(), s->stage, s->n * sizeof(float4), hipMemcpyDeviceToHost, s->stream));
+    if (mode == 1) LAUNCH_EVAL(s, 1, s->cur_x, 0u, s->stage);
+    else LAUNCH_EVAL(s, 2, s->cur_x, 0u, s->stage);
     st = check_errors(s);
     if (st != DB_OK) return st;
-    for (uint32_t t = 0; t < s->n; ++t) {
-        out3[3 * t] = h[t].x;
-        out3[3 * t + 1] = h[t].y;
-        out3[3 * t + 2] = h[t].z;
-    }
+    HIPCHK(s, hipMemcpyAsync(out3, s->stage, 3 * (size_t)s->n * sizeof(float), hipMemcpyDeviceToHost, s->stream));
+    HIPCHK(s, hipStreamSynchronize(s->stream));
     return DB_OK;
 }
 
@@ -2231,18 +2229,22 @@ static db_status read_vec_device(db_system* s, float* out3, void* stream, int mo
     if (!out3) return fail(s, DB_EINVAL, "output is NULL");
     HIPCHK(s, hipSetDevice(s->device));
     const hipStream_t q = stream ? (hipStream_t)stream : s->stream;
-    if (mode != 0) LAUNCH(s, k_eval, grid_of(s->n), kBlock, s->P, s->D, s->cur_x, 0u);
-    if (q != s->stream) {
+    const hipStream_t own = s->stream;
+    if (q != own) {
         if (!s->ev_out) HIPCHK(s, hipEventCreateWithFlags(&s->ev_out, hipEventDisableTiming));
         if (!s->ev_back) HIPCHK(s, hipEventCreateWithFlags(&s->ev_back, hipEventDisableTiming));
-        HIPCHK(s, hipEventRecord(s->ev_out, s->stream));
+        HIPCHK(s, hipEventRecord(s->ev_out, own));
         HIPCHK(s, hipStreamWaitEvent(q, s->ev_out, 0));
     }
-    hipLaunchKernelGGL(k_gather3, dim3(grid_of(s->n)), dim3(kBlock), 0, q, s->P, s->D, out3, s->cur_x, mode);
+    s->stream = q;                         // the launches below go to the caller's stream
+    if (mode == 0) LAUNCH(s, k_gather3, grid_of(s->n), kBlock, s->P, s->D, out3, s->cur_x);
+    else if (mode == 1) LAUNCH_EVAL(s, 1, s->cur_x, 0u, out3);
+    else LAUNCH_EVAL(s, 2, s->cur_x, 0u, out3);
+    s->stream = own;
     HIPCHK(s, hipGetLastError());
-    if (q != s->stream) {
+    if (q != own) {
         HIPCHK(s, hipEventRecord(s->ev_back, q));
-        HIPCHK(s, hipStreamWaitEvent(s->stream, s->ev_back, 0));
+        HIPCHK(s, hipStreamWaitEvent(own, s->ev_back, 0));
     }
     return DB_OK;
 }
@@ -2366,44 +2368,25 @@ db_status db_read_sweep_events(db_system* s, int which, uint32_t* pairs, uint32_
     return check_errors(s);
 }
 
-// Clusters of static + dynamic bonds: union by minimum index until no hook
-// changes a root; then D.parent holds each particle's root and D.scan each
-// root's cluster size.
-static db_status label_clusters(db_system* s) {
-    const unsigned g = grid_of(s->n);
-    const Params& P = s->P;
-    LAUNCH(s, k_cc_init, g, kBlock, P, s->D);
-    for (int it = 0; it < 64; ++it) {
-        uint32_t changed = 0;
-        HIPCHK(s, hipMemsetAsync(s->flag, 0, 4, s->stream));
-        LAUNCH(s, k_cc_hook, g, kBlock, P, s->D, s->flag, s->cur_x);
-        LAUNCH(s, k_cc_compress, g, kBlock, P, s->D);
-        HIPCHK(s, hipMemcpyAsync(&changed, s->flag, 4, hipMemcpyDeviceToHost, s->stream));
-        HIPCHK(s, hipStreamSynchronize(s->stream));
-        if (!changed) break;
-        if (it == 63) return fail(s, DB_EDEVICE, "cluster labelling did not converge");
-    }
-    HIPCHK(s, hipMemsetAsync(s->D.scan, 0, (size_t)s->n * 4, s->stream));
-    LAUNCH(s, k_cc_size, g, kBlock, P, s->D);
-    return DB_OK;
-}
-
 db_status db_cluster_sizes(db_system* s, uint64_t* hist, uint32_t len, uint64_t* n_clusters) {
     db_status st = ready(s);
     if (st != DB_OK) return st;
     if (!hist || !n_clusters || len < 1 || len > kAnaHist)
         return fail(s, DB_EINVAL, "histogram of 1..%u bins and output pointers required", kAnaHist);
     HIPCHK(s, hipSetDevice(s->device));
-    st = label_clusters(s);
-    if (st != DB_OK) return st;
+    const unsigned g = grid_of(s->n);
     HIPCHK(s, hipMemsetAsync(s->ana, 0, kAnaWords * 8, s->stream));
-    LAUNCH(s, k_cc_hist, grid_of(s->n), kBlock, s->P, s->D, s->ana + 1, len, s->ana);
-    unsigned long long h[kAnaWords];
-    HIPCHK(s, hipMemcpyAsync(h, s->ana, (len + 1) * 8, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(s, hipStreamSynchronize(s->stream));
-    *n_clusters = h[0];
-    for (uint32_t k = 0; k < len; ++k) hist[k] = h[1 + k];
-    return check_errors(s);
+    LAUNCH(s, k_cc_init, g, kBlock, s->P, s->D);
+    LAUNCH(s, k_cc_union, g, kBlock, s->P, s->D, s->cur_x);
+    LAUNCH(s, k_cc_size, g, kBlock, s->P, s->D);
+    LAUNCH(s, k_cc_hist, std::min(g, 512u), kBlock, s->P, s->D, s->ana + 1, len, s->ana);
+    // (k_cc_size also leaves the largest component in the observables' sums)
+    HIPCHK(s, hipMemsetAsync(s->D.red, 0, kObsSlots * kObsWords * sizeof(unsigned long long), s->stream));
+    HIPCHK(s, hipMemcpyAsync(s->obs_h, s->ana, (len + 1) * 8, hipMemcpyDeviceToHost, s->stream));
+    st = check_errors(s);
+    *n_clusters = s->obs_h[0];
+    for (uint32_t k = 0; k < len; ++k) hist[k] = s->obs_h[1 + k];
+    return st;
 }
 
 db_status db_bond_reference(db_system* s) {
@@ -2425,12 +2408,11 @@ db_status db_bond_correlation(db_system* s, uint64_t* n_reference, uint64_t* n_i
     HIPCHK(s, hipSetDevice(s->device));
     HIPCHK(s, hipMemsetAsync(s->ana, 0, 16, s->stream));
     LAUNCH(s, k_bond_corr, grid_of(s->n), kBlock, s->P, s->D, s->bref, s->ana);
-    unsigned long long h[2];
-    HIPCHK(s, hipMemcpyAsync(h, s->ana, 16, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(s, hipStreamSynchronize(s->stream));
-    *n_reference = h[0];
-    *n_intact = h[1];
-    return check_errors(s);
+    HIPCHK(s, hipMemcpyAsync(s->obs_h, s->ana, 16, hipMemcpyDeviceToHost, s->stream));
+    st = check_errors(s);
+    *n_reference = s->obs_h[0];
+    *n_intact = s->obs_h[1];
+    return st;
 }
 
 db_status db_bond_multiplicity(db_system* s, uint64_t* hist, uint32_t len, uint64_t* n_pairs, uint64_t* n_intra) {
@@ -2441,7 +2423,7 @@ db_status db_bond_multiplicity(db_system* s, uint64_t* hist, uint32_t len, uint6
     HIPCHK(s, hipSetDevice(s->device));
     // table: a power of two at least twice the largest possible number of bonds
     uint64_t max_bonds = 0;
-    for (uint32_t i = 0; i < s->n; ++i) max_bonds += s->types[s->type[i]].valence;
+    for (double v : s->val_sum) max_bonds += (uint64_t)v;
     uint32_t size = 1024;
     while (size < 2 * (max_bonds / 2 + 1)) size *= 2;
     unsigned long long* keys = nullptr;
@@ -2453,15 +2435,14 @@ db_status db_bond_multiplicity(db_system* s, uint64_t* hist, uint32_t len, uint6
     HIPCHK(s, hipMemsetAsync(s->ana, 0, kAnaWords * 8, s->stream));
     LAUNCH(s, k_mol_pairs, grid_of(s->n), kBlock, s->P, s->D, s->cur_x, keys, counts, size - 1u, s->ana);
     LAUNCH(s, k_mol_hist, grid_of(size), kBlock, keys, counts, size, s->ana + 2, len, s->ana + 1);
-    unsigned long long h[kAnaWords];
-    HIPCHK(s, hipMemcpyAsync(h, s->ana, (len + 2) * 8, hipMemcpyDeviceToHost, s->stream));
+    HIPCHK(s, hipMemcpyAsync(s->obs_h, s->ana, (len + 2) * 8, hipMemcpyDeviceToHost, s->stream));
     HIPCHK(s, hipFreeAsync(keys, s->stream));
     HIPCHK(s, hipFreeAsync(counts, s->stream));
-    HIPCHK(s, hipStreamSynchronize(s->stream));
-    *n_intra = h[0];
-    *n_pairs = h[1];
-    for (uint32_t k = 0; k < len; ++k) hist[k] = h[2 + k];
-    return check_errors(s);
+    st = check_errors(s);
+    *n_intra = s->obs_h[0];
+    *n_pairs = s->obs_h[1];
+    for (uint32_t k = 0; k < len; ++k) hist[k] = s->obs_h[2 + k];
+    return st;
 }
 
 db_status db_read_observables(db_system* s, db_observables* out) {
@@ -2471,42 +2452,42 @@ db_status db_read_observables(db_system* s, db_observables* out) {
     HIPCHK(s, hipSetDevice(s->device));
     const unsigned g = grid_of(s->n);
     const Params& P = s->P;
-    LAUNCH(s, k_eval, g, kBlock, P, s->D, s->cur_x, 0u);
-    HIPCHK(s, hipMemsetAsync(s->D.red, 0, (4 + kMaxRx) * 8, s->stream));
-    LAUNCH(s, k_observe, g, kBlock, P, s->D, s->cur_x);
-    // largest cluster
-    st = label_clusters(s);
+    // one workgroup does everything up to kObsOneMaxN particles: one launch
+    // and one wait (the sum kernel's answer lands in pinned memory)
+    if (s->n <= kObsOneMaxN) {
+        const size_t lds = s->n * sizeof(uint32_t);
+        if (P.ext)
+            hipLaunchKernelGGL((k_observe_one<true>), dim3(1), dim3(kObsOneThreads), lds, s->stream, P, s->D, s->cur_x, s->obs_h);
+        else
+            hipLaunchKernelGGL((k_observe_one<false>), dim3(1), dim3(kObsOneThreads), lds, s->stream, P, s->D, s->cur_x, s->obs_h);
+    } else {
+        LAUNCH_EXT(s, "k_observe", k_observe, g, kBlock, P, s->D, s->cur_x);
+        LAUNCH(s, k_cc_union, g, kBlock, P, s->D, s->cur_x);
+        LAUNCH(s, k_cc_size, g, kBlock, P, s->D);
+        LAUNCH(s, k_observe_sum, 1, 1024, P, s->D, s->obs_h);
+    }
+    HIPCHK(s, hipGetLastError());
+    HIPCHK(s, hipStreamSynchronize(s->stream));
+    flush_timing(s);
+    const unsigned long long* o = s->obs_h;
+    const uint32_t err[4] = {(uint32_t)o[kObsErr], (uint32_t)o[kObsErr + 1], (uint32_t)o[kObsErr + 2], (uint32_t)o[kObsErr + 3]};
+    st = report_errors(s, err);
     if (st != DB_OK) return st;
-    LAUNCH(s, k_cc_max, g, kBlock, P, s->D);
-    unsigned long long red[4 + kMaxRx];
-    std::vector<unsigned long long> slots((size_t)3 * kMaxRx * kCtrSlots);
-    HIPCHK(s, hipMemcpyAsync(red, s->D.red, sizeof red, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(s, hipMemcpyAsync(slots.data(), s->D.counters, slots.size() * sizeof(unsigned long long),
-                             hipMemcpyDeviceToHost, s->stream));
-    st = check_errors(s);
-    if (st != DB_OK) return st;
-    unsigned long long ctr[3 * kMaxRx] = {};
-    for (size_t c = 0; c < (size_t)3 * kMaxRx; ++c)
-        for (uint32_t w = 0; w < kCtrSlots; ++w) ctr[c] += slots[c * kCtrSlots + w];
     std::memset(out, 0, sizeof *out);
     out->step = s->step;
     out->n_reactions = P.nrx;
-    out->pe = (double)red[0] * kFixInv;
-    out->ke = (double)red[1] * kFixInv;
+    out->pe = (double)o[kObsPe] * kFixInv;
+    out->ke = (double)o[kObsKe] * kFixInv;
     out->t_kin = 2.0 * out->ke / (3.0 * (double)s->n);
-    out->largest_cluster_fraction = (double)red[2 + kMaxRx] / (double)s->n;
+    out->largest_cluster_fraction = (double)o[kObsLargest] / (double)s->n;
     for (uint32_t a = 0; a < P.nrx; ++a) {
-        out->n_bonds[a] = red[2 + a];
-        out->attempts[a] = ctr[3 * a];
-        out->forms[a] = ctr[3 * a + 1];
-        out->breaks[a] = ctr[3 * a + 2];
-        double cap_a = 0, cap_b = 0;
-        for (uint32_t i = 0; i < s->n; ++i) {
-            if (s->type[i] == s->rx[a].type_a) cap_a += s->types[s->type[i]].valence;
-            if (s->type[i] == s->rx[a].type_b) cap_b += s->types[s->type[i]].valence;
-        }
+        out->n_bonds[a] = o[kObsBonds + a];
+        out->attempts[a] = o[kObsCtr + 3 * a];
+        out->forms[a] = o[kObsCtr + 3 * a + 1];
+        out->breaks[a] = o[kObsCtr + 3 * a + 2];
+        const double cap_a = s->val_sum[s->rx[a].type_a], cap_b = s->val_sum[s->rx[a].type_b];
         const double denom = s->rx[a].type_a == s->rx[a].type_b ? cap_a / 2.0 : std::min(cap_a, cap_b);
-        out->bonded_fraction[a] = denom > 0 ? (double)red[2 + a] / denom : 0.0;
+        out->bonded_fraction[a] = denom > 0 ? (double)out->n_bonds[a] / denom : 0.0;
     }
     return DB_OK;
 }

@@ -109,156 +109,9 @@ __device__ __forceinline__ void bond_range_error(const Dev& D, uint32_t i, uint3
     }
 }
 
-// Bond force on site i from partner position pj (bond type bt), in FP64 from
-// the exact minimum-image separation.
-__device__ __forceinline__ void bond_force(const Params& P, const Dev& D, float4 pi, float4 pj,
-                                           uint32_t bt, uint32_t i, uint32_t j,
-                                           long long& fx, long long& fy, long long& fz,
-                                           double* e) {
-#pragma clang fp contract(off)
-    const double dx = mi_delta(pi.x, pj.x, P.L, P.invL);
-    const double dy = mi_delta(pi.y, pj.y, P.L, P.invL);
-    const double dz = mi_delta(pi.z, pj.z, P.L, P.invL);
-    const double r2 = (dx * dx + dy * dy) + dz * dz;
-    double f;
-    if (P.bkind[bt] == 1u) {                      // FENE: F_i = k / (1 - r^2/R0^2) d
-        const double g = 1.0 - r2 * P.binvR02[bt];
-        if (!(g > 0.0)) {
-            bond_range_error(D, i, j);
-            return;
-        }
-        f = P.bk[bt] * rcp64(g);
-        if (e) *e += 0.5 * (-0.5 * P.bk[bt] * P.bR02[bt] * log(g));
-    } else if (P.bkind[bt] == 2u) {               // tether: F_i = (dU/dr) / r d
-        const double r = sqrt(r2);
-        if (!(r > P.blmin[bt] && r < P.blmax[bt])) {
-            bond_range_error(D, i, j);
-            return;
-        }
-        double du;
-        const double U = tether_u(r, P.bk[bt], P.blmin[bt], P.blc1[bt], P.blc0[bt], P.blmax[bt], &du);
-        f = du / r;
-        if (e) *e += 0.5 * U;
-    } else {                                      // harmonic: F_i = k (r - r0) / r d
-        if (!(r2 > 0.0)) return;
-        const double ir = rsqrt64(r2);
-        const double dr = r2 * ir - P.br0[bt];
-        f = P.bk[bt] * dr * ir;
-        if (e) *e += 0.5 * (0.5 * P.bk[bt] * dr * dr);
-    }
-    fx += to_fix(f * dx, D.err);
-    fy += to_fix(f * dy, D.err);
-    fz += to_fix(f * dz, D.err);
-}
-
-// WCA force on pi from the cell-slot entry pj (position + index/type bits).
-// Screened in FP32 with a safety margin; pairs that survive are evaluated in
-// FP64.  The cutoff test r < 2^(1/6) sigma_ij is the oracle's: away from the
-// cutoff it is decided on r^2, within 1e-14 of it on the correctly rounded r.
-__device__ __forceinline__ void pair_force(const Params& P, const Dev& D, float4 pi, float4 pj, uint32_t ti,
-                                           long long& fx, long long& fy, long long& fz, double* e) {
-#pragma clang fp contract(off)
-    const int pt = (int)ti * kMaxTypes + (int)slot_type(pj);
-    const float fdx = mi_delta_f(pi.x, pj.x, P);
-    const float fdy = mi_delta_f(pi.y, pj.y, P);
-    const float fdz = mi_delta_f(pi.z, pj.z, P);
-    if (fdx * fdx + fdy * fdy + fdz * fdz >= P.rc2_pre[pt]) return;
-    const PairTab& pp = D.pair[pt];
-    const double dx = mi_delta(pi.x, pj.x, P.L, P.invL);
-    const double dy = mi_delta(pi.y, pj.y, P.L, P.invL);
-    const double dz = mi_delta(pi.z, pj.z, P.L, P.invL);
-    double r2;
-    {
-#pragma clang fp contract(off)
-        r2 = (dx * dx + dy * dy) + dz * dz;
-    }
-    if (r2 >= pp.rc2_hi) return;
-    if (r2 > pp.rc2_lo && !(sqrt(r2) < pp.rc)) return;
-    // F_i = -24 eps (sigma/r)^6 (2 (sigma/r)^6 - 1) / r^2 * d
-    const double ir2 = rcp64(r2);
-    const double sr2 = pp.sig2 * ir2;
-    const double sr6 = sr2 * sr2 * sr2;
-    const double f = pp.eps24 * sr6 * (2.0 * sr6 - 1.0) * ir2;
-    fx -= to_fix(f * dx, D.err);
-    fy -= to_fix(f * dy, D.err);
-    fz -= to_fix(f * dz, D.err);
-    if (e) *e += 0.5 * (4.0 * pp.eps * (sr6 * sr6 - sr6) + pp.eps);
-}
-
-// WCA force on pi from a position-array entry pj (type in the w bits).
-__device__ __forceinline__ void pair_force_xt(const Params& P, const Dev& D, float4 pi, float4 pj, uint32_t ti,
-                                              long long& fx, long long& fy, long long& fz, double* e) {
-    const float4 q = make_float4(pj.x, pj.y, pj.z, __uint_as_float(type_of(pj) << 24));
-    pair_force(P, D, pi, q, ti, fx, fy, fz, e);
-}
-
-// WCA force on pi from neighbour-list entry pj (type in the w bits).  When no
-// component of x_j - x_i needs a periodic image, the FP32 difference is the
-// correctly rounded separation, and pairs inside 0.98 rc (where
-// 2 (sigma/r)^6 - 1 > 0.12, no cancellation) are evaluated in FP32.  Pairs
-// near the cutoff and pairs across the boundary take the FP64 path of
-// pair_force.
-__device__ __forceinline__ void pair_force_list(const Params& P, const Dev& D, float4 pi, float4 pj, uint32_t ti,
-                                                long long& fx, long long& fy, long long& fz) {
-    const int pt = (int)ti * kMaxTypes + (int)type_of(pj);
-    const float dx = pj.x - pi.x, dy = pj.y - pi.y, dz = pj.z - pi.z;
-    if (fabsf(dx) <= P.halfLf && fabsf(dy) <= P.halfLf && fabsf(dz) <= P.halfLf) {
-        const float r2 = dx * dx + dy * dy + dz * dz;
-        if (r2 >= P.rc2_pre[pt]) return;
-        if (r2 < P.rc2_in[pt]) {
-            const float ir2 = __builtin_amdgcn_rcpf(r2);
-            const float sr2 = P.sig2f[pt] * ir2;
-            const float sr6 = sr2 * sr2 * sr2;
-            const float f = P.eps24f[pt] * sr6 * (2.0f * sr6 - 1.0f) * ir2;
-            fx -= to_fix((double)(f * dx), D.err);
-            fy -= to_fix((double)(f * dy), D.err);
-            fz -= to_fix((double)(f * dz), D.err);
-            return;
-        }
-    }
-    const float4 q = make_float4(pj.x, pj.y, pj.z, __uint_as_float(type_of(pj) << 24));
-    pair_force(P, D, pi, q, ti, fx, fy, fz, nullptr);
-}
-
-// Static and dynamic bond forces on particle i.
-__device__ __forceinline__ void bond_forces(const Params& P, const Dev& D, const float4* __restrict__ X,
-                                            uint32_t i, float4 pi, uint32_t ti,
-                                            long long& fx, long long& fy, long long& fz, double* e) {
-    for (uint32_t s = 0; s < P.stat_max; ++s) {
-        const uint32_t w = D.stat[(size_t)s * P.n + i];
-        if (w == kEmpty) break;
-        const uint32_t j = w & kIdxMask;
-        bond_force(P, D, pi, X[j], w >> 24, i, j, fx, fy, fz, e);
-    }
-    const uint32_t cap = P.cap[ti];
-    for (uint32_t s = 0; s < cap; ++s) {
-        const uint32_t w = D.dyn[(size_t)s * P.n + i];
-        if (w == kEmpty) continue;
-        const uint32_t j = w & kIdxMask;
-        bond_force(P, D, pi, X[j], P.rbt[(w >> 24) & 0x7Fu], i, j, fx, fy, fz, e);
-    }
-}
-
 __device__ __forceinline__ Force3 fix_to_force(const Dev& D, long long fx, long long fy, long long fz) {
     return Force3{(float)((double)fx * kFixInv), (float)((double)fy * kFixInv),
                   (float)((double)fz * kFixInv)};
-}
-
-// Total force on particle i at positions X from its neighbour list (valid
-// for X: every pair within the interaction range is listed until some
-// particle has moved by skin / 2 since the build, and the step that moves it
-// that far rebuilds the lists); optional per-particle energy (half of each
-// pair and bond energy).  Candidates are screened in FP32 with a safety
-// margin; pairs that survive are evaluated in FP64 with the same cutoff test
-// as the oracle (r < 2^(1/6) sigma_ij).  Each contribution is rounded to
-// 2^-32 and summed in 64-bit integers.
-__device__ __forceinline__ Force3 force_on(const Params& P, const Dev& D, const float4* __restrict__ X,
-                                           uint32_t i, float4 pi, uint32_t ti, double* e) {
-    long long fx = 0, fy = 0, fz = 0;
-    const uint32_t m = D.nl_cnt[i];
-    for (uint32_t k = 0; k < m; ++k) pair_force_xt(P, D, pi, X[D.nl[(size_t)k * P.n + i]], ti, fx, fy, fz, e);
-    bond_forces(P, D, X, i, pi, ti, fx, fy, fz, e);
-    return fix_to_force(D, fx, fy, fz);
 }
 
 __global__ void k_clear_counts(const Params P, const Dev D, int lst) {
@@ -316,16 +169,6 @@ __global__ void k_binr(const Params P, const Dev D, int xin, int f3) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     const bool valid = i < P.n;
     bin_wave(P, D, (int)D.rflag[3], i, valid, valid ? D.x[xin][i] : make_float4(0.f, 0.f, 0.f, 0.f));
-}
-
-// Forces (and per-particle energies) at the current positions into f4[off + i].
-__global__ void k_eval(const Params P, const Dev D, int xin, uint32_t off) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= P.n) return;
-    const float4 pi = D.x[xin][i];
-    double e = 0.0;
-    const Force3 f = force_on(P, D, D.x[xin], i, pi, type_of(pi), &e);
-    D.f4[off + i] = make_float4(f.x, f.y, f.z, (float)e);
 }
 
 // u = v - h F / m (turn full-step velocities into the stored form).
@@ -800,7 +643,7 @@ __device__ __forceinline__ bool pair_force_f32(const Params& P, const StepTabs& 
 
 __device__ __forceinline__ void pair_force_f64(const Params& P, const StepTabs& T, uint32_t* err, float4 pi,
                                                float4 pj, uint32_t ti, long long& fx, long long& fy,
-                                               long long& fz) {
+                                               long long& fz, double* e = nullptr) {
 #pragma clang fp contract(off)
     const PairTab& pp = T.pair[(int)ti * kMaxTypes + (int)type_of(pj)];
     const double ex = mi_delta(pi.x, pj.x, P.L, P.invL);
@@ -820,6 +663,7 @@ __device__ __forceinline__ void pair_force_f64(const Params& P, const StepTabs& 
     fx -= to_fix(f * ex, err);
     fy -= to_fix(f * ey, err);
     fz -= to_fix(f * ez, err);
+    if (e) *e += 0.5 * (4.0 * pp.eps * (sr6 * sr6 - sr6) + pp.eps);
 }
 
 __device__ __forceinline__ void pair_force_tab(const Params& P, const StepTabs& T, uint32_t* err, float4 pi,
@@ -829,13 +673,14 @@ __device__ __forceinline__ void pair_force_tab(const Params& P, const StepTabs& 
 }
 
 // Bond force on site i from partner j (bond type bt), FP64 from the exact
-// minimum-image separation, constants from LDS.
+// minimum-image separation, constants from LDS; with `e`, half the bond's
+// energy is added there.
 // EXT: the system has tether bonds or rate modifiers (kernels are built in
 // two variants, so that systems without them keep the lean register budget).
 template <bool EXT>
 __device__ __forceinline__ void bond_force_tab(const Params& P, const StepTabs& T, const Dev& D, float4 pi,
                                                float4 pj, uint32_t bt, uint32_t i, uint32_t j,
-                                               long long& fx, long long& fy, long long& fz) {
+                                               long long& fx, long long& fy, long long& fz, double* e = nullptr) {
 #pragma clang fp contract(off)
     const double dx = mi_delta(pi.x, pj.x, P.L, P.invL);
     const double dy = mi_delta(pi.y, pj.y, P.L, P.invL);
@@ -849,6 +694,7 @@ __device__ __forceinline__ void bond_force_tab(const Params& P, const StepTabs& 
             return;
         }
         f = T.bk[bt] * rcp64(g);
+        if (e) *e += 0.5 * (-0.5 * T.bk[bt] * P.bR02[bt] * log(g));
     } else if (EXT && T.bkind[bt] == 2u) {        // tether: F_i = (dU/dr) / r d
         const double r = sqrt(r2);
         if (!(r > T.blmin[bt] && r < T.blmax[bt])) {
@@ -856,16 +702,107 @@ __device__ __forceinline__ void bond_force_tab(const Params& P, const StepTabs& 
             return;
         }
         double du;
-        (void)tether_u(r, T.bk[bt], T.blmin[bt], T.blc1[bt], T.blc0[bt], T.blmax[bt], &du);
+        const double U = tether_u(r, T.bk[bt], T.blmin[bt], T.blc1[bt], T.blc0[bt], T.blmax[bt], &du);
         f = du / r;
+        if (e) *e += 0.5 * U;
     } else {                                      // harmonic: F_i = k (r - r0) / r d
         if (!(r2 > 0.0)) return;
         const double ir = rsqrt64(r2);
-        f = T.bk[bt] * (r2 * ir - T.br0[bt]) * ir;
+        const double dr = r2 * ir - T.br0[bt];
+        f = T.bk[bt] * dr * ir;
+        if (e) *e += 0.5 * (0.5 * T.bk[bt] * dr * dr);
     }
     fx += to_fix(f * dx, D.err);
     fy += to_fix(f * dy, D.err);
     fz += to_fix(f * dz, D.err);
+}
+
+// ------------------------------------------------------------ evaluation
+// Total force on particle i at positions X for the read-outs, from its
+// neighbour list (valid for X: every pair within the interaction range is
+// listed until some particle has moved by skin / 2 since the build, and the
+// step that moves it that far rebuilds the lists); optional per-particle
+// energy (half of each pair and bond energy).  Candidates are screened in
+// FP32 with a safety margin; every pair that survives is evaluated in FP64
+// with the oracle's cutoff test r < 2^(1/6) sigma_ij.  Each contribution is
+// rounded to 2^-32 and summed in 64-bit integers.  List rows, bond words and
+// the positions they name are loaded four at a time, so that a particle
+// waits for a memory round trip per four entries and not for two per entry.
+template <bool EXT>
+__device__ __forceinline__ Force3 force_eval(const Params& P, const StepTabs& T, const Dev& D,
+                                             const float4* __restrict__ X, uint32_t i, float4 pi, double* e) {
+    constexpr int Q = 4;
+    const size_t n = P.n;
+    const uint32_t ti = type_of(pi);
+    const uint32_t nstat = P.stat_max, nslot = P.stat_max + T.cap[ti];
+    long long fx = 0, fy = 0, fz = 0;
+    const uint32_t m = D.nl_cnt[i];
+    auto bond_word = [&](uint32_t b) {
+        return b < nslot ? (b < nstat ? D.stat[(size_t)b * n + i] : D.dyn[(size_t)(b - nstat) * n + i]) : kEmpty;
+    };
+    for (uint32_t k0 = 0; k0 < m; k0 += Q) {
+        uint32_t nb[Q];
+        float4 pj[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) nb[q] = D.nl[(size_t)min(k0 + (uint32_t)q, m - 1u) * n + i];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) pj[q] = X[nb[q]];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            if (k0 + (uint32_t)q >= m) break;
+            const float dx = mi_delta_f(pi.x, pj[q].x, P);
+            const float dy = mi_delta_f(pi.y, pj[q].y, P);
+            const float dz = mi_delta_f(pi.z, pj[q].z, P);
+            if (dx * dx + dy * dy + dz * dz < T.rc2_pre[(int)ti * kMaxTypes + (int)type_of(pj[q])])
+                pair_force_f64(P, T, D.err, pi, pj[q], ti, fx, fy, fz, e);
+        }
+    }
+    for (uint32_t b0 = 0; b0 < nslot; b0 += Q) {
+        uint32_t w[Q];
+        float4 pw[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) w[q] = bond_word(b0 + (uint32_t)q);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) pw[q] = X[w[q] != kEmpty ? (w[q] & kIdxMask) : i];
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (w[q] != kEmpty)
+                bond_force_tab<EXT>(P, T, D, pi, pw[q],
+                                    b0 + (uint32_t)q < nstat ? w[q] >> 24 : T.rbt[(w[q] >> 24) & 0x7Fu], i,
+                                    w[q] & kIdxMask, fx, fy, fz, e);
+    }
+    return fix_to_force(D, fx, fy, fz);
+}
+
+// Forces at the current positions.  MODE 0: into f4[off + i] (in index
+// order); 1: full-step velocities u + h F / m, 2: forces, as x, y, z triplets
+// in tag order into out3 (3 n floats).
+template <bool EXT, int MODE>
+__global__ __launch_bounds__(256) void k_eval(const Params P, const Dev D, int xin, uint32_t off,
+                                              float* __restrict__ out3) {
+    __shared__ StepTabs T;
+    stage_tabs(D, T, threadIdx.x);
+    __syncthreads();
+    const uint32_t i = xcd_block() * blockDim.x + threadIdx.x;
+    if (i >= P.n) return;
+    const float4* __restrict__ X = D.x[xin];
+    const float4 pi = X[i];
+    float4 u = make_float4(0.f, 0.f, 0.f, 0.f);
+    uint32_t tag = 0;
+    if (MODE == 1) u = D.u[i];
+    if (MODE != 0) tag = D.tag[i];
+    Force3 f = force_eval<EXT>(P, T, D, X, i, pi, nullptr);
+    if (MODE == 0) {
+        D.f4[off + i] = make_float4(f.x, f.y, f.z, 0.0f);
+        return;
+    }
+    if (MODE == 1) {
+        const float hm = T.hm[type_of(pi)];
+        f = Force3{u.x + hm * f.x, u.y + hm * f.y, u.z + hm * f.z};
+    }
+    out3[3 * (size_t)tag] = f.x;
+    out3[3 * (size_t)tag + 1] = f.y;
+    out3[3 * (size_t)tag + 2] = f.z;
 }
 
 // One BAOAB step t -> s = t + 1 over 256 / TPP particles per workgroup.
@@ -1808,38 +1745,11 @@ __global__ __launch_bounds__(256) void k_break(const Params P, const Dev D, int 
 }
 
 // ------------------------------------------------------------ I/O kernels
-// Gather index-ordered float4 (positions, u, or f4 + h F/m) into tag order.
-// mode 0: positions, 1: full-step velocities (u + h F/m, F in f4), 2: forces (f4)
-__global__ void k_gather(const Params P, const Dev D, float4* __restrict__ out, int xin, int mode) {
+// Positions as x, y, z triplets in tag order (out3 holds 3 n floats).
+__global__ void k_gather3(const Params P, const Dev D, float* __restrict__ out3, int xin) {
     const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= P.n) return;
-    const uint32_t i = D.rtag[t];
-    if (mode == 0) {
-        out[t] = D.x[xin][i];
-    } else if (mode == 1) {
-        const float hm = P.h * P.inv_mass[type_of(D.x[xin][i])];
-        const float4 u = D.u[i], f = D.f4[i];
-        out[t] = make_float4(u.x + hm * f.x, u.y + hm * f.y, u.z + hm * f.z, 0.0f);
-    } else {
-        out[t] = D.f4[i];
-    }
-}
-// The same read-outs as k_gather, as x, y, z triplets in tag order into
-// caller memory (out3 holds 3 n floats).
-__global__ void k_gather3(const Params P, const Dev D, float* __restrict__ out3, int xin, int mode) {
-    const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= P.n) return;
-    const uint32_t i = D.rtag[t];
-    float4 v;
-    if (mode == 0) {
-        v = D.x[xin][i];
-    } else if (mode == 1) {
-        const float hm = P.h * P.inv_mass[type_of(D.x[xin][i])];
-        const float4 u = D.u[i], f = D.f4[i];
-        v = make_float4(u.x + hm * f.x, u.y + hm * f.y, u.z + hm * f.z, 0.0f);
-    } else {
-        v = D.f4[i];
-    }
+    const float4 v = D.x[xin][D.rtag[t]];
     out3[3 * (size_t)t] = v.x;
     out3[3 * (size_t)t + 1] = v.y;
     out3[3 * (size_t)t + 2] = v.z;
@@ -1853,96 +1763,301 @@ __global__ void k_gather_img(const Params P, const Dev D, int32_t* __restrict__ 
     out[3 * t + 2] = D.img[2 * P.n + i];
 }
 
-// Energies and bond counts: red[0] = PE, red[1] = KE (2^-32 fixed point),
-// red[2 + a] = bonds of reaction a.
-__global__ __launch_bounds__(256) void k_observe(const Params P, const Dev D, int xin) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    __shared__ uint32_t nb[kMaxRx];
-    if (threadIdx.x < kMaxRx) nb[threadIdx.x] = 0u;
-    __syncthreads();
-    unsigned long long pe = 0, ke = 0;
-    if (i < P.n) {
-        const uint32_t ti = type_of(D.x[xin][i]);
-        const float4 f = D.f4[i];
-        const float4 u = D.u[i];
-        const float hm = P.h * P.inv_mass[ti];
-        const double vx = u.x + hm * f.x, vy = u.y + hm * f.y, vz = u.z + hm * f.z;
-        pe = (unsigned long long)rint((double)f.w * 4294967296.0);
-        ke = (unsigned long long)rint(0.5 * (double)P.mass[ti] * ((vx * vx + vy * vy) + vz * vz) * 4294967296.0);
-        const uint32_t tgi = D.tag[i];
-        for (uint32_t k = 0; k < P.cap[ti]; ++k) {
-            const uint32_t w = D.dyn[(size_t)k * P.n + i];
-            if (w == kEmpty) continue;
-            if (D.tag[w & kIdxMask] > tgi) atomicAdd(&nb[(w >> 24) & 0x7Fu], 1u);
-        }
-    }
-    for (int off = 32; off >= 1; off >>= 1) {
-        pe += __shfl_xor(pe, off, 64);
-        ke += __shfl_xor(ke, off, 64);
-    }
-    if (__lane_id() == 0) {
-        atomicAdd(&D.red[0], pe);
-        atomicAdd(&D.red[1], ke);
-    }
-    __syncthreads();
-    if (threadIdx.x < P.nrx && nb[threadIdx.x]) atomicAdd(&D.red[2 + threadIdx.x], (unsigned long long)nb[threadIdx.x]);
+// Connected components over static + dynamic bonds: a union-find forest of
+// parent words in which a root is the smallest index of its component, built
+// without locks by all threads at once.  A hook swaps a root's own index for
+// a smaller one by compare-and-swap; where that fails, another thread has
+// just hooked the same root, and the walk goes on from the parent it set.
+// Every link points to a smaller index, so walks end, and a stale parent is
+// still an ancestor, so nothing waits for another thread.  MEM: the scope of
+// the words (LDS of one workgroup, or global memory of the whole device).
+template <int MEM>
+__device__ __forceinline__ uint32_t uf_load(const uint32_t* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, MEM);
 }
-
-// Connected components over static + dynamic bonds (union by minimum index).
-__device__ __forceinline__ uint32_t cc_root(const uint32_t* parent, uint32_t v) {
-    uint32_t p = parent[v];
-    while (p != v) { v = p; p = parent[v]; }
+template <int MEM>
+__device__ __forceinline__ uint32_t uf_root(uint32_t* parent, uint32_t v) {
+    uint32_t p = uf_load<MEM>(parent + v);
+    while (p != v) {
+        const uint32_t g = uf_load<MEM>(parent + p);
+        if (g != p) __hip_atomic_store(parent + v, g, __ATOMIC_RELAXED, MEM);   // halve the path
+        v = p;
+        p = g;
+    }
     return v;
 }
-__global__ void k_cc_init(const Params P, const Dev D) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < P.n) D.parent[i] = i;
+template <int MEM>
+__device__ __forceinline__ void uf_unite(uint32_t* parent, uint32_t a, uint32_t b) {
+    a = uf_root<MEM>(parent, a);
+    b = uf_root<MEM>(parent, b);
+    while (a != b) {
+        if (a < b) {
+            const uint32_t t = a;
+            a = b;
+            b = t;
+        }
+        uint32_t seen = a;
+        if (__hip_atomic_compare_exchange_strong(parent + a, &seen, b, __ATOMIC_RELAXED, __ATOMIC_RELAXED, MEM)) return;
+        a = uf_root<MEM>(parent, seen);
+        b = uf_root<MEM>(parent, b);
+    }
 }
-__device__ __forceinline__ void cc_hook_edge(const Dev& D, uint32_t i, uint32_t j, uint32_t* changed) {
-    if (j < i) return;                     // each edge once, from its lower index
-    const uint32_t ri = cc_root(D.parent, i), rj = cc_root(D.parent, j);
-    if (ri == rj) return;
-    atomicMin(&D.parent[ri < rj ? rj : ri], ri < rj ? ri : rj);
-    *changed = 1u;
+// The bonds of particle i, each from its lower index.
+template <int MEM>
+__device__ __forceinline__ void uf_bonds(const Params& P, const Dev& D, uint32_t* parent, uint32_t i, uint32_t ti) {
+    const size_t n = P.n;
+    const uint32_t nstat = P.stat_max, nslot = P.stat_max + P.cap[ti];
+    for (uint32_t b0 = 0; b0 < nslot; b0 += 4) {
+        uint32_t w[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t b = b0 + (uint32_t)q;
+            w[q] = b < nslot ? (b < nstat ? D.stat[(size_t)b * n + i] : D.dyn[(size_t)(b - nstat) * n + i]) : kEmpty;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (w[q] != kEmpty && (w[q] & kIdxMask) > i) uf_unite<MEM>(parent, i, w[q] & kIdxMask);
+    }
 }
-__global__ void k_cc_hook(const Params P, const Dev D, uint32_t* changed, int xin) {
+
+// Count each lane's root r (lanes with `valid`) in size[].  Most particles of
+// a network belong to one component, whose counter would take one atomic per
+// particle: the two commonest-first roots of a wave are counted by one lane.
+// Returns the largest count this lane has seen (the count after its own
+// addition: the last addition to a counter sees the component's size).
+template <int MEM>
+__device__ __forceinline__ uint32_t uf_count(uint32_t* size, uint32_t r, bool valid) {
+    uint32_t most = 0;
+    for (int k = 0; k < 2; ++k) {
+        const unsigned long long todo = __ballot(valid);
+        if (!todo) return most;
+        const int leader = __ffsll((long long)todo) - 1;
+        const bool same = valid && r == (uint32_t)__shfl((int)r, leader, 64);
+        const uint32_t c = (uint32_t)__popcll(__ballot(same));
+        if ((int)__lane_id() == leader) most = __hip_atomic_fetch_add(size + r, c, __ATOMIC_RELAXED, MEM) + c;
+        valid = valid && !same;
+    }
+    if (valid) {
+        const uint32_t c = __hip_atomic_fetch_add(size + r, 1u, __ATOMIC_RELAXED, MEM) + 1u;
+        most = most > c ? most : c;
+    }
+    return most;
+}
+
+__global__ __launch_bounds__(256) void k_cc_init(const Params P, const Dev D) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= P.n) return;
-    for (uint32_t k = 0; k < P.stat_max; ++k) {
-        const uint32_t w = D.stat[(size_t)k * P.n + i];
-        if (w == kEmpty) break;
-        cc_hook_edge(D, i, w & kIdxMask, changed);
+    D.parent[i] = i;
+    D.scan[i] = 0u;
+}
+__global__ __launch_bounds__(256) void k_cc_union(const Params P, const Dev D, int xin) {
+    const uint32_t i = xcd_block() * blockDim.x + threadIdx.x;
+    if (i < P.n) uf_bonds<__HIP_MEMORY_SCOPE_AGENT>(P, D, D.parent, i, type_of(D.x[xin][i]));
+}
+
+// Where the observables of a call are reduced: kObsSlots copies of kObsWords
+// 64-bit sums (a workgroup adds to the copy of its index, so that the
+// workgroups do not queue on one address): PE and KE in 2^-32 fixed point,
+// the bonds of each reaction, the largest component.
+constexpr uint32_t kObsSlots = 64, kObsWords = 16;
+enum : int { kObsPe = 0, kObsKe = 1, kObsBonds = 2, kObsLargest = 2 + kMaxRx };
+// The answer in pinned host memory: the sums, the device error words, the
+// event counters (3 per reaction).
+constexpr uint32_t kObsErr = kObsWords, kObsCtr = kObsErr + 4, kObsOut = kObsCtr + 3 * kMaxRx;
+static_assert(kObsLargest < (int)kObsWords, "sums fit a slot");
+
+// Component sizes at the roots (D.scan), the largest one into the sums.
+__global__ __launch_bounds__(256) void k_cc_size(const Params P, const Dev D) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    constexpr int M = __HIP_MEMORY_SCOPE_AGENT;
+    uint32_t v = i < P.n ? D.parent[i] : 0u;
+    if (i < P.n) {
+        for (uint32_t p = D.parent[v]; p != v; p = D.parent[v]) v = p;   // no hook is in flight any more
     }
-    const uint32_t cap = P.cap[type_of(D.x[xin][i])];
-    for (uint32_t k = 0; k < cap; ++k) {
-        const uint32_t w = D.dyn[(size_t)k * P.n + i];
-        if (w != kEmpty) cc_hook_edge(D, i, w & kIdxMask, changed);
+    uint32_t most = uf_count<M>(D.scan, v, i < P.n);
+    for (int off = 32; off >= 1; off >>= 1) most = max(most, (uint32_t)__shfl_xor((int)most, off, 64));
+    if (__lane_id() == 0 && most)
+        atomicMax(&D.red[(blockIdx.x % kObsSlots) * kObsWords + kObsLargest], (unsigned long long)most);
+}
+
+// Energy and bonds of particle i for the observables: PE and KE in 2^-32
+// fixed point, its bonds to higher tags counted per reaction in nb.
+template <bool EXT>
+__device__ __forceinline__ void observe_site(const Params& P, const StepTabs& T, const Dev& D,
+                                             const float4* __restrict__ X, uint32_t i, unsigned long long& pe,
+                                             unsigned long long& ke, uint32_t* nb) {
+    const float4 pi = X[i];
+    const float4 u = D.u[i];
+    const uint32_t ti = type_of(pi), tgi = __float_as_uint(u.w);
+    double e = 0.0;
+    const Force3 f = force_eval<EXT>(P, T, D, X, i, pi, &e);
+    const float hm = T.hm[ti];
+    const double vx = u.x + hm * f.x, vy = u.y + hm * f.y, vz = u.z + hm * f.z;
+    pe += (unsigned long long)rint((double)(float)e * 4294967296.0);
+    ke += (unsigned long long)rint(0.5 * (double)T.mass[ti] * ((vx * vx + vy * vy) + vz * vz) * 4294967296.0);
+    const size_t n = P.n;
+    const uint32_t cap = T.cap[ti];
+    for (uint32_t b0 = 0; b0 < cap; b0 += 4) {
+        uint32_t w[4], tj[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) w[q] = b0 + (uint32_t)q < cap ? D.dyn[(size_t)(b0 + (uint32_t)q) * n + i] : kEmpty;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) tj[q] = D.tag[w[q] != kEmpty ? (w[q] & kIdxMask) : i];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (tj[q] > tgi) atomicAdd(&nb[(w[q] >> 24) & 0x7Fu], 1u);
     }
 }
-__global__ void k_cc_compress(const Params P, const Dev D) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < P.n) D.parent[i] = cc_root(D.parent, i);
+
+__device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
+    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
 }
-__global__ void k_cc_size(const Params P, const Dev D) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < P.n) atomicAdd(&D.scan[D.parent[i]], 1u);
+
+// The spread event counters summed into the answer (whole waves call this
+// together).
+__device__ __forceinline__ void observe_counters(const Params& P, const Dev& D, unsigned long long* out) {
+    const uint32_t lane = __lane_id();
+    for (uint32_t c = threadIdx.x >> 6; c < 3 * P.nrx; c += blockDim.x >> 6) {
+        unsigned long long v = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < kCtrSlots / 64; ++k) v += D.counters[(size_t)c * kCtrSlots + k * 64 + lane];
+        v = wave_sum(v);
+        if (lane == 0) out[kObsCtr + c] = v;
+    }
 }
-__global__ void k_cc_max(const Params P, const Dev D) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < P.n && D.scan[i]) atomicMax((unsigned long long*)&D.red[2 + kMaxRx], (unsigned long long)D.scan[i]);
+
+// Every observable of a small system in one workgroup, the answer written
+// straight to pinned host memory: a parameter sweep reads the observables of
+// every replica after each span, and launches, not work, are what that costs
+// (25 launches and 4 to 5 waits per system before, 310 us a call; one and one
+// now, 15 to 30 us of kernel at 256 to 4096 particles).  Components are built
+// in LDS (n parent words, dynamic).  Above kObsOneMaxN particles one CU is
+// slower than four launches over the chip (74 against about 40 us at 8000).
+constexpr uint32_t kObsOneMaxN = 4096;
+constexpr uint32_t kObsOneThreads = 1024;
+template <bool EXT>
+__global__ __launch_bounds__(1024) void k_observe_one(const Params P, const Dev D, int xin,
+                                                      unsigned long long* __restrict__ out) {
+    __shared__ StepTabs T;
+    __shared__ unsigned long long sum[2];
+    __shared__ uint32_t nb[kMaxRx], largest;
+    extern __shared__ uint32_t uf[];
+    constexpr int M = __HIP_MEMORY_SCOPE_WORKGROUP;
+    constexpr uint32_t kPer = kObsOneMaxN / kObsOneThreads;
+    const uint32_t tid = threadIdx.x, n = P.n;
+    stage_tabs(D, T, tid);
+    if (tid < kMaxRx) nb[tid] = 0u;
+    if (tid < 2) sum[tid] = 0ull;
+    if (tid == 0) largest = 0u;
+    for (uint32_t i = tid; i < n; i += kObsOneThreads) uf[i] = i;
+    __syncthreads();
+    const float4* __restrict__ X = D.x[xin];
+    unsigned long long pe = 0, ke = 0;
+    for (uint32_t i = tid; i < n; i += kObsOneThreads) {
+        observe_site<EXT>(P, T, D, X, i, pe, ke, nb);
+        uf_bonds<M>(P, D, uf, i, type_of(X[i]));
+    }
+    pe = wave_sum(pe);
+    ke = wave_sum(ke);
+    if (__lane_id() == 0) {
+        atomicAdd(&sum[0], pe);
+        atomicAdd(&sum[1], ke);
+    }
+    observe_counters(P, D, out);
+    __syncthreads();
+    uint32_t r[kPer];
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k) {
+        const uint32_t i = tid + k * kObsOneThreads;
+        r[k] = i < n ? uf_root<M>(uf, i) : 0u;
+    }
+    __syncthreads();
+    for (uint32_t i = tid; i < n; i += kObsOneThreads) uf[i] = 0u;
+    __syncthreads();
+    uint32_t most = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k)
+        if (k * kObsOneThreads < n) most = max(most, uf_count<M>(uf, r[k], tid + k * kObsOneThreads < n));
+    atomicMax(&largest, most);
+    __syncthreads();
+    if (tid < 2) out[tid] = sum[tid];
+    if (tid < kMaxRx) out[kObsBonds + tid] = nb[tid];
+    if (tid == 0) out[kObsLargest] = largest;
+    if (tid < 4) out[kObsErr + tid] = __hip_atomic_load(&D.err[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The same over the whole chip, for larger systems: energies, velocities and
+// bond counts into the sums, and the component words set up.
+template <bool EXT>
+__global__ __launch_bounds__(256) void k_observe(const Params P, const Dev D, int xin) {
+    __shared__ StepTabs T;
+    __shared__ unsigned long long sum[2];
+    __shared__ uint32_t nb[kMaxRx];
+    stage_tabs(D, T, threadIdx.x);
+    if (threadIdx.x < kMaxRx) nb[threadIdx.x] = 0u;
+    if (threadIdx.x < 2) sum[threadIdx.x] = 0ull;
+    __syncthreads();
+    const uint32_t i = xcd_block() * blockDim.x + threadIdx.x;
+    unsigned long long pe = 0, ke = 0;
+    if (i < P.n) {
+        observe_site<EXT>(P, T, D, D.x[xin], i, pe, ke, nb);
+        D.parent[i] = i;
+        D.scan[i] = 0u;
+    }
+    pe = wave_sum(pe);
+    ke = wave_sum(ke);
+    if (__lane_id() == 0) {
+        atomicAdd(&sum[0], pe);
+        atomicAdd(&sum[1], ke);
+    }
+    __syncthreads();
+    unsigned long long* red = D.red + (size_t)(blockIdx.x % kObsSlots) * kObsWords;
+    if (threadIdx.x < 2) atomicAdd(&red[threadIdx.x], sum[threadIdx.x]);
+    if (threadIdx.x < P.nrx && nb[threadIdx.x])
+        atomicAdd(&red[kObsBonds + threadIdx.x], (unsigned long long)nb[threadIdx.x]);
+}
+
+// The answer from the sums, which are left cleared for the next call.
+__global__ __launch_bounds__(1024) void k_observe_sum(const Params P, const Dev D, unsigned long long* __restrict__ out) {
+    static_assert(kObsSlots == 64, "one wave per sum");
+    const uint32_t w = threadIdx.x >> 6, lane = __lane_id();
+    unsigned long long v = D.red[(size_t)lane * kObsWords + w];
+    D.red[(size_t)lane * kObsWords + w] = 0ull;
+    if (w == (uint32_t)kObsLargest) {
+        for (int off = 32; off >= 1; off >>= 1) {
+            const unsigned long long o = __shfl_xor(v, off, 64);
+            v = o > v ? o : v;
+        }
+    } else {
+        v = wave_sum(v);
+    }
+    if (lane == 0) out[w] = v;
+    observe_counters(P, D, out);
+    if (threadIdx.x < 4) out[kObsErr + threadIdx.x] = D.err[threadIdx.x];
 }
 
 // ------------------------------------------------------------ network analyses
 // Clusters of size k (k < len) in hist[k - 1], larger ones in hist[len - 1];
 // D.scan holds each root's cluster size (k_cc_size).
-__global__ void k_cc_hist(const Params P, const Dev D, unsigned long long* hist, uint32_t len,
-                          unsigned long long* n_clusters) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= P.n) return;
-    const uint32_t k = D.scan[i];
-    if (k == 0u) return;
-    atomicAdd(&hist[(k < len ? k : len) - 1u], 1ull);
-    atomicAdd(n_clusters, 1ull);
+// Each workgroup counts in LDS first: with one global atomic per cluster, the
+// few common sizes queued on their words (691 us at 200k particles).
+constexpr uint32_t kHistMax = 256;
+__global__ __launch_bounds__(256) void k_cc_hist(const Params P, const Dev D, unsigned long long* hist, uint32_t len,
+                                                 unsigned long long* n_clusters) {
+    __shared__ uint32_t h[kHistMax], all;
+    h[threadIdx.x] = 0u;
+    if (threadIdx.x == 0) all = 0u;
+    __syncthreads();
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < P.n; i += gridDim.x * blockDim.x) {
+        const uint32_t k = D.scan[i];
+        if (k == 0u) continue;
+        atomicAdd(&h[(k < len ? k : len) - 1u], 1u);
+        atomicAdd(&all, 1u);
+    }
+    __syncthreads();
+    if (h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], (unsigned long long)h[threadIdx.x]);
+    if (threadIdx.x == 0 && all) atomicAdd(n_clusters, (unsigned long long)all);
 }
 
 // Reference bond table for the bond correlation, by tag: slot c of tag t

@@ -1,0 +1,52 @@
+"""Observables at the edges of the one-workgroup kernel (at most 4096
+particles) and of its 1024 threads, against values worked out from the
+read-outs: bond counts, bonded fraction, clusters and kinetic energy."""
+
+import numpy as np
+import pytest
+
+from paper_2609_21204_amd import dybond as db
+from paper_2609_21204_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def component_sizes(n, pairs):
+    parent = list(range(n))
+
+    def find(v):
+        while parent[v] != v:
+            parent[v] = parent[parent[v]]
+            v = parent[v]
+        return v
+
+    for a, b in pairs:
+        ra, rb = find(int(a)), find(int(b))
+        if ra != rb:
+            parent[max(ra, rb)] = min(ra, rb)
+    return np.bincount(np.bincount([find(v) for v in range(n)], minlength=n), minlength=2)
+
+
+@pytest.mark.parametrize("n, kind", [(63, "mono"), (1024, "mono"), (1025, "mono"), (4096, "mono"), (4097, "mono"),
+                                     (3000, "chains"), (6000, "chains")])
+def test_observables_match_the_read_outs(n, kind):
+    w = inputs.replica(11, n, 9.0, 0.3, 2, kind)
+    with db.System.from_workload(w) as s:
+        s.step(200)
+        o, bonds, vel = s.observables(), s.bonds(), s.velocities().astype(np.float64)
+        again = s.observables()
+        hist, clusters = db.db_cluster_sizes(s.h, 256)
+    assert o["n_bonds"][0] == len(bonds) > 0
+    assert o["forms"][0] - o["breaks"][0] == len(bonds)
+    t = w.reactions[0]["type_a"], w.reactions[0]["type_b"]
+    caps = [w.types[k][0] * int(np.sum(w.type_id == k)) for k in t]
+    assert o["bonded_fraction"][0] == len(bonds) / min(caps)
+    # the kinetic energy is a sum of n terms, each rounded to 2^-32
+    assert abs(o["KE"] - 0.5 * np.sum(vel * vel)) <= w.n * 2.0 ** -32
+    sizes = component_sizes(w.n, np.concatenate([bonds[:, :2], w.static_pairs]))
+    assert o["largest_cluster_fraction"] == (len(sizes) - 1) / w.n
+    want = np.zeros(256, dtype=np.int64)
+    np.add.at(want, np.minimum(np.arange(1, len(sizes)), 256) - 1, sizes[1:])
+    assert np.array_equal(hist, want) and clusters == sizes[1:].sum()
+    for k in o:
+        assert np.array_equal(o[k], again[k]), k
