@@ -108,7 +108,7 @@ __device__ __forceinline__ Force3 force_site(const Params& P, const StepTabs& T,
     uint32_t defer = 0u;
 #pragma unroll
     for (int q = 0; q < QL; ++q)
-        if ((uint32_t)q < m && !pair_force_f32(P, T, D.err, pi, pj[q], ti, fx, fy, fz)) defer |= 1u << q;
+        if (pair_force_f32(P, T, D.err, pi, pj[q], ti, (uint32_t)q < m, fx, fy, fz)) defer |= 1u << q;
     for (uint32_t k0 = QL; k0 < m; k0 += 8) {
         uint32_t nx[8];
         float4 px[8];
@@ -119,7 +119,7 @@ __device__ __forceinline__ Force3 force_site(const Params& P, const StepTabs& T,
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const uint32_t k = k0 + (uint32_t)q;
-            if (k < m && !pair_force_f32(P, T, D.err, pi, px[q], ti, fx, fy, fz)) {
+            if (pair_force_f32(P, T, D.err, pi, px[q], ti, k < m, fx, fy, fz)) {
                 if (k < 32u) defer |= 1u << k;
                 else pair_force_f64(P, T, D.err, pi, px[q], ti, fx, fy, fz);
             }
@@ -134,8 +134,7 @@ __device__ __forceinline__ Force3 force_site(const Params& P, const StepTabs& T,
     }
     auto bond = [&](uint32_t b, uint32_t w, float4 pw) {
         const uint32_t j = w & kIdxMask;
-        if (b < nstat) bond_force_tab<EXT>(P, T, D, pi, pw, w >> 24, i, j, fx, fy, fz);
-        else bond_force_tab<EXT>(P, T, D, pi, pw, T.rbt[(w >> 24) & 0x7Fu], i, j, fx, fy, fz);
+        bond_force_tab<EXT>(P, T, D, pi, pw, b < nstat ? w >> 24 : T.rbt[(w >> 24) & 0x7Fu], i, j, fx, fy, fz);
     };
 #pragma unroll
     for (int q = 0; q < QB; ++q)

@@ -209,6 +209,7 @@ struct Params {
     uint32_t seed, period, kt_kinetic, any_self_avoid;
     double L, invL;
     float Lf, halfLf, cell_scale, h;   // h = dt / 2
+    float invLf;                       // 1 / Lf, rounded once
     float c1;                          // exp(-gamma dt)
     uint32_t tpp;                      // threads per particle in k_propose (host side: launch shape)
     uint32_t tpp_step;                 // threads per particle in k_step
@@ -259,8 +260,7 @@ struct PairTab {
 // with lane-varying types, which from the kernel-argument block would be one
 // more dependent memory round trip per neighbour.
 struct alignas(16) StepTabs {
-    float rc2_pre[kMaxTypes * kMaxTypes], rc2_in[kMaxTypes * kMaxTypes];
-    float sig2f[kMaxTypes * kMaxTypes], eps24f[kMaxTypes * kMaxTypes];
+    float4 pf[kMaxTypes * kMaxTypes];   // what the FP32 pair force reads: rc2_pre, rc2_in, sig2f, eps24f of Params
     float rl2[kMaxTypes * kMaxTypes];   // neighbour-list radius^2 of the type pair
     PairTab pair[kMaxTypes * kMaxTypes];
     double bk[kMaxBondTypes], br0[kMaxBondTypes], binvR02[kMaxBondTypes];
@@ -347,16 +347,30 @@ __device__ __forceinline__ size_t cell_slot(const Params& P, uint32_t c, uint32_
     return (size_t)k * P.ncell + c;
 }
 
-// Round v * 2^32 to the nearest integer (ties to even) with one FMA: adding
-// 1.5 * 2^52 leaves round(v * 2^32) in the low mantissa bits.  Exact for
-// |v| < 2^19; larger contributions are clamped and flagged.
-__device__ __forceinline__ long long to_fix(double v, uint32_t* err) {
-    constexpr double kMagic = 6755399441055744.0;   // 1.5 * 2^52
-    if (!(fabs(v) < 524288.0)) {
-        atomicOr(err, kErrForce);
-        v = v > 0.0 ? 524287.0 : -524287.0;
-    }
-    return __double_as_longlong(fma(v, 4294967296.0, kMagic)) - __double_as_longlong(kMagic);
+// Fixed-point force sums.  A contribution v is rounded to the nearest
+// multiple of 2^-32 (ties to even) with one FMA: v 2^32 + 1.5 2^52 leaves
+// round(v 2^32) in the low mantissa bits.  Exact for |v| < 2^19; larger
+// contributions are clamped and flagged (fix_clamp), which one test per
+// contribution vector decides (fix_out): a branch for every component cost
+// the force loops more issue slots than their arithmetic.
+constexpr double kFixMagic = 6755399441055744.0;   // 1.5 * 2^52
+constexpr double kFixLimit = 524288.0;
+__device__ __forceinline__ long long fix_of(double v) {
+    return __double_as_longlong(fma(v, 4294967296.0, kFixMagic)) - __double_as_longlong(kFixMagic);
+}
+__device__ __forceinline__ bool fix_out(double x, double y, double z) {
+    return !(fmax(fmax(fabs(x), fabs(y)), fabs(z)) < kFixLimit);
+}
+__device__ __forceinline__ bool fix_out(float x, float y, float z) {
+    return !(fmaxf(fmaxf(fabsf(x), fabsf(y)), fabsf(z)) < (float)kFixLimit);
+}
+template <class T>
+__device__ __forceinline__ void fix_clamp(T& x, T& y, T& z, uint32_t* err) {
+    atomicOr(err, kErrForce);
+    auto clamp = [](T v) { return fabs(v) < (T)kFixLimit ? v : (v > (T)0 ? (T)524287 : (T)-524287); };
+    x = clamp(x);
+    y = clamp(y);
+    z = clamp(z);
 }
 
 // 1/x and 1/sqrt(x) in FP64 from the hardware estimates plus two Newton
@@ -379,7 +393,7 @@ __device__ __forceinline__ double rsqrt64(double x) {
 // the exact FP64 evaluation (its error, ~1e-5, is far below the margins).
 __device__ __forceinline__ float mi_delta_f(float xi, float xj, const Params& P) {
     float d = xj - xi;
-    if (fabsf(d) > P.halfLf) d -= P.Lf * rintf(d * (1.0f / P.Lf));
+    if (fabsf(d) > P.halfLf) d -= P.Lf * rintf(d * P.invLf);
     return d;
 }
 

@@ -490,10 +490,7 @@ void fill_tabs(const db_system* s, StepTabs& th) {
     const Params& P = s->P;
     th = StepTabs{};
     for (int k = 0; k < kMaxTypes * kMaxTypes; ++k) {
-        th.rc2_pre[k] = P.rc2_pre[k];
-        th.rc2_in[k] = P.rc2_in[k];
-        th.sig2f[k] = P.sig2f[k];
-        th.eps24f[k] = P.eps24f[k];
+        th.pf[k] = make_float4(P.rc2_pre[k], P.rc2_in[k], P.sig2f[k], P.eps24f[k]);
         th.rl2[k] = P.rl2[k];
         th.pair[k] = s->pair_h[k];
     }
@@ -559,6 +556,7 @@ void fill_params(db_system* s) {
     P.invL = 1.0 / s->L;
     P.Lf = (float)s->L;
     P.halfLf = (float)(0.5 * s->L);
+    P.invLf = 1.0f / P.Lf;
     P.h = (float)(0.5 * s->dt);
     const double c1 = std::exp(-s->gamma * s->dt);
     P.c1 = (float)c1;
