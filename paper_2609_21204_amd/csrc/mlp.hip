@@ -7,7 +7,9 @@
 // 16 x 16 output tile; the 4-wide input layer, the 2-wide output layer, the
 // bias and weight reductions over the minibatch and Adam are plain FP32
 // lanes.  Reductions run over the minibatch in a fixed order, so a training
-// run is reproducible bit for bit.
+// run is reproducible bit for bit.  An Adam step is two launches: the rows
+// (k_mlp_rows: everything that stays inside 16 rows) and the parameters
+// (k_mlp_grads: everything that reduces over all rows).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -55,116 +57,187 @@ struct Net {
     float* v;          // Adam second moments
     float* g;          // gradient
     uint16_t* wb;      // bf16 copy of the parameter vector (weights used; biases unused)
-    // minibatch (bp rows, bp a multiple of 16) and intermediates
+    uint16_t* w2t;     // bf16 W2 transposed (k, h), for the layer's backward pass
+    // minibatch of bp rows (a multiple of 16): what its gradients reduce over
     float* x;          // bp x 4
-    float* t;          // bp x 2
-    float* z1;         // bp x 128
-    uint16_t* a1b;     // bp x 128, bf16 SiLU(z1)
-    float* z2;         // bp x 128
     float* a2;         // bp x 128
-    float* y;          // bp x 2
     float* dz3;        // bp x 2
     float* dz2;        // bp x 128
-    uint16_t* dz2b;    // bp x 128
     float* dz1;        // bp x 128
-    float* loss;       // [0] loss of the last full evaluation
+    uint16_t* a1t;     // 128 x ld, bf16 SiLU(z1) transposed
+    uint16_t* dz2t;    // 128 x ld, bf16 dz2 transposed
+    uint32_t ld;       // rows the transposed arrays have room for
 };
 
-// One 16 x 16 tile of C = A B with bf16 operands and FP32 accumulation on
-// the matrix cores.  A(m, k) = a[m * sam + k * sak], B(k, n) = b[k * sbk + n * sbn]
-// for m, n < 16 (tile origin folded into the pointers) and k < K (a
-// multiple of 16).  Lane l supplies A(l % 16, 4 (l / 16) + j) and
-// B(4 (l / 16) + j, l % 16), j = 0..3, and receives C(4 (l / 16) + j, l % 16).
-__device__ __forceinline__ f32x4 mfma_tile(const uint16_t* a, int sam, int sak, const uint16_t* b, int sbk,
-                                           int sbn, int K) {
-    const int l = (int)(threadIdx.x & 63u);
-    const int r = l & 15, kq = (l >> 4) * 4;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        bf16x4 av, bv;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            av[j] = (short)a[r * sam + (k0 + kq + j) * sak];
-            bv[j] = (short)b[(k0 + kq + j) * sbk + r * sbn];
-        }
-        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, acc, 0, 0, 0);
-    }
-    return acc;
+// bf16 copies of the weight matrices (biases are read in FP32), W2 also
+// transposed.
+__device__ __forceinline__ void round_param(const Net& N, uint32_t k, float p) {
+    const uint16_t b = to_bf16(p);
+    N.wb[k] = b;
+    if (k >= kW2 && k < kB2) N.w2t[((k - kW2) % kHid) * kHid + (k - kW2) / kHid] = b;
 }
-
-// bf16 copies of the three weight matrices (biases are read in FP32).
 __global__ void k_mlp_round(Net N) {
     const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < kNP) N.wb[k] = to_bf16(N.p[k]);
+    if (k < kNP) round_param(N, k, N.p[k]);
 }
 
-// rows [0, bp) of the minibatch gathered from the full data set by index
-// (rows at or past nb are zero inputs whose outputs are ignored)
-__global__ void k_mlp_gather(Net N, const float* __restrict__ X, const float* __restrict__ Tt,
-                             const uint32_t* __restrict__ idx, uint32_t nb, uint32_t bp) {
-    const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= bp) return;
-    const uint32_t r = b < nb ? idx[b] : 0u;
+// One tile of 16 rows through the whole network, and with BACK back again
+// down to dz1, in one workgroup of 8 waves.  Wave w owns the hidden units
+// [16 w, 16 w + 16) in both hidden layers, in the output layout of the matrix
+// cores (lane l holds rows 4 (l / 16) + j, j < 4, of unit 16 w + l % 16), so
+// that the pre-activations z1 and z2 stay in the registers of the lane that
+// needs them again in the backward pass and only bf16 operands and the
+// 2-wide output layer go through LDS.  v_mfma_f32_16x16x16_bf16: lane l
+// supplies A(l % 16, 4 (l / 16) + j) and B(4 (l / 16) + j, l % 16) as 8
+// contiguous bytes each.  With a kernel per layer a minibatch cost 10
+// launches, 160 us, at 256 rows; the layers of a tile depend on nothing
+// outside it.  A workgroup takes the tiles blockIdx, blockIdx + grid, ...,
+// and keeps its W2 fragments in registers over them.
+// Rows come from X (and targets from Tt) by idx, or in order when idx is
+// null; rows at or past nb are zeros whose outputs are ignored.
+constexpr int kRowTile = 16, kRowThreads = 512;
+constexpr int kLdA = kHid + 8;        // bf16 row stride in LDS (8-byte aligned, rows on other banks)
+constexpr int kLdF = kHid + 4;        // FP32 row stride in LDS
+template <bool BACK>
+__global__ __launch_bounds__(kRowThreads) void k_mlp_rows(Net N, const float* __restrict__ X,
+                                                          const float* __restrict__ Tt,
+                                                          const uint32_t* __restrict__ idx, uint32_t nb,
+                                                          uint32_t tiles, float* __restrict__ y_out) {
+    __shared__ float4 xs[kRowTile];
+    __shared__ float2 ts[kRowTile], dz3s[kRowTile];
+    __shared__ __attribute__((aligned(16))) uint16_t ab[kRowTile * kLdA];
+    __shared__ __attribute__((aligned(16))) uint16_t db[kRowTile * kLdA];
+    __shared__ __attribute__((aligned(16))) float a2s[kRowTile * kLdF];
+    __shared__ __attribute__((aligned(16))) float w3s[kOut * kHid];
+    const int tid = (int)threadIdx.x, l = tid & 63, r = l & 15, q4 = (l >> 4) * 4;
+    const uint32_t h = (uint32_t)(tid >> 6) * 16u + (uint32_t)r;       // this lane's hidden unit
+    // what depends on the weights alone
+    bf16x4 w2f[kHid / 16];
 #pragma unroll
-    for (int k = 0; k < kIn; ++k) N.x[b * kIn + k] = b < nb ? X[(size_t)r * kIn + k] : 0.0f;
-    if (Tt)
+    for (int k = 0; k < kHid / 16; ++k)
+        w2f[k] = *reinterpret_cast<const bf16x4*>(N.wb + kW2 + h * kHid + k * 16 + q4);
+    const bf16x4 w1 = *reinterpret_cast<const bf16x4*>(N.wb + kW1 + h * kIn);
+    const float b1 = N.p[kB1 + h], b2 = N.p[kB2 + h];
+    if (tid < kOut * kHid) w3s[tid] = from_bf16(N.wb[kW3 + tid]);
+    for (uint32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const uint32_t row0 = tile * kRowTile;
+        __syncthreads();                 // the last tile's LDS is free
+        if (tid < kRowTile) {
+            const uint32_t b = row0 + (uint32_t)tid;
+            const uint32_t src = b < nb ? (idx ? idx[b] : b) : 0u;
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (b < nb) v = reinterpret_cast<const float4*>(X)[src];
+            xs[tid] = v;
+            if (BACK) {
+                reinterpret_cast<float4*>(N.x)[b] = v;
+                float2 t = make_float2(0.f, 0.f);
+                if (b < nb) t = reinterpret_cast<const float2*>(Tt)[src];
+                ts[tid] = t;
+            }
+        }
+        __syncthreads();
+        // layer 1: z1 = W1 x + b1, a1 = SiLU(z1) rounded to bf16
+        float z1[4];
+        bf16x4 a1;
 #pragma unroll
-        for (int k = 0; k < kOut; ++k) N.t[b * kOut + k] = b < nb ? Tt[(size_t)r * kOut + k] : 0.0f;
-}
-
-// layer 1: z1 = W1 x + b1, a1 = SiLU(z1) rounded to bf16
-__global__ void k_mlp_fwd1(Net N, uint32_t bp) {
-    const uint32_t e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= bp * kHid) return;
-    const uint32_t b = e / kHid, h = e % kHid;
-    float z = N.p[kB1 + h];
+        for (int j = 0; j < 4; ++j) {
+            const float4 x = xs[q4 + j];
+            float z = b1;
+            z = fmaf(from_bf16((uint16_t)w1[0]), x.x, z);
+            z = fmaf(from_bf16((uint16_t)w1[1]), x.y, z);
+            z = fmaf(from_bf16((uint16_t)w1[2]), x.z, z);
+            z = fmaf(from_bf16((uint16_t)w1[3]), x.w, z);
+            z1[j] = z;
+            a1[j] = (short)to_bf16(siluf_(z));
+            ab[(q4 + j) * kLdA + h] = (uint16_t)a1[j];
+        }
+        if (BACK) *reinterpret_cast<bf16x4*>(N.a1t + (size_t)h * N.ld + row0 + q4) = a1;
+        __syncthreads();
+        // layer 2 on the matrix cores: z2(b, h) = sum_k a1(b, k) W2(h, k) + b2(h)
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int k = 0; k < kIn; ++k) z = fmaf(from_bf16(N.wb[kW1 + h * kIn + k]), N.x[b * kIn + k], z);
-    N.z1[e] = z;
-    N.a1b[e] = to_bf16(siluf_(z));
-}
-
-// layer 2 on the matrix cores: z2(b, h) = sum_k a1(b, k) W2(h, k) + b2(h);
-// one wave per 16 x 16 tile of (b, h)
-__global__ void k_mlp_fwd2(Net N, uint32_t bp) {
-    const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const uint32_t ntn = kHid / 16;
-    if (wave >= (bp / 16) * ntn) return;
-    const uint32_t bm = (wave / ntn) * 16, hn = (wave % ntn) * 16;
-    const f32x4 acc = mfma_tile(N.a1b + bm * kHid, kHid, 1, N.wb + kW2 + hn * kHid, 1, kHid, kHid);
-    const int l = (int)(threadIdx.x & 63u);
-    const uint32_t h = hn + (l & 15);
+        for (int k = 0; k < kHid / 16; ++k)
+            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
+                *reinterpret_cast<const bf16x4*>(ab + r * kLdA + k * 16 + q4), w2f[k], acc, 0, 0, 0);
+        float z2[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const uint32_t b = bm + (l >> 4) * 4 + j;
-        const float z = acc[j] + N.p[kB2 + h];
-        N.z2[b * kHid + h] = z;
-        N.a2[b * kHid + h] = siluf_(z);
+        for (int j = 0; j < 4; ++j) {
+            z2[j] = acc[j] + b2;
+            const float a = siluf_(z2[j]);
+            a2s[(q4 + j) * kLdF + h] = a;
+            if (BACK) N.a2[(size_t)(row0 + q4 + j) * kHid + h] = a;
+        }
+        __syncthreads();
+        // layer 3: y = sigmoid(W3 a2 + b3); dz3 = dL/dz3 for the mean-squared
+        // error over the nb valid rows
+        if (tid < kRowTile * kOut) {
+            const uint32_t b = row0 + (uint32_t)(tid / kOut);
+            const int o = tid % kOut;
+            const f32x4* a = reinterpret_cast<const f32x4*>(a2s + (tid / kOut) * kLdF);
+            const f32x4* w = reinterpret_cast<const f32x4*>(w3s + o * kHid);
+            float z = N.p[kB3 + o];
+            // (a serial chain: its LDS reads are issued 32 units ahead)
+#pragma unroll
+            for (int k0 = 0; k0 < kHid / 4; k0 += 8) {
+                f32x4 av[8], wv[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    av[k] = a[k0 + k];
+                    wv[k] = w[k0 + k];
+                }
+#pragma unroll
+                for (int k = 0; k < 32; ++k) z = fmaf(wv[k / 4][k % 4], av[k / 4][k % 4], z);
+            }
+            const float y = sigmoidf_(z);
+            if (y_out && b < nb) y_out[(size_t)b * kOut + o] = y;
+            if (BACK) {
+                const float t = o ? ts[tid / kOut].y : ts[tid / kOut].x;
+                const float dy = b < nb ? 2.0f * (y - t) / (float)(nb * kOut) : 0.0f;
+                const float d = dy * y * (1.0f - y);
+                reinterpret_cast<float*>(dz3s)[tid] = d;
+                N.dz3[(size_t)b * kOut + o] = d;
+            }
+        }
+        if (!BACK) continue;
+        __syncthreads();
+        // back through layer 3: dz2 = (dz3 W3) * SiLU'(z2), kept in FP32 and bf16
+        bf16x4 d2;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float2 d3 = dz3s[q4 + j];
+            float da = fmaf(d3.x, w3s[h], 0.0f);
+            da = fmaf(d3.y, w3s[kHid + h], da);
+            const float dz = da * dsiluf_(z2[j]);
+            d2[j] = (short)to_bf16(dz);
+            db[(q4 + j) * kLdA + h] = (uint16_t)d2[j];
+            N.dz2[(size_t)(row0 + q4 + j) * kHid + h] = dz;
+        }
+        *reinterpret_cast<bf16x4*>(N.dz2t + (size_t)h * N.ld + row0 + q4) = d2;
+        __syncthreads();
+        // da1(b, k) = sum_h dz2(b, h) W2(h, k) on the matrix cores, then
+        // dz1 = da1 * SiLU'(z1)
+        f32x4 da1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < kHid / 16; ++k)
+            da1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
+                *reinterpret_cast<const bf16x4*>(db + r * kLdA + k * 16 + q4),
+                *reinterpret_cast<const bf16x4*>(N.w2t + h * kHid + k * 16 + q4), da1, 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) N.dz1[(size_t)(row0 + q4 + j) * kHid + h] = da1[j] * dsiluf_(z1[j]);
     }
 }
 
-// layer 3: y = sigmoid(W3 a2 + b3); with targets, dz3 = dL/dz3 for the
-// mean-squared error over the nb valid rows
-__global__ void k_mlp_fwd3(Net N, uint32_t bp, uint32_t nb, int with_grad) {
-    const uint32_t e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= bp * kOut) return;
-    const uint32_t b = e / kOut, o = e % kOut;
-    float z = N.p[kB3 + o];
-    for (int h = 0; h < kHid; ++h) z = fmaf(from_bf16(N.wb[kW3 + o * kHid + h]), N.a2[b * kHid + h], z);
-    const float y = sigmoidf_(z);
-    N.y[e] = y;
-    if (with_grad) {
-        const float dy = b < nb ? 2.0f * (y - N.t[e]) / (float)(nb * kOut) : 0.0f;
-        N.dz3[e] = dy * y * (1.0f - y);
-    }
-}
-
-// mean-squared error of the nb valid rows (one workgroup, fixed order)
-__global__ __launch_bounds__(256) void k_mlp_loss(Net N, uint32_t nb) {
+// mean-squared error of each run of `chunk` rows of y against t (one
+// workgroup per run, fixed order)
+__global__ __launch_bounds__(256) void k_mlp_loss(const float* __restrict__ y, const float* __restrict__ t,
+                                                  uint32_t n, uint32_t chunk, float* __restrict__ loss) {
     __shared__ float part[256];
+    const uint32_t r0 = blockIdx.x * chunk, nb = min(chunk, n - r0);
+    y += (size_t)r0 * kOut;
+    t += (size_t)r0 * kOut;
     float s = 0.0f;
     for (uint32_t e = threadIdx.x; e < nb * kOut; e += 256) {
-        const float d = N.y[e] - N.t[e];
+        const float d = y[e] - t[e];
         s = fmaf(d, d, s);
     }
     part[threadIdx.x] = s;
@@ -173,101 +246,159 @@ __global__ __launch_bounds__(256) void k_mlp_loss(Net N, uint32_t nb) {
         if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) N.loss[0] = part[0] / (float)(nb * kOut);
+    if (threadIdx.x == 0) loss[blockIdx.x] = part[0] / (float)(nb * kOut);
 }
 
-// back through layer 3: dz2 = (dz3 W3) * SiLU'(z2), kept in FP32 and bf16
-__global__ void k_mlp_bwd3(Net N, uint32_t bp) {
-    const uint32_t e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= bp * kHid) return;
-    const uint32_t b = e / kHid, h = e % kHid;
-    float da = 0.0f;
-#pragma unroll
-    for (int o = 0; o < kOut; ++o) da = fmaf(N.dz3[b * kOut + o], from_bf16(N.wb[kW3 + o * kHid + h]), da);
-    const float dz = da * dsiluf_(N.z2[e]);
-    N.dz2[e] = dz;
-    N.dz2b[e] = to_bf16(dz);
+// What Adam holds for parameter k, read before the gradient is there.
+struct AdamState { float p, m, v; };
+template <bool ADAM>
+__device__ __forceinline__ AdamState adam_state(const Net& N, uint32_t k) {
+    return ADAM ? AdamState{N.p[k], N.m[k], N.v[k]} : AdamState{0.0f, 0.0f, 0.0f};
 }
-
-// parameter gradients that reduce over the minibatch in FP32, one thread
-// per parameter: W3, b3, b2 (and, after the layer-2 GEMMs, W1, b1)
-__global__ void k_mlp_grad3(Net N, uint32_t bp) {
-    const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < kOut * kHid) {                                // dW3(o, h) = sum_b dz3(b, o) a2(b, h)
-        const uint32_t o = k / kHid, h = k % kHid;
-        float s = 0.0f;
-        for (uint32_t b = 0; b < bp; ++b) s = fmaf(N.dz3[b * kOut + o], N.a2[b * kHid + h], s);
-        N.g[kW3 + k] = s;
-    } else if (k < kOut * kHid + kOut) {                  // db3
-        const uint32_t o = k - kOut * kHid;
-        float s = 0.0f;
-        for (uint32_t b = 0; b < bp; ++b) s += N.dz3[b * kOut + o];
-        N.g[kB3 + o] = s;
-    } else if (k < kOut * kHid + kOut + kHid) {           // db2
-        const uint32_t h = k - kOut * kHid - kOut;
-        float s = 0.0f;
-        for (uint32_t b = 0; b < bp; ++b) s += N.dz2[b * kHid + h];
-        N.g[kB2 + h] = s;
-    }
-}
-
-// both GEMMs of layer 2's backward pass on the matrix cores, one wave per
-// 16 x 16 tile: waves [0, 64) make dW2(h, k) = sum_b dz2(b, h) a1(b, k);
-// the rest make da1(b, k) = sum_h dz2(b, h) W2(h, k), then
-// dz1 = da1 * SiLU'(z1)
-__global__ void k_mlp_bwd2(Net N, uint32_t bp) {
-    const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const uint32_t ntn = kHid / 16;
-    const int l = (int)(threadIdx.x & 63u);
-    if (wave < ntn * ntn) {
-        const uint32_t hm = (wave / ntn) * 16, kn = (wave % ntn) * 16;
-        const f32x4 acc = mfma_tile(N.dz2b + hm, 1, kHid, N.a1b + kn, kHid, 1, (int)bp);
-        const uint32_t k = kn + (l & 15);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) N.g[kW2 + (hm + (l >> 4) * 4 + j) * kHid + k] = acc[j];
+// The gradient of parameter k: stored, or taken by Adam (Kingma & Ba,
+// bias-corrected) on the FP32 master parameters, then the bf16 copies;
+// c1 = 1 - beta1^t, c2 = 1 - beta2^t.
+template <bool ADAM>
+__device__ __forceinline__ void apply_grad(const Net& N, uint32_t k, AdamState a, float g, float lr, float c1,
+                                           float c2) {
+    if (!ADAM) {
+        N.g[k] = g;
         return;
     }
-    const uint32_t w2 = wave - ntn * ntn;
-    if (w2 >= (bp / 16) * ntn) return;
-    const uint32_t bm = (w2 / ntn) * 16, kn = (w2 % ntn) * 16;
-    const f32x4 acc = mfma_tile(N.dz2b + bm * kHid, kHid, 1, N.wb + kW2 + kn, kHid, 1, kHid);
-    const uint32_t k = kn + (l & 15);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const uint32_t b = bm + (l >> 4) * 4 + j;
-        N.dz1[b * kHid + k] = acc[j] * dsiluf_(N.z1[b * kHid + k]);
-    }
-}
-
-// dW1(h, k) = sum_b dz1(b, h) x(b, k), db1(h) = sum_b dz1(b, h)
-__global__ void k_mlp_grad1(Net N, uint32_t bp) {
-    const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < kHid * kIn) {
-        const uint32_t h = k / kIn, c = k % kIn;
-        float s = 0.0f;
-        for (uint32_t b = 0; b < bp; ++b) s = fmaf(N.dz1[b * kHid + h], N.x[b * kIn + c], s);
-        N.g[kW1 + k] = s;
-    } else if (k < kHid * kIn + kHid) {
-        const uint32_t h = k - kHid * kIn;
-        float s = 0.0f;
-        for (uint32_t b = 0; b < bp; ++b) s += N.dz1[b * kHid + h];
-        N.g[kB1 + h] = s;
-    }
-}
-
-// Adam on the FP32 master parameters (Kingma & Ba, bias-corrected), then
-// the bf16 copy; c1 = 1 - beta1^t, c2 = 1 - beta2^t
-__global__ void k_mlp_adam(Net N, float lr, float c1, float c2) {
-    const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= kNP) return;
-    const float g = N.g[k];
-    const float m = 0.9f * N.m[k] + 0.1f * g;
-    const float v = 0.999f * N.v[k] + 0.001f * g * g;
+    const float m = 0.9f * a.m + 0.1f * g;
+    const float v = 0.999f * a.v + 0.001f * g * g;
     N.m[k] = m;
     N.v[k] = v;
-    const float p = N.p[k] - lr * (m / c1) / (sqrtf(v / c2) + 1e-8f);
+    const float p = a.p - lr * (m / c1) / (sqrtf(v / c2) + 1e-8f);
     N.p[k] = p;
-    N.wb[k] = to_bf16(p);
+    round_param(N, k, p);
+}
+
+// Every parameter gradient of a minibatch and the Adam update, one launch of
+// 40 workgroups.  Workgroups 0 to 15: dW2(h, k) = sum_b dz2(b, h) a1(b, k) on
+// the matrix cores, one wave per 16 x 16 tile, the operands read along b from
+// the transposed copies.  The others: the reductions over 16 columns each of
+// a2 (dW3), dz2 (db2, db3) and dz1 (dW1, db1) in FP32 in row order, one chain
+// per parameter.  A chain is a serial sum over the rows; from global memory it
+// waited for a load per few rows (72 us at 256 rows), so the workgroup first
+// brings kGradRows rows of its columns into LDS with all loads in flight, and
+// a thread sums up to three chains of one column from one LDS read.  Sixteen
+// columns and one tile row to a workgroup, because one CU has only so many
+// misses in flight: with all 128 columns in one workgroup the launch took 18
+// us at 256 rows.
+constexpr int kGradThreads = 256, kGradRows = 256, kGradCols = 16;
+constexpr uint32_t kGradTiles = (kHid / 16) * (kHid / 16) / (kGradThreads / 64);       // workgroups of dW2
+constexpr uint32_t kGradGrid = kGradTiles + 3 * (kHid / kGradCols);
+template <bool ADAM>
+__global__ __launch_bounds__(kGradThreads) void k_mlp_grads(Net N, uint32_t bp, float lr, float c1, float c2) {
+    const int tid = (int)threadIdx.x;
+    if (blockIdx.x < kGradTiles) {
+        const int l = tid & 63, r = l & 15, q4 = (l >> 4) * 4;
+        const uint32_t wave = blockIdx.x * (kGradThreads / 64) + (uint32_t)(tid >> 6);
+        const uint32_t hm = (wave / 8) * 16, kn = (wave % 8) * 16;
+        const uint16_t* a = N.dz2t + (size_t)(hm + r) * N.ld + q4;
+        const uint16_t* b = N.a1t + (size_t)(kn + r) * N.ld + q4;
+        const uint32_t k0 = kW2 + (hm + q4) * kHid + kn + r;
+        AdamState st[4];
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (uint32_t b0 = 0; b0 < bp; b0 += 256) {
+            bf16x4 av[16], bv[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const uint32_t at = min(b0 + 16u * k, bp - 16u);
+                av[k] = *reinterpret_cast<const bf16x4*>(a + at);
+                bv[k] = *reinterpret_cast<const bf16x4*>(b + at);
+            }
+            if (b0 == 0) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) st[j] = adam_state<ADAM>(N, k0 + j * kHid);
+            }
+#pragma unroll
+            for (int k = 0; k < 16; ++k)
+                if (b0 + 16u * k < bp) acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[k], bv[k], acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) apply_grad<ADAM>(N, k0 + j * kHid, st[j], acc[j], lr, c1, c2);
+        return;
+    }
+    constexpr int kQuads = kGradRows * kGradCols / 4 / kGradThreads;                   // 16-byte loads per thread
+    __shared__ f32x4 rows4[kGradRows * kGradCols / 4];
+    __shared__ __attribute__((aligned(16))) float side[kGradRows * kIn];               // x (4 per row) or dz3 (2 per row)
+    float* const rows = reinterpret_cast<float*>(rows4);
+    const uint32_t part = (blockIdx.x - kGradTiles) / (kHid / kGradCols);              // 0: a2, 1: dz2, 2: dz1
+    const uint32_t c0 = ((blockIdx.x - kGradTiles) % (kHid / kGradCols)) * kGradCols;
+    const float* src = (part == 0 ? N.a2 : (part == 1 ? N.dz2 : N.dz1)) + c0;
+    const float* ssrc = part == 2 ? N.x : N.dz3;
+    const uint32_t sw = part == 2 ? kIn : kOut;
+    // thread (col, half): chains of column col, times side columns 2 half and
+    // 2 half + 1, and alone; db3 sums side columns with two more threads
+    const uint32_t lc = (uint32_t)tid % kGradCols, half = (uint32_t)tid / kGradCols, col = c0 + lc;
+    const bool weights = tid < (part == 0 ? kGradCols : (part == 1 ? 0 : 2 * kGradCols));
+    const bool b3 = part == 1 && c0 == 0 && tid >= kGradCols && tid < kGradCols + kOut;
+    const bool bias = (part != 0 && tid < kGradCols) || b3;
+    const uint32_t p0 = part == 0 ? kW3 + col : kW1 + col * kIn + 2u * half, p1 = part == 0 ? p0 + kHid : p0 + 1u;
+    const uint32_t pb = b3 ? kB3 + lc : (part == 1 ? kB2 : kB1) + col;
+    const float* const uc = b3 ? side + lc : rows + lc;
+    const uint32_t us = b3 ? sw : kGradCols;
+    const float* const wc = side + (weights ? 2u * half : 0u);
+    AdamState a0{}, a1{}, ab{};
+    if (weights) {
+        a0 = adam_state<ADAM>(N, p0);
+        a1 = adam_state<ADAM>(N, p1);
+    }
+    if (bias) ab = adam_state<ADAM>(N, pb);
+    float s0 = 0.0f, s1 = 0.0f, sb = 0.0f;
+    for (uint32_t b0 = 0; b0 < bp; b0 += kGradRows) {
+        const uint32_t nr = min((uint32_t)kGradRows, bp - b0);      // a multiple of 16
+        f32x4 v[kQuads];
+        float sv[kIn];
+#pragma unroll
+        for (int k = 0; k < kQuads; ++k) {
+            const uint32_t e = (uint32_t)(tid + k * kGradThreads), b = min(e / (kGradCols / 4), nr - 1u);
+            v[k] = *reinterpret_cast<const f32x4*>(src + (size_t)(b0 + b) * kHid + (e % (kGradCols / 4)) * 4);
+        }
+#pragma unroll
+        for (int k = 0; k < kIn; ++k) sv[k] = ssrc[(size_t)b0 * sw + min((uint32_t)(tid + k * kGradThreads), nr * sw - 1u)];
+        __syncthreads();                 // the rows before these have been summed
+#pragma unroll
+        for (int k = 0; k < kQuads; ++k) rows4[tid + k * kGradThreads] = v[k];
+#pragma unroll
+        for (int k = 0; k < kIn; ++k) side[tid + k * kGradThreads] = sv[k];
+        __syncthreads();
+        if (!weights && !bias) continue;
+        // 16 rows are read while the 16 before them are summed
+        float u[16];
+        float2 w[16];
+        auto read = [&](uint32_t b) {
+#pragma unroll
+            for (uint32_t k = 0; k < 16; ++k) {
+                u[k] = uc[(b + k) * us];
+                w[k] = *reinterpret_cast<const float2*>(wc + (b + k) * sw);
+            }
+        };
+        read(0);
+        for (uint32_t b = 0; b < nr; b += 16) {
+            float cu[16];
+            float2 cw[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                cu[k] = u[k];
+                cw[k] = w[k];
+            }
+            read(b + 16 < nr ? b + 16 : b);
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                s0 = fmaf(cw[k].x, cu[k], s0);
+                s1 = fmaf(cw[k].y, cu[k], s1);
+                sb += cu[k];
+            }
+        }
+    }
+    if (weights) {
+        apply_grad<ADAM>(N, p0, a0, s0, lr, c1, c2);
+        apply_grad<ADAM>(N, p1, a1, s1, lr, c1, c2);
+    }
+    if (bias) apply_grad<ADAM>(N, pb, ab, sb, lr, c1, c2);
 }
 
 }  // namespace
@@ -280,10 +411,16 @@ struct db_mlp {
     Net N{};
     std::vector<void*> allocs;
     std::string err;
-    float* dX = nullptr;         // training set on the device
+    float* dX = nullptr;         // training set on the device, and its outputs
     float* dT = nullptr;
-    uint32_t* dIdx = nullptr;
+    float* dY = nullptr;
     uint64_t cap_rows = 0;
+    uint32_t* dIdx = nullptr;    // row orders: two slots
+    uint32_t* hIdx = nullptr;    // the same in pinned memory
+    uint64_t cap_idx = 0;        // entries of one slot
+    hipEvent_t idx_done[2] = {nullptr, nullptr};   // the copy out of a pinned slot
+    float* hRows = nullptr;      // pinned rows of a prediction: kPredictRows x 4 in, x 2 out
+    uint64_t cap_pred = 0;
 };
 
 namespace {
@@ -324,26 +461,36 @@ db_status malloc_n(db_mlp* s, T*& p, size_t n) {
 
 inline unsigned blocks(uint64_t n, unsigned bs) { return (unsigned)((n + bs - 1) / bs); }
 
-// forward (and, with targets, backward) over the bp-row minibatch already in N.x / N.t
-void run_pass(db_mlp* s, uint32_t nb, bool grad) {
-    const uint32_t bp = (nb + 15u) & ~15u;
-    Net& N = s->N;
-    hipLaunchKernelGGL(k_mlp_fwd1, dim3(blocks((uint64_t)bp * kHid, 256)), dim3(256), 0, s->stream, N, bp);
-    hipLaunchKernelGGL(k_mlp_fwd2, dim3(blocks((uint64_t)(bp / 16) * (kHid / 16) * 64, 256)), dim3(256), 0,
-                       s->stream, N, bp);
-    hipLaunchKernelGGL(k_mlp_fwd3, dim3(blocks((uint64_t)bp * kOut, 256)), dim3(256), 0, s->stream, N, bp, nb,
-                       grad ? 1 : 0);
-    if (!grad) return;
-    hipLaunchKernelGGL(k_mlp_bwd3, dim3(blocks((uint64_t)bp * kHid, 256)), dim3(256), 0, s->stream, N, bp);
-    hipLaunchKernelGGL(k_mlp_grad3, dim3(blocks(kOut * kHid + kOut + kHid, 256)), dim3(256), 0, s->stream, N, bp);
-    const uint64_t waves = (uint64_t)(kHid / 16) * (kHid / 16) + (uint64_t)(bp / 16) * (kHid / 16);
-    hipLaunchKernelGGL(k_mlp_bwd2, dim3(blocks(waves * 64, 256)), dim3(256), 0, s->stream, N, bp);
-    hipLaunchKernelGGL(k_mlp_grad1, dim3(blocks(kHid * kIn + kHid, 256)), dim3(256), 0, s->stream, N, bp);
+// Minibatch orders on their way to the device, and rows of a prediction, go
+// through pinned buffers (allocated on first use: 2 x 1 MiB, or 2 x 4 B a row
+// up to 2 x 16 MiB, and at most 1.5 MiB).
+constexpr uint64_t kIdxSlot = 262144, kIdxPinnedMax = 16 * kIdxSlot, kPredictRows = 65536;
+// Workgroups of the forward pass over many rows: two per CU; each keeps its
+// weights over its tiles.
+constexpr uint32_t kRowGrid = 512;
+
+void launch_rows(db_mlp* s, const float* x, uint64_t n, float* y) {
+    const uint32_t tiles = (uint32_t)((n + kRowTile - 1) / kRowTile);
+    hipLaunchKernelGGL(k_mlp_rows<false>, dim3(std::min(tiles, kRowGrid)), dim3(kRowThreads), 0, s->stream, s->N, x,
+                       (const float*)nullptr, (const uint32_t*)nullptr, (uint32_t)n, tiles, y);
+}
+
+// Forward and backward over the nb rows idx names (the first nb when null),
+// then the gradients: into N.g (lr <= 0) or into the parameters.
+void launch_minibatch(db_mlp* s, const uint32_t* idx, uint32_t nb, float* y, float lr, float c1, float c2) {
+    const uint32_t tiles = (nb + kRowTile - 1) / kRowTile, bp = tiles * kRowTile;
+    hipLaunchKernelGGL(k_mlp_rows<true>, dim3(tiles), dim3(kRowThreads), 0, s->stream, s->N, (const float*)s->dX,
+                       (const float*)s->dT, idx, nb, tiles, y);
+    if (lr > 0.0f)
+        hipLaunchKernelGGL(k_mlp_grads<true>, dim3(kGradGrid), dim3(kGradThreads), 0, s->stream, s->N, bp, lr, c1, c2);
+    else
+        hipLaunchKernelGGL(k_mlp_grads<false>, dim3(kGradGrid), dim3(kGradThreads), 0, s->stream, s->N, bp, 0.0f, 1.0f,
+                           1.0f);
 }
 
 db_status upload_rows(db_mlp* s, const float* x, const float* t, uint64_t n) {
     if (n > s->cap_rows) {
-        for (void* q : {(void*)s->dX, (void*)s->dT, (void*)s->dIdx}) {
+        for (void* q : {(void*)s->dX, (void*)s->dT, (void*)s->dY}) {
             auto it = std::find(s->allocs.begin(), s->allocs.end(), q);
             if (it != s->allocs.end()) {
                 (void)hipFree(q);
@@ -352,22 +499,54 @@ db_status upload_rows(db_mlp* s, const float* x, const float* t, uint64_t n) {
         }
         s->dX = nullptr;
         s->dT = nullptr;
-        s->dIdx = nullptr;
+        s->dY = nullptr;
         s->cap_rows = 0;
         MALLOC(s, s->dX, n * kIn);
         MALLOC(s, s->dT, n * kOut);
-        MALLOC(s, s->dIdx, n);
+        MALLOC(s, s->dY, n * kOut);
         s->cap_rows = n;
     }
     MCHK(s, hipMemcpyAsync(s->dX, x, n * kIn * sizeof(float), hipMemcpyHostToDevice, s->stream));
-    if (t) MCHK(s, hipMemcpyAsync(s->dT, t, n * kOut * sizeof(float), hipMemcpyHostToDevice, s->stream));
+    MCHK(s, hipMemcpyAsync(s->dT, t, n * kOut * sizeof(float), hipMemcpyHostToDevice, s->stream));
     return DB_OK;
 }
 
+// (bitwise on the exponent, without an early exit, so that the loop is vectorised)
 bool finite_rows(const float* a, uint64_t count) {
-    for (uint64_t k = 0; k < count; ++k)
-        if (!std::isfinite(a[k])) return false;
-    return true;
+    uint32_t bad = 0;
+    for (uint64_t k = 0; k < count; ++k) {
+        uint32_t u;
+        std::memcpy(&u, a + k, 4);
+        bad |= (u & 0x7F800000u) == 0x7F800000u ? 1u : 0u;
+    }
+    return bad == 0u;
+}
+
+// The device and pinned buffers of the minibatch orders.  Above kIdxPinnedMax
+// rows (or where pinned memory is short) an order goes straight from the
+// host's own array, one epoch at a time (hIdx stays null).
+db_status index_buffers(db_mlp* s, uint64_t n) {
+    const bool pin = n <= kIdxPinnedMax;
+    const uint64_t slot = pin ? std::max<uint64_t>(kIdxSlot, n) : n;
+    if (s->dIdx && slot <= s->cap_idx && (s->hIdx || !pin)) return DB_OK;
+    MCHK(s, hipStreamSynchronize(s->stream));
+    if (s->hIdx) (void)hipHostFree(s->hIdx);
+    s->hIdx = nullptr;
+    s->cap_idx = 0;
+    auto it = std::find(s->allocs.begin(), s->allocs.end(), (void*)s->dIdx);
+    if (s->dIdx && it != s->allocs.end()) {
+        (void)hipFree(s->dIdx);
+        s->allocs.erase(it);
+    }
+    s->dIdx = nullptr;
+    for (auto& e : s->idx_done)
+        if (!e) MCHK(s, hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    MALLOC(s, s->dIdx, (pin ? 2 : 1) * slot);
+    s->cap_idx = slot;
+    void* h = nullptr;
+    if (pin && hipHostMalloc(&h, 2 * slot * sizeof(uint32_t), hipHostMallocDefault) == hipSuccess) s->hIdx = (uint32_t*)h;
+    else if (pin) (void)hipGetLastError();
+    return DB_OK;
 }
 
 }  // namespace
@@ -396,14 +575,15 @@ db_status db_mlp_create(uint32_t batch_max, int device, db_mlp** out) {
     const size_t b = s->bmax;
     db_status st = DB_OK;
     auto A = [&](auto*& p, size_t n) { if (st == DB_OK) st = malloc_n(s, p, n); };
-    A(N.p, kNP); A(N.m, kNP); A(N.v, kNP); A(N.g, kNP); A(N.wb, kNP);
-    A(N.x, b * kIn); A(N.t, b * kOut); A(N.z1, b * kHid); A(N.a1b, b * kHid); A(N.z2, b * kHid);
-    A(N.a2, b * kHid); A(N.y, b * kOut); A(N.dz3, b * kOut); A(N.dz2, b * kHid); A(N.dz2b, b * kHid);
-    A(N.dz1, b * kHid); A(N.loss, 1);
+    A(N.p, kNP); A(N.m, kNP); A(N.v, kNP); A(N.g, kNP); A(N.wb, kNP); A(N.w2t, kHid * kHid);
+    A(N.x, b * kIn); A(N.a2, b * kHid); A(N.dz3, b * kOut); A(N.dz2, b * kHid); A(N.dz1, b * kHid);
+    A(N.a1t, b * kHid); A(N.dz2t, b * kHid);
+    N.ld = (uint32_t)b;
     if (st != DB_OK) return bad(st);
     for (void* q : {(void*)N.p, (void*)N.m, (void*)N.v, (void*)N.g})
         if (hipMemsetAsync(q, 0, kNP * sizeof(float), s->stream) != hipSuccess) return bad(DB_EDEVICE);
     if (hipMemsetAsync(N.wb, 0, kNP * sizeof(uint16_t), s->stream) != hipSuccess ||
+        hipMemsetAsync(N.w2t, 0, kHid * kHid * sizeof(uint16_t), s->stream) != hipSuccess ||
         hipStreamSynchronize(s->stream) != hipSuccess)
         return bad(DB_EDEVICE);
     *out = s;
@@ -415,6 +595,10 @@ void db_mlp_destroy(db_mlp* s) {
     (void)hipSetDevice(s->device);
     if (s->stream) (void)hipStreamSynchronize(s->stream);
     for (void* q : s->allocs) (void)hipFree(q);
+    if (s->hIdx) (void)hipHostFree(s->hIdx);
+    if (s->hRows) (void)hipHostFree(s->hRows);
+    for (hipEvent_t e : s->idx_done)
+        if (e) (void)hipEventDestroy(e);
     if (s->stream) (void)hipStreamDestroy(s->stream);
     delete s;
 }
@@ -447,20 +631,32 @@ db_status db_mlp_predict(db_mlp* s, const float* x, uint64_t n, float* y) {
     if (n == 0) return DB_OK;
     if (!finite_rows(x, n * kIn)) return mfail(s, DB_EINVAL, "non-finite input");
     MCHK(s, hipSetDevice(s->device));
-    db_status st = upload_rows(s, x, nullptr, n);
-    if (st != DB_OK) return st;
-    std::vector<uint32_t> idx(s->bmax);
-    for (uint64_t r0 = 0; r0 < n; r0 += s->bmax) {
-        const uint32_t nb = (uint32_t)std::min<uint64_t>(s->bmax, n - r0);
-        for (uint32_t k = 0; k < nb; ++k) idx[k] = (uint32_t)(r0 + k);
-        MCHK(s, hipMemcpyAsync(s->dIdx, idx.data(), nb * sizeof(uint32_t), hipMemcpyHostToDevice, s->stream));
-        const uint32_t bp = (nb + 15u) & ~15u;
-        hipLaunchKernelGGL(k_mlp_gather, dim3(blocks(bp, 256)), dim3(256), 0, s->stream, s->N, s->dX,
-                           (const float*)nullptr, s->dIdx, nb, bp);
-        run_pass(s, nb, false);
+    // rows go through pinned memory, which the kernel reads and writes itself
+    // (a copy, a launch per layer and a wait for every batch_max rows took
+    // 2.5 ms for 65 536 rows)
+    const uint64_t cap = std::min<uint64_t>(n, kPredictRows);
+    if (cap > s->cap_pred) {
+        if (s->hRows) (void)hipHostFree(s->hRows);
+        s->hRows = nullptr;
+        s->cap_pred = 0;
+        const uint64_t want = std::min<uint64_t>(kPredictRows, std::max<uint64_t>(cap, 1024));
+        void* h = nullptr;
+        if (hipHostMalloc(&h, want * (kIn + kOut) * sizeof(float), hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            return mfail(s, DB_ENOMEM, "pinned host allocation failed");
+        }
+        s->hRows = (float*)h;
+        s->cap_pred = want;
+    }
+    float* const hx = s->hRows;
+    float* const hy = s->hRows + s->cap_pred * kIn;
+    for (uint64_t r0 = 0; r0 < n; r0 += s->cap_pred) {
+        const uint64_t nb = std::min<uint64_t>(s->cap_pred, n - r0);
+        std::memcpy(hx, x + r0 * kIn, nb * kIn * sizeof(float));
+        launch_rows(s, hx, nb, hy);
         MCHK(s, hipGetLastError());
-        MCHK(s, hipMemcpyAsync(y + r0 * kOut, s->N.y, nb * kOut * sizeof(float), hipMemcpyDeviceToHost, s->stream));
         MCHK(s, hipStreamSynchronize(s->stream));
+        std::memcpy(y + r0 * kOut, hy, nb * kOut * sizeof(float));
     }
     return DB_OK;
 }
@@ -473,17 +669,12 @@ db_status db_mlp_loss_grad(db_mlp* s, const float* x, const float* t, uint32_t n
     MCHK(s, hipSetDevice(s->device));
     db_status st = upload_rows(s, x, t, n);
     if (st != DB_OK) return st;
-    std::vector<uint32_t> idx(n);
-    std::iota(idx.begin(), idx.end(), 0u);
-    MCHK(s, hipMemcpyAsync(s->dIdx, idx.data(), n * sizeof(uint32_t), hipMemcpyHostToDevice, s->stream));
-    const uint32_t bp = (n + 15u) & ~15u;
-    hipLaunchKernelGGL(k_mlp_gather, dim3(blocks(bp, 256)), dim3(256), 0, s->stream, s->N, s->dX, s->dT, s->dIdx,
-                       n, bp);
-    run_pass(s, n, true);
-    hipLaunchKernelGGL(k_mlp_loss, dim3(1), dim3(256), 0, s->stream, s->N, n);
+    launch_minibatch(s, nullptr, n, s->dY, 0.0f, 1.0f, 1.0f);
+    float* const dl = s->N.dz3;                  // the backward pass is done with dz3
+    hipLaunchKernelGGL(k_mlp_loss, dim3(1), dim3(256), 0, s->stream, (const float*)s->dY, (const float*)s->dT, n, n, dl);
     MCHK(s, hipGetLastError());
     MCHK(s, hipMemcpyAsync(grad, s->N.g, kNP * sizeof(float), hipMemcpyDeviceToHost, s->stream));
-    MCHK(s, hipMemcpyAsync(loss, s->N.loss, sizeof(float), hipMemcpyDeviceToHost, s->stream));
+    MCHK(s, hipMemcpyAsync(loss, dl, sizeof(float), hipMemcpyDeviceToHost, s->stream));
     MCHK(s, hipStreamSynchronize(s->stream));
     return DB_OK;
 }
@@ -498,47 +689,57 @@ db_status db_mlp_train(db_mlp* s, const float* x, const float* t, uint64_t n, ui
     MCHK(s, hipSetDevice(s->device));
     db_status st = upload_rows(s, x, t, n);
     if (st != DB_OK) return st;
+    st = index_buffers(s, n);
+    if (st != DB_OK) return st;
     std::mt19937_64 gen(seed);
     std::vector<uint32_t> perm(n);
     std::iota(perm.begin(), perm.end(), 0u);
-    for (uint32_t ep = 0; ep < epochs; ++ep) {
-        for (uint64_t k = n - 1; k > 0; --k) std::swap(perm[k], perm[gen() % (k + 1)]);
-        MCHK(s, hipMemcpyAsync(s->dIdx, perm.data(), n * sizeof(uint32_t), hipMemcpyHostToDevice, s->stream));
-        for (uint64_t r0 = 0; r0 < n; r0 += batch) {
-            const uint32_t nb = (uint32_t)std::min<uint64_t>(batch, n - r0);
-            const uint32_t bp = (nb + 15u) & ~15u;
-            hipLaunchKernelGGL(k_mlp_gather, dim3(blocks(bp, 256)), dim3(256), 0, s->stream, s->N, s->dX, s->dT,
-                               s->dIdx + r0, nb, bp);
-            run_pass(s, nb, true);
-            ++s->adam_t;
-            const float c1 = (float)(1.0 - std::pow(0.9, (double)s->adam_t));
-            const float c2 = (float)(1.0 - std::pow(0.999, (double)s->adam_t));
-            hipLaunchKernelGGL(k_mlp_adam, dim3(blocks(kNP, 256)), dim3(256), 0, s->stream, s->N, lr, c1, c2);
+    // epochs are drawn in groups that fill a slot, while the device works on
+    // the group before
+    const bool pinned = s->hIdx != nullptr;
+    const uint32_t group = pinned ? (uint32_t)std::max<uint64_t>(1, s->cap_idx / n) : 1u;
+    for (uint32_t e0 = 0, turn = 0; e0 < epochs; e0 += group, ++turn) {
+        const uint32_t ne = std::min(group, epochs - e0);
+        const uint64_t at = pinned ? (turn & 1u) * s->cap_idx : 0;
+        uint32_t* const d = s->dIdx + at;
+        // the last copy out of this slot (or out of `perm`) must be done
+        if (pinned && turn >= 2) MCHK(s, hipEventSynchronize(s->idx_done[turn & 1u]));
+        else if (!pinned && turn) MCHK(s, hipStreamSynchronize(s->stream));
+        for (uint32_t e = 0; e < ne; ++e) {
+            for (uint64_t k = n - 1; k > 0; --k) std::swap(perm[k], perm[gen() % (k + 1)]);
+            if (pinned) std::memcpy(s->hIdx + at + (size_t)e * n, perm.data(), n * sizeof(uint32_t));
         }
+        const uint32_t* const h = pinned ? s->hIdx + at : perm.data();
+        MCHK(s, hipMemcpyAsync(d, h, (size_t)ne * n * sizeof(uint32_t), hipMemcpyHostToDevice, s->stream));
+        MCHK(s, hipEventRecord(s->idx_done[turn & 1u], s->stream));
+        for (uint32_t e = 0; e < ne; ++e)
+            for (uint64_t r0 = 0; r0 < n; r0 += batch) {
+                ++s->adam_t;
+                const float c1 = (float)(1.0 - std::pow(0.9, (double)s->adam_t));
+                const float c2 = (float)(1.0 - std::pow(0.999, (double)s->adam_t));
+                launch_minibatch(s, d + (size_t)e * n + r0, (uint32_t)std::min<uint64_t>(batch, n - r0), nullptr, lr, c1,
+                                 c2);
+            }
         MCHK(s, hipGetLastError());
-        // the host copies the next epoch's order into the index buffer: wait for this one
+    }
+    if (!final_loss) {
         MCHK(s, hipStreamSynchronize(s->stream));
+        return DB_OK;
     }
-    if (final_loss) {
-        // mean-squared error over all rows, batch_max rows at a time
-        double acc = 0.0;
-        std::vector<uint32_t> idx(s->bmax);
-        for (uint64_t r0 = 0; r0 < n; r0 += s->bmax) {
-            const uint32_t nb = (uint32_t)std::min<uint64_t>(s->bmax, n - r0);
-            for (uint32_t k = 0; k < nb; ++k) idx[k] = (uint32_t)(r0 + k);
-            MCHK(s, hipMemcpyAsync(s->dIdx, idx.data(), nb * sizeof(uint32_t), hipMemcpyHostToDevice, s->stream));
-            const uint32_t bp = (nb + 15u) & ~15u;
-            hipLaunchKernelGGL(k_mlp_gather, dim3(blocks(bp, 256)), dim3(256), 0, s->stream, s->N, s->dX, s->dT,
-                               s->dIdx, nb, bp);
-            run_pass(s, nb, false);
-            hipLaunchKernelGGL(k_mlp_loss, dim3(1), dim3(256), 0, s->stream, s->N, nb);
-            float l = 0.0f;
-            MCHK(s, hipMemcpyAsync(&l, s->N.loss, sizeof(float), hipMemcpyDeviceToHost, s->stream));
-            MCHK(s, hipStreamSynchronize(s->stream));
-            acc += (double)l * nb;
-        }
-        *final_loss = (float)(acc / (double)n);
-    }
+    // mean-squared error over all rows, from the errors of batch_max rows at a time
+    const uint32_t chunks = (uint32_t)((n + s->bmax - 1) / s->bmax);
+    launch_rows(s, s->dX, n, s->dY);
+    // (one error per run of bmax rows, and x has 4 words per row)
+    hipLaunchKernelGGL(k_mlp_loss, dim3(chunks), dim3(256), 0, s->stream, (const float*)s->dY, (const float*)s->dT,
+                       (uint32_t)n, s->bmax, s->dX);
+    std::vector<float> l(chunks);
+    MCHK(s, hipGetLastError());
+    MCHK(s, hipMemcpyAsync(l.data(), s->dX, chunks * sizeof(float), hipMemcpyDeviceToHost, s->stream));
+    MCHK(s, hipStreamSynchronize(s->stream));
+    double acc = 0.0;
+    for (uint32_t k = 0; k < chunks; ++k)
+        acc += (double)l[k] * (double)std::min<uint64_t>(s->bmax, n - (uint64_t)k * s->bmax);
+    *final_loss = (float)(acc / (double)n);
     return DB_OK;
 }
 
