@@ -286,11 +286,10 @@ DB_API db_status db_commit(db_system* sys);
  * update and before the forces at the new positions; each sweep forms bonds
  * with P_on = P0_on exp(-U_b(r)/kT) and breaks the bonds present at its
  * start with P0_off (Eq. pon, Eq. probs).  Synchronous: returns when the
- * GPU work is done.  A system of at most 768 particles advanced by 200 or
- * more steps in one call, with the automatic launch shape, can run as a
- * batch of one (db_step_batch: one workgroup takes every step) instead of
- * the grid kernels, with the same result bit for bit: the first such call
- * times 100 steps on each and later calls keep the faster.  Errors: DB_ESTATE (not committed, invalid state),
+ * GPU work is done.  A small system (up to 1024 particles, fewer where they
+ * have many neighbours) with the automatic launch shape runs in one workgroup
+ * that keeps its state on the chip, instead of the grid kernels, with the same
+ * result bit for bit.  Errors: DB_ESTATE (not committed, invalid state),
  * DB_EDEVICE, DB_ENOMEM; DB_EBOND / DB_EOVERFLOW leave the state invalid
  * (DB_ESTATE) until db_set_state. */
 DB_API db_status db_step(db_system* sys, uint64_t n_steps);
@@ -313,11 +312,10 @@ typedef struct {
  * (db_set_batch_plan, db_batch_autotune; by default one class of
  * 1024-thread workgroups).  One workgroup per system runs all of its steps,
  * with workgroup barriers between the phases of a step and the system's own
- * device state and buffers.  All launches of a call form one HIP graph: each
- * occupied size class is a branch of its own (the classes run concurrently),
- * a chain of launches of at most 2000 steps each (a bound on how long one
- * kernel runs) that hand each system's step and buffer indices on in device
- * memory.  The result is bitwise identical to db_step(systems[k], n_steps)
+ * device state and buffers.  Each occupied size class is a chain of launches
+ * on a stream of its own (the classes run concurrently), of at most 2000 steps
+ * each (a bound on how long one kernel runs), that hand each system's step and
+ * buffer indices on without the host.  The result is bitwise identical to db_step(systems[k], n_steps)
  * on every system (same forces, integrator, random streams and greedy
  * matching); positions may be numbered differently inside the library,
  * which db_read_* never show.  Synchronous.  Errors: DB_EINVAL (null or
@@ -347,7 +345,7 @@ DB_API db_status db_get_batch_plan(int device, db_batch_plan* plan);
  * the plan in hand timed both just before and just after the candidate (the
  * systems evolve between trials, and with them the cost of a step).
  * Adjacent classes with the same size are merged in every plan tried and in
- * the result (each class is a concurrent branch of the batch's graph, which
+ * the result (each class is a concurrent chain of launches, which
  * costs time when it gains nothing), so a batch that gains from no change
  * gets the one-class default back.  Every
  * trial advances all systems by trial_steps (1..2000): since results do not

@@ -12,7 +12,7 @@
 // a batched run is bitwise identical to db_step on each system.
 #pragma once
 
-#include "kernels.hpp"
+#include "resident.hpp"
 
 namespace dyb {
 
@@ -20,13 +20,7 @@ namespace dyb {
 struct BatchItem {
     Params P;
     Dev D;
-};
-
-// Where a system's run stands: read at the start of a launch, written back
-// at its end, so consecutive launches of a batch chain on the device alone.
-struct BatchState {
-    unsigned long long t;    // step of the system
-    int cur_x, cur_list;     // current position buffer and cell list
+    uint32_t resident;       // threads per particle of the resident form (resident_steps), 0: k_batch's own loop
 };
 
 constexpr int kBatchMaxThreads = 1024;
@@ -312,6 +306,15 @@ void k_batch(const BatchItem* __restrict__ items, BatchState* __restrict__ state
     const uint32_t n = P.n;
     stage_tabs(D, T, tid);
     if (tid < 3) flag[tid] = more[tid] = 0u;
+    if constexpr (LX) {
+        if (B.resident) {                 // (the same for the whole workgroup)
+            __syncthreads();
+            unsigned char* const lds = reinterpret_cast<unsigned char*>(xs);
+            if (B.resident == 2u) resident_steps<EXT, 2>(P, D, T, lds, st0, nsteps, flag, more, &state[blockIdx.x]);
+            else resident_steps<EXT, 1>(P, D, T, lds, st0, nsteps, flag, more, &state[blockIdx.x]);
+            return;
+        }
+    }
     int xin = st0.cur_x, lcur = st0.cur_list;
     if constexpr (LX) {
         const float4* __restrict__ Xg = D.x[xin];
@@ -465,8 +468,23 @@ void k_batch(const BatchItem* __restrict__ items, BatchState* __restrict__ state
         st.t = t0 + nsteps;
         st.cur_x = xin;
         st.cur_list = lcur;
+        for (int w = 0; w < 4; ++w) st.err[w] = __hip_atomic_load(&D.err[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         state[blockIdx.x] = st;
     }
+}
+
+// One small system on its own (db_step), its parameters in the kernel
+// arguments and its state by value: nothing to upload before the launch.
+template <bool EXT, int TPP>
+__global__ __launch_bounds__(kBatchMaxThreads) __attribute__((amdgpu_waves_per_eu(4)))
+void k_resident(const Params P, const Dev D, BatchState st, uint32_t nsteps, BatchState* __restrict__ out) {
+    __shared__ StepTabs T;
+    __shared__ uint32_t flag[3], more[3];
+    extern __shared__ float4 xs[];
+    stage_tabs(D, T, threadIdx.x);
+    if (threadIdx.x < 3) flag[threadIdx.x] = more[threadIdx.x] = 0u;
+    __syncthreads();
+    resident_steps<EXT, TPP>(P, D, T, reinterpret_cast<unsigned char*>(xs), st, nsteps, flag, more, out);
 }
 
 // Spatial renumbering of system blockIdx.x inside one workgroup, launched
@@ -482,6 +500,7 @@ void k_batch(const BatchItem* __restrict__ items, BatchState* __restrict__ state
 __global__ __launch_bounds__(kBatchMaxThreads)
 void k_batch_sort(const BatchItem* __restrict__ items, const BatchState* __restrict__ state) {
     const BatchItem& B = items[blockIdx.x];
+    if (B.resident) return;               // positions in LDS: the numbering does not matter
     const Params& P = B.P;
     const Dev& D = B.D;
     const BatchState st = state[blockIdx.x];

@@ -397,6 +397,13 @@ __device__ __forceinline__ float mi_delta_f(float xi, float xj, const Params& P)
     return d;
 }
 
+// The same without the test for a component beyond half a box, for list
+// builds and rebuild tests, which only need it to their margins.
+__device__ __forceinline__ float mi_delta_list(float xi, float xj, const Params& P) {
+    const float d = xj - xi;
+    return fmaf(-P.Lf, rintf(d * P.invLf), d);
+}
+
 // Position at the last neighbour-list build, kept only for the rebuild test:
 // each coordinate as a 21-bit cell index of a grid of spacing L / 2^21 over
 // [-L/2, L/2), the three packed into 63 bits (8 bytes instead of 16).

@@ -68,6 +68,39 @@ constexpr double kDefaultSkin = 0.3;
 // steps, 37.7 every 240, 37.5 every 480 (4 M particles: 504, 492, 494 us).
 constexpr uint64_t kSortPeriod = 480;
 
+// Workspace of db_step_batch, kept by the first system of the batch: the
+// batch's items on the device (and in pinned memory on their way there), the
+// systems' states in pinned memory, which the kernels read and write in place,
+// and streams and events of the further size classes.
+struct BatchWork {
+    BatchItem* items = nullptr;
+    BatchItem* items_h = nullptr;
+    BatchState* state = nullptr;
+    uint32_t cap = 0;                      // systems there is room for
+    std::vector<hipStream_t> streams;
+    std::vector<hipEvent_t> joins;
+    hipEvent_t fork = nullptr, t_a = nullptr, t_b = nullptr;
+
+    void drop_buffers() {
+        if (items) (void)hipFree(items);
+        if (items_h) (void)hipHostFree(items_h);
+        if (state) (void)hipHostFree(state);
+        items = items_h = nullptr;
+        state = nullptr;
+        cap = 0;
+    }
+    void drop() {
+        drop_buffers();
+        for (hipStream_t q : streams) (void)hipStreamDestroy(q);
+        for (hipEvent_t e : joins) (void)hipEventDestroy(e);
+        for (hipEvent_t e : {fork, t_a, t_b})
+            if (e) (void)hipEventDestroy(e);
+        streams.clear();
+        joins.clear();
+        fork = t_a = t_b = nullptr;
+    }
+};
+
 struct db_system {
     // configuration (host)
     uint32_t n = 0, ntypes = 0;
@@ -96,9 +129,10 @@ struct db_system {
     hipStream_t stream = nullptr, own_stream = nullptr;
     uint32_t* bsum = nullptr;       // block sums for the bond read-out (nb + 1)
     float* stage = nullptr;         // tag-ordered staging buffer (3 n words)
-    uint32_t* err_h = nullptr;      // pinned host memory: the device error words, then `obs_h`
+    uint32_t* err_h = nullptr;      // pinned host memory: the device error words, then `obs_h` and `one_h`
     unsigned long long* obs_h = nullptr;   // pinned answers of the observables and histograms
     std::vector<double> val_sum;           // per type: valence x particles
+    double mean_nb = 0.0;                  // neighbours within the list radius at the mean density
     uint64_t step = 0;
     int cur_x = 0, cur_list = 0;
     std::vector<uint32_t> tag_h, rtag_h;   // host mirrors of tag / rtag
@@ -120,9 +154,9 @@ struct db_system {
     bool tags_dirty = false;               // device tag/rtag changed since the host mirrors were read
     bool sort_enabled = true;              // renumber particles in cell order (every kSortPeriod steps)
     uint64_t sort_due = 0;                 // step from which the next renumbering is due
-    int path_pick = 0;                     // long calls on a small system: 0 not measured, 1 one workgroup, 2 grid
-    bool path_pending = false;             // a measurement of the two paths awaits the end of the call
-    hipEvent_t path_ev[3] = {nullptr, nullptr, nullptr};
+    bool tail = false;                     // work may be in flight that no call has waited for
+    BatchState* one_h = nullptr;           // pinned answer of k_resident
+    BatchWork batch;                       // workspace of the batches this system leads
 };
 
 namespace {
@@ -668,6 +702,7 @@ void fill_params(db_system* s) {
     // neighbour slots: room for 2.5x the mean count of an ideal gas at this
     // density plus 32, at least 64 (or exactly what the caller asked for)
     const double mean_nb = 4.18879020478639 * rlist * rlist * rlist * (double)s->n / (s->L * s->L * s->L);
+    s->mean_nb = mean_nb;
     const uint32_t auto_nl = (std::max<uint32_t>(64u, (uint32_t)std::ceil(2.5 * mean_nb + 32.0)) + 7u) & ~7u;
     P.nlmax = s->nlmax_user ? s->nlmax_user : auto_nl;
 
@@ -807,6 +842,7 @@ db_status check_errors(db_system* s) {
     // the stream: one synchronisation per call
     HIPCHK(s, hipMemcpyAsync(s->err_h, s->D.err, 4 * sizeof(uint32_t), hipMemcpyDeviceToHost, s->stream));
     HIPCHK(s, hipStreamSynchronize(s->stream));
+    s->tail = false;
     flush_timing(s);
     uint32_t err[4];
     std::memcpy(err, s->err_h, sizeof err);
@@ -1020,81 +1056,69 @@ db_status prepare_graphs(db_system* s) {
     return DB_OK;
 }
 
-db_status run_batch(db_system* const* systems, uint32_t count, uint64_t nsteps, const db_batch_plan& plan,
-                    float* ms);
+constexpr uint32_t kBatchChunk = 2000;     // steps per launch of a one-workgroup run
 
-// Small systems advanced by many steps in one call can run as a batch of one
-// (one 1024-thread workgroup runs every step, barriers in place of kernel
-// launches; bitwise the same trajectory).  Which is faster depends on the
-// system, not only on its size: a 512-particle dimer gas at density 0.1
-// takes 9.5 us per step that way against 12.5 us on the grid kernels, but
-// sweep replicas of 257 to 684 particles at densities 0.08 to 0.39 take
-// 12.8 to 18.8 us against 12.0 to 14.3 us.  So the first call of at least
-// 2 kPathTrial steps on such a system runs kPathTrial steps on each path
-// between events, and the end of that call keeps the faster path for every
-// later call (path_pick).  kPathTrial stays below the shortest span graph
-// (120 steps), so the grid's part replays only graphs captured before the
-// first event (prepare_graphs; spans are captured when first used, and a
-// capture inside the timed part would leave the GPU idle and count against
-// the grid).  Above kOneGroupMaxN particles one CU is slower than
-// the whole GPU (sweep replicas of 800 to 1030 particles: 15.6 to 19.3 us
-// against 12.4 to 14.5); below kOneGroupMinSteps steps per call the batch's
-// per-call set-up is not repaid.  Neither path is measured or taken with a
-// caller-chosen launch shape, with graphs off or with kernel timing on.
-constexpr uint32_t kOneGroupMaxN = 768;
-constexpr uint64_t kOneGroupMinSteps = 200;
-constexpr uint64_t kPathTrial = 100;
-static_assert(kPathTrial < 120, "the grid's timed part must not need a span graph");
+// Threads per particle of the resident form (resident_steps) in a workgroup
+// of `threads`, 0 where the system has more particles or list cells than it
+// holds.  Two threads share a particle's pairs and bonds, and both integrate
+// it: up to 384 particles that shortens the step (256 particles at densities
+// 0.1 and 0.3: 5.8 and 7.3 us against 6.6 and 9.2), above it the second
+// integration costs more issue than the split saves (512 particles: 7.7 and
+// 9.4 us against 6.8 and 9.5).
+constexpr uint32_t kResTwoThreadN = 384;
+uint32_t resident_tpp(const db_system* s, uint32_t threads) {
+    if (s->n > kResMaxN || s->n > threads || s->P.ncell > kResMaxCells) return 0u;
+    return s->n <= kResTwoThreadN && 2u * s->n <= threads ? 2u : 1u;
+}
+
+// Dynamic LDS beyond the default limit (a runtime that needs no such opt-in
+// may refuse the call: ignored).
+void allow_lds(const void* kernel) {
+    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)(kBatchLdsTotal - kBatchLdsStatic)) != hipSuccess)
+        (void)hipGetLastError();
+}
+
+// db_step runs a small system in one workgroup that keeps its state on the
+// chip (k_resident) instead of the grid kernels, whatever the number of steps
+// (a launch costs no set-up).  One CU is limited by instruction issue, which
+// grows with the particles and their listed neighbours (m on average), the
+// grid kernels by launches, 11 to 13 us per step at any of these sizes:
+// 256, 512 and 1000 particles at density 0.1 (m = 1.7) take 5.8, 6.8 and 9.0
+// us, at density 0.3 (m = 5.1) 7.3, 9.5 and 12.4 us, 1000 at density 0.4 (m =
+// 6.9) 15.3 us.  The line n (2 + m) = 7000 runs between these.  A
+// caller-chosen launch shape, graphs off or kernel timing take the grid
+// kernels.
+constexpr double kOneGroupWork = 7000.0;
+bool one_group(const db_system* s) {
+    if (!s->use_graphs || s->timing.on || s->tpp_user != 0) return false;
+    return resident_tpp(s, kBatchMaxThreads) != 0u && s->n * (2.0 + s->mean_nb) <= kOneGroupWork;
+}
 
 db_status run_one_group(db_system* s, uint64_t nsteps) {
-    db_batch_plan plan{};
-    plan.n_classes = 1;
-    plan.n_max[0] = 0xFFFFFFFFu;
-    plan.threads[0] = (uint32_t)kBatchMaxThreads;
-    db_system* one[1] = {s};
-    return run_batch(one, 1, nsteps, plan, nullptr);
-}
-
-db_status run_grid(db_system* s, uint64_t nsteps);
-
-db_status run_steps(db_system* s, uint64_t nsteps) {
-    const bool small = s->use_graphs && !s->timing.on && s->tpp_user == 0 && s->n <= kOneGroupMaxN &&
-                       nsteps >= kOneGroupMinSteps;
-    if (!small || s->path_pick == 2) return run_grid(s, nsteps);
-    if (s->path_pick == 0 && !s->path_pending && nsteps >= 2 * kPathTrial) {
-        // the grid's graphs are captured before the first event, so that
-        // their set-up is not timed
-        for (auto& e : s->path_ev)
-            if (!e) HIPCHK(s, hipEventCreate(&e));
-        if (s->graphs.empty()) {
-            const db_status st = prepare_graphs(s);
-            if (st != DB_OK) return st;
-        }
-        HIPCHK(s, hipEventRecord(s->path_ev[0], s->stream));
-        db_status st = run_grid(s, kPathTrial);
-        if (st != DB_OK) return st;
-        HIPCHK(s, hipEventRecord(s->path_ev[1], s->stream));
-        st = run_one_group(s, kPathTrial);
-        if (st != DB_OK) return st;
-        HIPCHK(s, hipEventRecord(s->path_ev[2], s->stream));
-        s->path_pending = true;
-        nsteps -= 2 * kPathTrial;
+    const uint32_t tpp = resident_tpp(s, kBatchMaxThreads);
+    const uint32_t threads = (s->n * tpp + 63u) & ~63u;
+    const size_t lds = res_lds_bytes(s->n, s->P.ncell, tpp);
+    const void* const fn = s->P.ext ? (tpp == 2u ? reinterpret_cast<const void*>(&k_resident<true, 2>)
+                                                 : reinterpret_cast<const void*>(&k_resident<true, 1>))
+                                    : (tpp == 2u ? reinterpret_cast<const void*>(&k_resident<false, 2>)
+                                                 : reinterpret_cast<const void*>(&k_resident<false, 1>));
+    if (lds > 64u * 1024u) allow_lds(fn);
+    while (nsteps) {
+        uint32_t chunk = (uint32_t)std::min<uint64_t>(kBatchChunk, nsteps);
+        BatchState st{};
+        st.t = s->step;
+        st.cur_x = s->cur_x;
+        st.cur_list = s->cur_list;
+        BatchState* out = s->one_h;
+        void* args[] = {&s->P, &s->D, &st, &chunk, &out};
+        HIPCHK(s, hipLaunchKernel(fn, dim3(1), dim3(threads), args, lds, s->stream));
+        s->step += chunk;
+        s->cur_x ^= (int)(chunk & 1u);
+        s->cur_list = (int)((s->cur_list + chunk) % 3u);
+        nsteps -= chunk;
     }
-    if (nsteps == 0) return DB_OK;
-    return nsteps >= kOneGroupMinSteps ? run_one_group(s, nsteps) : run_grid(s, nsteps);
-}
-
-// After a call that measured both paths has synchronised: keep the faster.
-void settle_path(db_system* s) {
-    if (!s->path_pending) return;
-    s->path_pending = false;
-    float grid_ms = 0.f, one_ms = 0.f;
-    if (hipEventElapsedTime(&grid_ms, s->path_ev[0], s->path_ev[1]) != hipSuccess ||
-        hipEventElapsedTime(&one_ms, s->path_ev[1], s->path_ev[2]) != hipSuccess) {
-        (void)hipGetLastError();           // measured again by a later call
-        return;
-    }
-    s->path_pick = one_ms <= grid_ms ? 1 : 2;
+    return DB_OK;
 }
 
 db_status run_grid(db_system* s, uint64_t nsteps) {
@@ -1282,8 +1306,7 @@ void db_destroy(db_system* s) {
         for (auto e : s->timing.pool) (void)hipEventDestroy(e);
         if (s->ev_out) (void)hipEventDestroy(s->ev_out);
         if (s->ev_back) (void)hipEventDestroy(s->ev_back);
-        for (auto e : s->path_ev)
-            if (e) (void)hipEventDestroy(e);
+        s->batch.drop();
         if (s->err_h) (void)hipHostFree(s->err_h);
         for (void* p : s->allocs) (void)hipFree(p);
         if (s->own_stream) (void)hipStreamDestroy(s->own_stream);
@@ -1619,12 +1642,13 @@ static db_status commit_impl(db_system* s) {
     DALLOC(s, s->stage, 3 * (size_t)n);
     {
         void* h = nullptr;
-        if (hipHostMalloc(&h, 16 + kPinnedWords * sizeof(unsigned long long), hipHostMallocDefault) != hipSuccess) {
+        if (hipHostMalloc(&h, 16 + kPinnedWords * sizeof(unsigned long long) + sizeof(BatchState), hipHostMallocDefault) != hipSuccess) {
             (void)hipGetLastError();
             return fail(s, DB_ENOMEM, "pinned host allocation failed");
         }
         s->err_h = (uint32_t*)h;
         s->obs_h = (unsigned long long*)((char*)h + 16);
+        s->one_h = (BatchState*)(s->obs_h + kPinnedWords);
     }
     s->val_sum.assign(s->ntypes, 0.0);
     for (uint32_t i = 0; i < n; ++i) s->val_sum[s->type[i]] += s->types[s->type[i]].valence;
@@ -1662,11 +1686,16 @@ db_status db_step(db_system* s, uint64_t nsteps) {
     db_status st = ready(s);
     if (st != DB_OK) return st;
     HIPCHK(s, hipSetDevice(s->device));
-    st = run_steps(s, nsteps);
+    if (nsteps && one_group(s)) {
+        st = run_one_group(s, nsteps);
+        if (st != DB_OK) return st;
+        HIPCHK(s, hipStreamSynchronize(s->stream));
+        s->tail = false;
+        return report_errors(s, s->one_h->err);
+    }
+    st = run_grid(s, nsteps);
     if (st != DB_OK) return st;
-    st = check_errors(s);
-    if (st == DB_OK) settle_path(s);
-    return st;
+    return check_errors(s);
 }
 
 }  // extern "C"
@@ -1716,50 +1745,63 @@ db_status batch_check(db_system* const* systems, uint32_t count) {
     for (uint32_t k = 0; k < count; ++k) {
         db_status st = ready(systems[k]);
         if (st != DB_OK) return st;
-        for (uint32_t q = 0; q < k; ++q)
-            if (systems[q] == systems[k]) return fail(systems[k], DB_EINVAL, "system listed twice in a batch");
         if (systems[k]->device != systems[0]->device)
             return fail(systems[k], DB_EINVAL, "batched systems must share one device");
+    }
+    std::vector<db_system*> sorted(systems, systems + count);
+    std::sort(sorted.begin(), sorted.end());
+    const auto twice = std::adjacent_find(sorted.begin(), sorted.end());
+    if (twice != sorted.end()) return fail(*twice, DB_EINVAL, "system listed twice in a batch");
+    return DB_OK;
+}
+
+// Room for `count` systems and `classes` concurrent chains in s0's workspace.
+db_status batch_workspace(db_system* s0, uint32_t count, size_t classes) {
+    BatchWork& W = s0->batch;
+    if (count > W.cap) {
+        W.drop_buffers();
+        if (hipMalloc(&W.items, count * sizeof(BatchItem)) != hipSuccess ||
+            hipHostMalloc((void**)&W.items_h, count * sizeof(BatchItem), hipHostMallocDefault) != hipSuccess ||
+            hipHostMalloc((void**)&W.state, count * sizeof(BatchState), hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            W.drop_buffers();
+            return fail(s0, DB_ENOMEM, "batch: allocation failed");
+        }
+        W.cap = count;
+    }
+    if (!W.fork) HIPCHK(s0, hipEventCreateWithFlags(&W.fork, hipEventDisableTiming));
+    if (!W.t_a) HIPCHK(s0, hipEventCreate(&W.t_a));
+    if (!W.t_b) HIPCHK(s0, hipEventCreate(&W.t_b));
+    while (W.streams.size() + 1 < classes) {
+        hipStream_t q = nullptr;
+        HIPCHK(s0, hipStreamCreateWithFlags(&q, hipStreamNonBlocking));
+        W.streams.push_back(q);
+    }
+    while (W.joins.size() + 1 < classes) {
+        hipEvent_t e = nullptr;
+        HIPCHK(s0, hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        W.joins.push_back(e);
     }
     return DB_OK;
 }
 
-// Device buffers, streams, events and graph of one batch run, released on
-// every exit path.
-struct BatchRun {
-    BatchItem* items = nullptr;
-    BatchState* state = nullptr;
-    std::vector<hipStream_t> streams;      // extra streams of the 2nd, 3rd ... occupied class
-    std::vector<hipEvent_t> events;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-    ~BatchRun() {
-        if (exec) (void)hipGraphExecDestroy(exec);
-        if (graph) (void)hipGraphDestroy(graph);
-        for (hipEvent_t e : events) (void)hipEventDestroy(e);
-        for (hipStream_t q : streams) (void)hipStreamDestroy(q);
-        if (items) (void)hipFree(items);
-        if (state) (void)hipFree(state);
-    }
-    hipEvent_t event() {
-        hipEvent_t e = nullptr;
-        if (hipEventCreate(&e) != hipSuccess) return nullptr;
-        events.push_back(e);
-        return e;
-    }
-};
-
-constexpr uint32_t kBatchChunk = 2000;     // steps per launch
-
 // Every system advanced by nsteps under `plan`; *ms (may be null) receives
-// the device time of the graph.  On a device error every system is marked
-// dead; per-system errors are checked afterwards.
+// the device time.  On a device error every system is marked dead;
+// per-system errors are checked afterwards.  The launches go straight to the
+// streams: captured into a graph of their own on every call, with buffers
+// allocated and freed around it, a call cost 90 us before its first step, and
+// 15 us more per system to read its error words one by one.
 db_status run_batch(db_system* const* systems, uint32_t count, uint64_t nsteps, const db_batch_plan& plan,
                     float* ms) {
     db_system* s0 = systems[0];
     if (ms) *ms = 0.0f;
     HIPCHK(s0, hipSetDevice(s0->device));
-    for (uint32_t k = 0; k < count; ++k) HIPCHK(systems[k], hipStreamSynchronize(systems[k]->stream));
+    for (uint32_t k = 0; k < count; ++k) {
+        db_system* s = systems[k];
+        if (!s->tail && s->stream == s->own_stream) continue;      // nothing in flight
+        HIPCHK(s, hipStreamSynchronize(s->stream));
+        s->tail = false;
+    }
     if (nsteps == 0) return DB_OK;
     // classes in plan order; largest systems first inside a class, so that
     // their workgroups start in the first wave
@@ -1768,130 +1810,117 @@ db_status run_batch(db_system* const* systems, uint32_t count, uint64_t nsteps, 
     std::vector<std::vector<uint32_t>> groups(2 * plan.n_classes);
     for (uint32_t k = 0; k < count; ++k)
         groups[2 * class_of(plan, systems[k]->n) + (systems[k]->P.ext ? 1 : 0)].push_back(k);
+    struct Group {
+        uint32_t first, size, threads;
+        bool full, sort;       // the kernel's full variant; some system of it is not resident
+        size_t lds;            // dynamic LDS (0: positions stay in memory)
+    };
     std::vector<uint32_t> order;
-    std::vector<std::pair<uint32_t, uint32_t>> spans;    // (offset, size) of each occupied group
-    std::vector<uint32_t> threads, full;
+    std::vector<Group> runs;
     for (uint32_t g = 0; g < 2 * plan.n_classes; ++g) {
         auto& v = groups[g];
         if (v.empty()) continue;
         std::stable_sort(v.begin(), v.end(), [&](uint32_t a, uint32_t b) { return systems[a]->n > systems[b]->n; });
-        spans.emplace_back((uint32_t)order.size(), (uint32_t)v.size());
-        threads.push_back(plan.threads[g / 2]);
-        full.push_back(g & 1u);
+        runs.push_back(Group{(uint32_t)order.size(), (uint32_t)v.size(), plan.threads[g / 2], (g & 1u) != 0u, false, 0});
         order.insert(order.end(), v.begin(), v.end());
+    }
+    db_status st = batch_workspace(s0, count, runs.size());
+    if (st != DB_OK) return st;
+    BatchWork& W = s0->batch;
+    for (uint32_t k = 0; k < count; ++k) {
+        const db_system* s = systems[order[k]];
+        W.items_h[k].P = s->P;
+        W.items_h[k].D = s->D;
+        W.items_h[k].resident = 0u;
+        W.state[k] = BatchState{};
+        W.state[k].t = s->step;
+        W.state[k].cur_x = s->cur_x;
+        W.state[k].cur_list = s->cur_list;
     }
     // Positions in LDS (the LX variant of k_batch) wherever the largest
     // system of a group fits in the LDS share its workgroup has anyway: the
     // registers of a step let one 1024-thread workgroup, two of 512 or four
-    // of 256 share a CU.
-    std::vector<size_t> xlds(spans.size(), 0);
-    for (size_t g = 0; g < spans.size(); ++g) {
-        const size_t nmax = systems[order[spans[g].first]]->n;
-        const size_t share = (size_t)kBatchLdsTotal * threads[g] / kBatchMaxThreads;
-        if (nmax * sizeof(float4) + kBatchLdsStatic <= share) xlds[g] = nmax * sizeof(float4);
-    }
-    std::vector<BatchItem> items(count);
-    std::vector<BatchState> state(count);
-    for (uint32_t k = 0; k < count; ++k) {
-        const db_system* s = systems[order[k]];
-        items[k].P = s->P;
-        items[k].D = s->D;
-        state[k].t = s->step;
-        state[k].cur_x = s->cur_x;
-        state[k].cur_list = s->cur_list;
-    }
-    db_status st = DB_OK;
-    {
-        BatchRun R;
-        auto dev_fail = [&](const char* what) {
-            for (uint32_t k = 0; k < count; ++k) systems[k]->dead = true;
-            return fail(s0, DB_EDEVICE, "batch: %s", what);
-        };
-        if (hipMalloc(&R.items, count * sizeof(BatchItem)) != hipSuccess ||
-            hipMalloc(&R.state, count * sizeof(BatchState)) != hipSuccess)
-            return fail(s0, DB_ENOMEM, "batch: device allocation failed");
-        if (hipMemcpyAsync(R.items, items.data(), count * sizeof(BatchItem), hipMemcpyHostToDevice, s0->stream) !=
-                hipSuccess ||
-            hipMemcpyAsync(R.state, state.data(), count * sizeof(BatchState), hipMemcpyHostToDevice, s0->stream) !=
-                hipSuccess ||
-            hipStreamSynchronize(s0->stream) != hipSuccess)
-            return dev_fail("upload failed");
-        for (size_t g = 1; g < spans.size(); ++g) {
-            hipStream_t q = nullptr;
-            if (hipStreamCreateWithFlags(&q, hipStreamNonBlocking) != hipSuccess) return dev_fail("stream creation failed");
-            R.streams.push_back(q);
+    // of 256 share a CU.  Systems small enough for the resident form take it
+    // there; a group of nothing else needs only the threads they use.
+    for (Group& r : runs) {
+        const size_t share = (size_t)kBatchLdsTotal * r.threads / kBatchMaxThreads - kBatchLdsStatic;
+        if (systems[order[r.first]]->n * sizeof(float4) > share) {
+            r.sort = true;
+            continue;
         }
-        hipEvent_t fork = R.event(), t_a = R.event(), t_b = R.event();
-        std::vector<hipEvent_t> join;
-        for (size_t g = 1; g < spans.size(); ++g) join.push_back(R.event());
-        if (!fork || !t_a || !t_b || std::find(join.begin(), join.end(), nullptr) != join.end())
-            return dev_fail("event creation failed");
-        // dynamic LDS beyond the default limit for the LX variants (a
-        // runtime that needs no such opt-in may refuse the call: ignored)
-        {
-            const int most = (int)(kBatchLdsTotal - kBatchLdsStatic);
-            if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_batch<false, true>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, most) != hipSuccess ||
-                hipFuncSetAttribute(reinterpret_cast<const void*>(&k_batch<true, true>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, most) != hipSuccess)
-                (void)hipGetLastError();
-        }
-        // capture: one branch per occupied group, a chain of launches each
-        bool ok = hipStreamBeginCapture(s0->stream, hipStreamCaptureModeThreadLocal) == hipSuccess;
-        if (ok) {
-            ok = hipEventRecord(fork, s0->stream) == hipSuccess;
-            for (size_t g = 1; ok && g < spans.size(); ++g) ok = hipStreamWaitEvent(R.streams[g - 1], fork, 0) == hipSuccess;
-            for (size_t g = 0; ok && g < spans.size(); ++g) {
-                hipStream_t q = g ? R.streams[g - 1] : s0->stream;
-                for (uint64_t done = 0; ok && done < nsteps;) {
-                    const uint32_t chunk = (uint32_t)std::min<uint64_t>(kBatchChunk, nsteps - done);
-                    // renumber every system in cell order before each chunk
-                    hipLaunchKernelGGL(k_batch_sort, dim3(spans[g].second), dim3(threads[g]), 0, q,
-                                       (const BatchItem*)(R.items + spans[g].first),
-                                       (const BatchState*)(R.state + spans[g].first));
-                    const BatchItem* it = R.items + spans[g].first;
-                    BatchState* sg = R.state + spans[g].first;
-                    const dim3 grid(spans[g].second), blk(threads[g]);
-                    const size_t lds = xlds[g];
-                    if (full[g] && lds)
-                        hipLaunchKernelGGL((k_batch<true, true>), grid, blk, lds, q, it, sg, chunk);
-                    else if (full[g])
-                        hipLaunchKernelGGL((k_batch<true, false>), grid, blk, 0, q, it, sg, chunk);
-                    else if (lds)
-                        hipLaunchKernelGGL((k_batch<false, true>), grid, blk, lds, q, it, sg, chunk);
-                    else
-                        hipLaunchKernelGGL((k_batch<false, false>), grid, blk, 0, q, it, sg, chunk);
-                    ok = hipGetLastError() == hipSuccess;
-                    done += chunk;
-                }
+        uint32_t used = 64u;
+        for (uint32_t k = r.first; k < r.first + r.size; ++k) {
+            const db_system* s = systems[order[k]];
+            uint32_t tpp = resident_tpp(s, r.threads);
+            size_t need = tpp ? res_lds_bytes(s->n, s->P.ncell, tpp) : 0;
+            if (tpp == 2u && need > share) {
+                tpp = 1u;
+                need = res_lds_bytes(s->n, s->P.ncell, tpp);
             }
-            for (size_t g = 1; ok && g < spans.size(); ++g)
-                ok = hipEventRecord(join[g - 1], R.streams[g - 1]) == hipSuccess &&
-                     hipStreamWaitEvent(s0->stream, join[g - 1], 0) == hipSuccess;
-            hipGraph_t graph = nullptr;
-            const bool ended = hipStreamEndCapture(s0->stream, &graph) == hipSuccess;
-            R.graph = graph;
-            ok = ok && ended && graph;
+            if (!tpp || need > share) {
+                tpp = 0u;
+                need = s->n * sizeof(float4);
+                r.sort = true;
+            }
+            W.items_h[k].resident = tpp;
+            used = std::max(used, (s->n * tpp + 63u) & ~63u);
+            r.lds = std::max(r.lds, need);
         }
-        if (!ok) {
-            (void)hipGetLastError();
-            return dev_fail("graph capture failed");
-        }
-        if (hipGraphInstantiate(&R.exec, R.graph, nullptr, nullptr, 0) != hipSuccess) return dev_fail("graph instantiation failed");
-        if (hipEventRecord(t_a, s0->stream) != hipSuccess || hipGraphLaunch(R.exec, s0->stream) != hipSuccess ||
-            hipEventRecord(t_b, s0->stream) != hipSuccess || hipStreamSynchronize(s0->stream) != hipSuccess)
-            return dev_fail("launch failed");
-        if (ms) (void)hipEventElapsedTime(ms, t_a, t_b);
+        if (!r.sort) r.threads = used;
     }
+    auto dev_fail = [&](const char* what) {
+        (void)hipGetLastError();
+        for (uint32_t k = 0; k < count; ++k) systems[k]->dead = true;
+        return fail(s0, DB_EDEVICE, "batch: %s", what);
+    };
+    allow_lds(reinterpret_cast<const void*>(&k_batch<false, true>));
+    allow_lds(reinterpret_cast<const void*>(&k_batch<true, true>));
+    bool ok = hipMemcpyAsync(W.items, W.items_h, count * sizeof(BatchItem), hipMemcpyHostToDevice, s0->stream) == hipSuccess;
+    if (ms) ok = ok && hipEventRecord(W.t_a, s0->stream) == hipSuccess;
+    // one chain per occupied group, each on its own stream
+    if (runs.size() > 1) ok = ok && hipEventRecord(W.fork, s0->stream) == hipSuccess;
+    for (size_t g = 0; ok && g < runs.size(); ++g) {
+        const Group& r = runs[g];
+        hipStream_t q = g ? W.streams[g - 1] : s0->stream;
+        if (g) ok = hipStreamWaitEvent(q, W.fork, 0) == hipSuccess;
+        const BatchItem* it = W.items + r.first;
+        BatchState* sg = W.state + r.first;
+        const dim3 grid(r.size), blk(r.threads);
+        for (uint64_t done = 0; ok && done < nsteps;) {
+            const uint32_t chunk = (uint32_t)std::min<uint64_t>(kBatchChunk, nsteps - done);
+            // renumber every system in cell order before each chunk
+            if (r.sort) hipLaunchKernelGGL(k_batch_sort, grid, blk, 0, q, it, (const BatchState*)sg);
+            if (r.full && r.lds) hipLaunchKernelGGL((k_batch<true, true>), grid, blk, r.lds, q, it, sg, chunk);
+            else if (r.full) hipLaunchKernelGGL((k_batch<true, false>), grid, blk, 0, q, it, sg, chunk);
+            else if (r.lds) hipLaunchKernelGGL((k_batch<false, true>), grid, blk, r.lds, q, it, sg, chunk);
+            else hipLaunchKernelGGL((k_batch<false, false>), grid, blk, 0, q, it, sg, chunk);
+            ok = hipGetLastError() == hipSuccess;
+            done += chunk;
+        }
+        if (g)
+            ok = ok && hipEventRecord(W.joins[g - 1], q) == hipSuccess &&
+                 hipStreamWaitEvent(s0->stream, W.joins[g - 1], 0) == hipSuccess;
+    }
+    if (ms) ok = ok && hipEventRecord(W.t_b, s0->stream) == hipSuccess;
+    if (!ok) {
+        (void)hipDeviceSynchronize();      // nothing of a broken batch stays in flight
+        return dev_fail("launch failed");
+    }
+    if (hipStreamSynchronize(s0->stream) != hipSuccess) return dev_fail("run failed");
+    if (ms) (void)hipEventElapsedTime(ms, W.t_a, W.t_b);
     for (uint32_t k = 0; k < count; ++k) {
-        db_system* s = systems[k];
+        db_system* s = systems[order[k]];
         s->step += nsteps;
         s->cur_x ^= (int)(nsteps & 1u);
         s->cur_list = (int)((s->cur_list + nsteps) % 3);
-        s->tags_dirty = true;              // renumbered by k_batch_sort
+        if (!W.items_h[k].resident) s->tags_dirty = true;          // renumbered by k_batch_sort
     }
+    // the first error in list order, every system's message in its own handle
+    std::vector<uint32_t> at(count);
+    for (uint32_t k = 0; k < count; ++k) at[order[k]] = k;
     for (uint32_t k = 0; k < count; ++k) {
-        const db_status e = check_errors(systems[k]);
+        flush_timing(systems[k]);
+        const db_status e = report_errors(systems[k], W.state[at[k]].err);
         if (e != DB_OK && st == DB_OK) st = e;
     }
     return st;
@@ -2234,6 +2263,7 @@ static db_status read_vec_device(db_system* s, float* out3, void* stream, int mo
         HIPCHK(s, hipEventRecord(s->ev_out, own));
         HIPCHK(s, hipStreamWaitEvent(q, s->ev_out, 0));
     }
+    s->tail = true;
     s->stream = q;                         // the launches below go to the caller's stream
     if (mode == 0) LAUNCH(s, k_gather3, grid_of(s->n), kBlock, s->P, s->D, out3, s->cur_x);
     else if (mode == 1) LAUNCH_EVAL(s, 1, s->cur_x, 0u, out3);
@@ -2395,6 +2425,7 @@ db_status db_bond_reference(db_system* s) {
     LAUNCH(s, k_bond_ref, grid_of(s->n), kBlock, s->P, s->D, s->bref, s->cur_x);
     HIPCHK(s, hipGetLastError());
     s->have_ref = true;
+    s->tail = true;
     return DB_OK;
 }
 

@@ -236,17 +236,18 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* t
     return base + x - v;
 }
 
-// Rest of one BAOAB step for particle i once its force F at x_t is known:
-// closing half kick of step t-1 (B), opening half kick (B), half drift (A),
-// Ornstein-Uhlenbeck velocity update with Philox Gaussians (O), half drift
-// (A), wrap into [-L/2, L/2), then write x_{t+1} (returned in po) and u
-// (with the particle's tag in its w word, where the next step reads it).
-// Returns m v^2 in 2^-32 fixed point when accum_ke is set.
+// Rest of one BAOAB step for a particle at pi once its force F at x_t is
+// known: closing half kick of step t-1 (B), opening half kick (B), half drift
+// (A), Ornstein-Uhlenbeck velocity update with Philox Gaussians (O), half
+// drift (A), wrap into [-L/2, L/2).  Gives x_{t+1} (type in the w word), the
+// velocity record (the particle's tag in its w word, where the next step
+// reads it) and the periodic images crossed; returns m v^2 in 2^-32 fixed
+// point when accum_ke is set.
 template <class Tabs>
-__device__ __forceinline__ unsigned long long advance_particle(const Params& P, const Tabs& T, const Dev& D, int xin,
-                                                               uint32_t i, float4 pi, uint32_t ti,
-                                                               Force3 F, float4 u, uint32_t tag,
-                                                               unsigned long long s, int accum_ke, float4& po) {
+__device__ __forceinline__ unsigned long long advance_state(const Params& P, const Tabs& T, float4 pi, uint32_t ti,
+                                                            Force3 F, float4 u, uint32_t tag, unsigned long long s,
+                                                            int accum_ke, float4& po, float4& uo, int& ix, int& iy,
+                                                            int& iz) {
     // The order of every rounding is written out (explicit fmaf, no implicit
     // contraction), so that the step gives the same bits in every kernel that
     // inlines it.
@@ -273,24 +274,37 @@ __device__ __forceinline__ unsigned long long advance_particle(const Params& P, 
     x = fmaf(P.h, vx, x);
     y = fmaf(P.h, vy, y);
     z = fmaf(P.h, vz, z);
-    int ix = 0, iy = 0, iz = 0;
+    ix = iy = iz = 0;
     if (x < -P.halfLf) { x += P.Lf; --ix; }
     if (x >= P.halfLf) { x -= P.Lf; ++ix; }
     if (y < -P.halfLf) { y += P.Lf; --iy; }
     if (y >= P.halfLf) { y -= P.Lf; ++iy; }
     if (z < -P.halfLf) { z += P.Lf; --iz; }
     if (z >= P.halfLf) { z -= P.Lf; ++iz; }
+    po = make_float4(x, y, z, __uint_as_float(ti));
+    uo = make_float4(vx, vy, vz, __uint_as_float(tag));   // the tag rides in the w word
+    if (!accum_ke) return 0ull;
+    const double v2 = ((double)vx * vx + (double)vy * vy) + (double)vz * vz;
+    return (unsigned long long)rint((double)T.mass[ti] * v2 * 4294967296.0);
+}
+
+// The same for particle i, its new state written to memory.
+template <class Tabs>
+__device__ __forceinline__ unsigned long long advance_particle(const Params& P, const Tabs& T, const Dev& D, int xin,
+                                                               uint32_t i, float4 pi, uint32_t ti,
+                                                               Force3 F, float4 u, uint32_t tag,
+                                                               unsigned long long s, int accum_ke, float4& po) {
+    float4 uo;
+    int ix, iy, iz;
+    const unsigned long long ke = advance_state(P, T, pi, ti, F, u, tag, s, accum_ke, po, uo, ix, iy, iz);
     if (ix | iy | iz) {
         D.img[i] += ix;
         D.img[P.n + i] += iy;
         D.img[2 * P.n + i] += iz;
     }
-    po = make_float4(x, y, z, __uint_as_float(ti));
     D.x[xin ^ 1][i] = po;
-    D.u[i] = make_float4(vx, vy, vz, __uint_as_float(tag));   // the tag rides in the w word
-    if (!accum_ke) return 0ull;
-    const double v2 = ((double)vx * vx + (double)vy * vy) + (double)vz * vz;
-    return (unsigned long long)rint((double)T.mass[ti] * v2 * 4294967296.0);
+    D.u[i] = uo;
+    return ke;
 }
 
 constexpr int kTileThreads = 512;
@@ -619,15 +633,10 @@ __device__ __forceinline__ void stage_tabs(const Dev& D, StepTabs& T, uint32_t t
 // spent more issue on per-lane branches than on the forces (k_step 20.2 ->
 // 18.6 us at 200k particles, 7.6 -> 6.4 at 10 500, k_step1 187 -> 166 at 4 M;
 // 226 -> 99 branches in k_step<4>).
-__device__ __forceinline__ bool pair_force_f32(const Params& P, const StepTabs& T, uint32_t* err, float4 pi,
-                                               float4 pj, uint32_t ti, bool valid, long long& fx, long long& fy,
-                                               long long& fz) {
+// The FP32 force of a pair with separation d and constants c, where `in`.
+__device__ __forceinline__ void near_force(uint32_t* err, float4 c, float dx, float dy, float dz, float r2, bool in,
+                                           long long& fx, long long& fy, long long& fz) {
 #pragma clang fp contract(off)
-    const float4 c = T.pf[(int)ti * kMaxTypes + (int)type_of(pj)];
-    const float dx = pj.x - pi.x, dy = pj.y - pi.y, dz = pj.z - pi.z;
-    const bool direct = fmaxf(fmaxf(fabsf(dx), fabsf(dy)), fabsf(dz)) <= P.halfLf;
-    float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-    const bool in = valid && direct && r2 < c.y;
     const float ir2 = __builtin_amdgcn_rcpf(r2);
     const float sr2 = c.z * ir2;
     const float sr6 = sr2 * sr2 * sr2;
@@ -638,11 +647,50 @@ __device__ __forceinline__ bool pair_force_f32(const Params& P, const StepTabs& 
     fx -= fix_of((double)px);
     fy -= fix_of((double)py);
     fz -= fix_of((double)pz);
-    if (!direct) {
-        const float ix = mi_delta_f(pi.x, pj.x, P), iy = mi_delta_f(pi.y, pj.y, P), iz = mi_delta_f(pi.z, pj.z, P);
-        r2 = fmaf(iz, iz, fmaf(iy, iy, ix * ix));
-    }
+}
+
+__device__ __forceinline__ float pair_r2(float dx, float dy, float dz) {
+#pragma clang fp contract(off)
+    return fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+}
+
+__device__ __forceinline__ bool pair_direct(const Params& P, float dx, float dy, float dz) {
+    return fmaxf(fmaxf(fabsf(dx), fabsf(dy)), fabsf(dz)) <= P.halfLf;
+}
+
+// r^2 of a pair for the screen of the FP64 evaluation.
+__device__ __forceinline__ float pair_r2_image(const Params& P, float4 pi, float4 pj) {
+    return pair_r2(mi_delta_f(pi.x, pj.x, P), mi_delta_f(pi.y, pj.y, P), mi_delta_f(pi.z, pj.z, P));
+}
+
+__device__ __forceinline__ bool pair_force_f32(const Params& P, const StepTabs& T, uint32_t* err, float4 pi,
+                                               float4 pj, uint32_t ti, bool valid, long long& fx, long long& fy,
+                                               long long& fz) {
+    const float4 c = T.pf[(int)ti * kMaxTypes + (int)type_of(pj)];
+    const float dx = pj.x - pi.x, dy = pj.y - pi.y, dz = pj.z - pi.z;
+    const bool direct = pair_direct(P, dx, dy, dz);
+    float r2 = pair_r2(dx, dy, dz);
+    const bool in = valid && direct && r2 < c.y;
+    near_force(err, c, dx, dy, dz, r2, in, fx, fy, fz);
+    if (!direct) r2 = pair_r2_image(P, pi, pj);
     return valid && !in && !(r2 >= c.x);
+}
+
+// The same in two steps, for lanes with many candidates of which few are
+// inside the cutoff: which evaluation the pair needs, and the FP32 one.
+enum : uint32_t { kPairFar = 0u, kPairNear = 1u, kPairExact = 2u };
+__device__ __forceinline__ uint32_t pair_screen(const Params& P, const StepTabs& T, float4 pi, float4 pj, uint32_t ti) {
+    const float4* c = &T.pf[(int)ti * kMaxTypes + (int)type_of(pj)];
+    const float dx = pj.x - pi.x, dy = pj.y - pi.y, dz = pj.z - pi.z;
+    const bool direct = pair_direct(P, dx, dy, dz);
+    float r2 = pair_r2(dx, dy, dz);
+    if (!direct) r2 = pair_r2_image(P, pi, pj);
+    return direct && r2 < c->y ? kPairNear : (r2 >= c->x ? kPairFar : kPairExact);
+}
+__device__ __forceinline__ void pair_force_near(const Params& P, const StepTabs& T, uint32_t* err, float4 pi, float4 pj,
+                                                uint32_t ti, long long& fx, long long& fy, long long& fz) {
+    const float dx = pj.x - pi.x, dy = pj.y - pi.y, dz = pj.z - pi.z;
+    near_force(err, T.pf[(int)ti * kMaxTypes + (int)type_of(pj)], dx, dy, dz, pair_r2(dx, dy, dz), true, fx, fy, fz);
 }
 
 __device__ __forceinline__ void pair_force_f64(const Params& P, const StepTabs& T, uint32_t* err, float4 pi,
@@ -1174,66 +1222,52 @@ __device__ __forceinline__ unsigned long long match_key(const Params& P, int a, 
     return ((unsigned long long)w.w0 << 32) | tgi;
 }
 
-// Proposal of site i for reaction a (Sec. 2.3, Fig. sweep a): TPP threads
-// share the site (`lane` = this thread's rank in the group); each scans every
-// TPP-th neighbour-list entry and the group keeps the lexicographic minimum of
-// (|r - r0|, tag).  Sites that cannot propose leave after loading their
-// position and occupancy.  For a proposer, the loads that need only i (the
-// first Q list entries per thread, the bond words) are issued together, then
-// everything the candidates need (position, occupancy, molecule, tag), so
-// that it waits for about four memory round trips.  The group issues 4 list
-// entries up front (TPP when TPP > 4): lists hold a few entries (1.7 on
-// average in the gel), and every entry issued is a separate row of the
-// slot-major list, a cache line or more for the group's sites, which at
-// millions of sites is most of the kernel's traffic.  Returns the chosen
-// partner (the same on every thread of the group) or -1; `tgi` receives the
-// site's tag.
-template <int TPP, int Q = (TPP < 4 ? 4 / TPP : 1)>
-__device__ __forceinline__ int propose_site(const Params& P, const Dev& D, int a, const float4* __restrict__ X,
-                                            uint32_t i, uint32_t lane, uint32_t& tgi_out) {
-    const size_t n = P.n;
-    // sites that cannot propose (wrong type, full valence) leave after one load
-    const float4 pi = X[i];
-    const uint32_t occ_i = D.occ[i];
-    const uint32_t ti = type_of(pi);
-    const uint32_t ta = P.ra[a], tb = P.rb[a];
-    if (ti != ta && ti != tb) return -1;
-    if (occ_i >= P.cap[ti]) return -1;
-    const uint32_t m = D.nl_cnt[i];
-    uint32_t nb[Q];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        const uint32_t k = lane + (uint32_t)q * TPP;
-        nb[q] = k < P.nlmax ? D.nl[k * n + i] : 0u;
-    }
-    // partners already bonded to i (any bond) are excluded; slots beyond the
-    // site's valence are empty
-    uint32_t mine[kMaxValence + kMaxStatic];
-#pragma unroll
-    for (int k = 0; k < kMaxValence; ++k)
-        mine[k] = (uint32_t)k < P.cap_max ? (D.dyn[(size_t)k * n + i] & kIdxMask) : kIdxMask;
-#pragma unroll
-    for (int k = 0; k < kMaxStatic; ++k)
-        mine[kMaxValence + k] = (uint32_t)k < P.stat_max ? (D.stat[(size_t)k * n + i] & kIdxMask) : kIdxMask;
-    const bool avoid = P.rself[a] != 0u;
-    const uint32_t mol_i = avoid ? D.mol[i] : 0u;
-    const uint32_t tgi = D.tag[i];
-    const uint32_t want = ti == ta ? tb : ta;
-    const uint32_t cap_want = P.cap[want];
-    const double rmin = P.rmin[a], rmax = P.rmax[a], r0 = P.r0[a];
-    const float rmax2 = P.rmax2_pre[a], rmin2 = P.rmin2_pre[a];
+// The scan of one site's candidates for a proposal (Sec. 2.3, Fig. sweep a):
+// TPP threads share the site, each considers its own candidates, and the
+// group keeps the lexicographic minimum of (|r - r0|, tag).
+template <int TPP>
+struct ProposeScan {
     // the best candidate so far; its tag is read only when an exact tie of
     // |r - r0| needs it (kTagUnread until then), so that a candidate costs a
     // position and an occupancy gather (and its molecule only when the
     // reaction avoids its own molecule)
-    constexpr uint32_t kTagUnread = 0xFFFFFFFFu;   // tags are below 2^24
+    static constexpr uint32_t kTagUnread = 0xFFFFFFFFu;   // tags are below 2^24
+    float4 pi;
+    uint32_t mine[kMaxValence + kMaxStatic];
+    bool avoid;
+    uint32_t mol_i, want, cap_want;
+    double rmin, rmax, r0;
+    float rmax2, rmin2;
     double best_score = 0.0;
     uint32_t best_tag = kTagUnread;
     int best_j = -1;
+
+    __device__ __forceinline__ void begin(const Params& P, const Dev& D, int a, uint32_t i, float4 p, uint32_t ti) {
+        const size_t n = P.n;
+        pi = p;
+        // partners already bonded to i (any bond) are excluded; slots beyond the
+        // site's valence are empty
+#pragma unroll
+        for (int k = 0; k < kMaxValence; ++k)
+            mine[k] = (uint32_t)k < P.cap_max ? (D.dyn[(size_t)k * n + i] & kIdxMask) : kIdxMask;
+#pragma unroll
+        for (int k = 0; k < kMaxStatic; ++k)
+            mine[kMaxValence + k] = (uint32_t)k < P.stat_max ? (D.stat[(size_t)k * n + i] & kIdxMask) : kIdxMask;
+        avoid = P.rself[a] != 0u;
+        mol_i = avoid ? D.mol[i] : 0u;
+        want = ti == P.ra[a] ? P.rb[a] : P.ra[a];
+        cap_want = P.cap[want];
+        rmin = P.rmin[a];
+        rmax = P.rmax[a];
+        r0 = P.r0[a];
+        rmax2 = P.rmax2_pre[a];
+        rmin2 = P.rmin2_pre[a];
+    }
     // candidate j: partner type, free, not yet bonded to i, other molecule if
     // required, inside [r_min, r_max] (FP32 screen, then the exact FP64 r);
     // keep the smallest (|r - r0|, tag)
-    auto consider = [&](uint32_t j, float4 pj, uint32_t occ_j, uint32_t mol_j) {
+    __device__ __forceinline__ void consider(const Params& P, const Dev& D, uint32_t j, float4 pj, uint32_t occ_j,
+                                             uint32_t mol_j) {
         if (type_of(pj) != want) return;
         if (occ_j >= cap_want) return;
         bool bonded = false;
@@ -1264,7 +1298,65 @@ __device__ __forceinline__ int propose_site(const Params& P, const Dev& D, int a
                 best_j = (int)j;
             }
         }
-    };
+    }
+    // The group's choice (the same on every thread of it), or -1.
+    __device__ __forceinline__ int finish(const Dev& D) {
+#pragma unroll
+        for (int o = TPP / 2; o >= 1; o >>= 1) {
+            const double os = __shfl_xor(best_score, o, 64);
+            uint32_t ot = __shfl_xor(best_tag, o, 64);
+            const int oj2 = __shfl_xor(best_j, o, 64);
+            if (oj2 < 0) continue;
+            bool take = best_j < 0 || os < best_score;
+            if (!take && os == best_score) {            // tie across the group: compare tags
+                if (ot == kTagUnread) ot = D.tag[oj2];
+                if (best_tag == kTagUnread) best_tag = D.tag[best_j];
+                take = ot < best_tag;
+            }
+            if (take) {
+                best_score = os;
+                best_tag = ot;
+                best_j = oj2;
+            }
+        }
+        return best_j;
+    }
+};
+
+// Proposal of site i for reaction a from its neighbour list in memory: TPP
+// threads share the site (`lane` = this thread's rank in the group), each
+// scans every TPP-th entry.  Sites that cannot propose leave after loading
+// their position and occupancy.  For a proposer, the loads that need only i
+// (the first Q list entries per thread, the bond words) are issued together,
+// then everything the candidates need (position, occupancy, molecule), so
+// that it waits for about four memory round trips.  The group issues 4 list
+// entries up front (TPP when TPP > 4): lists hold a few entries (1.7 on
+// average in the gel), and every entry issued is a separate row of the
+// slot-major list, a cache line or more for the group's sites, which at
+// millions of sites is most of the kernel's traffic.  Returns the chosen
+// partner (the same on every thread of the group) or -1; `tgi` receives the
+// site's tag.
+template <int TPP, int Q = (TPP < 4 ? 4 / TPP : 1)>
+__device__ __forceinline__ int propose_site(const Params& P, const Dev& D, int a, const float4* __restrict__ X,
+                                            uint32_t i, uint32_t lane, uint32_t& tgi_out) {
+    const size_t n = P.n;
+    // sites that cannot propose (wrong type, full valence) leave after one load
+    const float4 pi = X[i];
+    const uint32_t occ_i = D.occ[i];
+    const uint32_t ti = type_of(pi);
+    if (ti != P.ra[a] && ti != P.rb[a]) return -1;
+    if (occ_i >= P.cap[ti]) return -1;
+    const uint32_t m = D.nl_cnt[i];
+    uint32_t nb[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const uint32_t k = lane + (uint32_t)q * TPP;
+        nb[q] = k < P.nlmax ? D.nl[k * n + i] : 0u;
+    }
+    ProposeScan<TPP> scan;
+    scan.begin(P, D, a, i, pi, ti);
+    const bool avoid = scan.avoid;
+    const uint32_t tgi = D.tag[i];
     // the neighbour list (rebuilt right after every step that needed it) holds
     // every pair within r_search >= r_max
     float4 pj[Q];
@@ -1278,31 +1370,13 @@ __device__ __forceinline__ int propose_site(const Params& P, const Dev& D, int a
     }
 #pragma unroll
     for (int q = 0; q < Q; ++q)
-        if (lane + (uint32_t)q * TPP < m) consider(nb[q], pj[q], oj[q], mj[q]);
+        if (lane + (uint32_t)q * TPP < m) scan.consider(P, D, nb[q], pj[q], oj[q], mj[q]);
     for (uint32_t k = lane + (uint32_t)Q * TPP; k < m; k += TPP) {
         const uint32_t j = D.nl[k * n + i];
-        consider(j, X[j], D.occ[j], avoid ? D.mol[j] : 0u);
-    }
-#pragma unroll
-    for (int o = TPP / 2; o >= 1; o >>= 1) {
-        const double os = __shfl_xor(best_score, o, 64);
-        uint32_t ot = __shfl_xor(best_tag, o, 64);
-        const int oj2 = __shfl_xor(best_j, o, 64);
-        if (oj2 < 0) continue;
-        bool take = best_j < 0 || os < best_score;
-        if (!take && os == best_score) {            // tie across the group: compare tags
-            if (ot == kTagUnread) ot = D.tag[oj2];
-            if (best_tag == kTagUnread) best_tag = D.tag[best_j];
-            take = ot < best_tag;
-        }
-        if (take) {
-            best_score = os;
-            best_tag = ot;
-            best_j = oj2;
-        }
+        scan.consider(P, D, j, X[j], D.occ[j], avoid ? D.mol[j] : 0u);
     }
     tgi_out = tgi;
-    return best_j;
+    return scan.finish(D);
 }
 
 // Proposal phase fused with the first matching round: proposals and their

@@ -304,7 +304,7 @@ def _plan_list(p):
 
 def db_step_batch(handles, n_steps):
     """Advance several committed systems (handles) by n_steps each in one
-    graph of batched launches, under the device's stored plan; bitwise equal
+    chain of batched launches per size class, under the stored plan; bitwise equal
     to db_step on each."""
     hs = list(handles)
     arr = (ctypes.c_void_p * len(hs))(*hs)
