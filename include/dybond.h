@@ -245,13 +245,11 @@ DB_API db_status db_set_matching(db_system* sys, uint32_t grid_rounds, uint32_t 
 
 /* Launch shape of the step kernel and the proposal kernel of the sweep:
  * threads that share one particle (1, 2, 4, 8, 16 or 32, both kernels; 0 =
- * automatic: 8 in both below 32 768 particles, 4 in the step kernel and 2
- * in the proposal kernel up to 1.5 M particles, 1 and 2 from there on) and, with 4
- * threads per particle, how many neighbour-list entries each thread loads
- * before its first gather (1, 2 or 4; 0 = automatic: 1; the next three
- * entries per thread of a longer list are loaded with the first gathers,
- * where the list has them, and any beyond in further rounds).  Any shape
- * gives the same result bit for
+ * automatic: 8 in both below 32 768 particles; from there 2 in the proposal
+ * kernel, and in the step kernel 4 up to 130 000 particles, 2 up to 3 M and 1
+ * beyond) and, with 4 threads per particle, how many neighbour-list entries
+ * each thread loads up front (1, 2 or 4; 0 = automatic: 1; the rest of a
+ * longer list in further rounds).  Any shape gives the same result bit for
  * bit (forces are summed exactly); it changes only the speed.  May be
  * called before or after db_commit.  Errors: DB_EINVAL, DB_EDEVICE. */
 DB_API db_status db_set_step_shape(db_system* sys, uint32_t threads_per_particle, uint32_t list_batch);

@@ -151,7 +151,7 @@ __device__ __forceinline__ void nl_build_site(const Params& P, const StepTabs& T
     const float4* __restrict__ cp = D.cpos[lst];
     const int nc = (int)P.nc;
     const int cx = cell_coord(pi.x, P), cy = cell_coord(pi.y, P), cz = cell_coord(pi.z, P);
-    const float* rrow = T.rl2 + type_of(pi) * kMaxTypes;
+    const float* rrow = T.rl2 + pair_index(P, type_of(pi), 0u);
     const uint32_t cap = P.cellcap;
     uint32_t m = 0;
     auto consider = [&](float4 q) {
@@ -222,7 +222,7 @@ __device__ __forceinline__ void nl_build_site_lds(const Params& P, const StepTab
     uint32_t* __restrict__ nl = as_global(D.nl);
     const int nc = (int)P.nc;
     const int cx = cell_coord(pi.x, P), cy = cell_coord(pi.y, P), cz = cell_coord(pi.z, P);
-    const float* rrow = T.rl2 + type_of(pi) * kMaxTypes;
+    const float* rrow = T.rl2 + pair_index(P, type_of(pi), 0u);
     const uint32_t cap = P.cellcap;
     uint32_t m = 0;
     auto consider = [&](uint32_t j) {
@@ -304,7 +304,7 @@ void k_batch(const BatchItem* __restrict__ items, BatchState* __restrict__ state
     extern __shared__ float4 xs[];        // with LX: the positions of the current step
     const uint32_t tid = threadIdx.x, bs = blockDim.x;
     const uint32_t n = P.n;
-    stage_tabs(D, T, tid);
+    stage_tabs(P, D, T, tid, true);
     if (tid < 3) flag[tid] = more[tid] = 0u;
     if constexpr (LX) {
         if (B.resident) {                 // (the same for the whole workgroup)
@@ -481,7 +481,7 @@ void k_resident(const Params P, const Dev D, BatchState st, uint32_t nsteps, Bat
     __shared__ StepTabs T;
     __shared__ uint32_t flag[3], more[3];
     extern __shared__ float4 xs[];
-    stage_tabs(D, T, threadIdx.x);
+    stage_tabs(P, D, T, threadIdx.x, true);
     if (threadIdx.x < 3) flag[threadIdx.x] = more[threadIdx.x] = 0u;
     __syncthreads();
     resident_steps<EXT, TPP>(P, D, T, reinterpret_cast<unsigned char*>(xs), st, nsteps, flag, more, out);
@@ -508,7 +508,7 @@ void k_batch_sort(const BatchItem* __restrict__ items, const BatchState* __restr
     const uint32_t tid = threadIdx.x, bs = blockDim.x;
     const size_t n = P.n;
     __shared__ StepTabs T;
-    stage_tabs(D, T, tid);
+    stage_tabs(P, D, T, tid, true);
     // the current positions binned into cell list `lst`, the other two empty
     // (db_step keeps its cell lists in its own way)
     for (int l = 0; l < 3; ++l)

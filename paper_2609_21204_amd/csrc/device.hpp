@@ -212,9 +212,10 @@ struct Params {
     float invLf;                       // 1 / Lf, rounded once
     float c1;                          // exp(-gamma dt)
     uint32_t tpp;                      // threads per particle in k_propose (host side: launch shape)
-    uint32_t tpp_step;                 // threads per particle in k_step
-    uint32_t qb_step;                  // list entries per thread issued up front in k_step (0: by TPP)
+    uint32_t tpp_step;                 // threads per particle in the step kernel
+    uint32_t qb_step;                  // list entries per thread issued up front in k_stepq<4> (0: 1)
     uint32_t ext;                      // tether bonds or rate modifiers present: kernels in their full variant
+    uint32_t ext_force;                // tether bonds present: force kernels in their full variant
     float disp2;                       // (skin / 2 - 1e-4 - packing error of xref)^2: displacement that triggers a rebuild
     float xq, xqinv;                   // 2^21 / L and L / 2^21: the 21-bit grid of the packed build positions
     uint32_t nlmax;                    // neighbour-list slots per particle
@@ -259,9 +260,10 @@ struct PairTab {
 // at commit and staged in LDS by every workgroup: the force loop indexes them
 // with lane-varying types, which from the kernel-argument block would be one
 // more dependent memory round trip per neighbour.
+// Type pair (ti, tj) sits at pair_index of the arrays, so that the pairs in
+// use are the first ntypes^2 entries and only those are staged.
 struct alignas(16) StepTabs {
     float4 pf[kMaxTypes * kMaxTypes];   // what the FP32 pair force reads: rc2_pre, rc2_in, sig2f, eps24f of Params
-    float rl2[kMaxTypes * kMaxTypes];   // neighbour-list radius^2 of the type pair
     PairTab pair[kMaxTypes * kMaxTypes];
     double bk[kMaxBondTypes], br0[kMaxBondTypes], binvR02[kMaxBondTypes];
     double blmin[kMaxBondTypes], blc1[kMaxBondTypes], blc0[kMaxBondTypes], blmax[kMaxBondTypes];
@@ -269,6 +271,7 @@ struct alignas(16) StepTabs {
     uint32_t rbt[kMaxRx];
     float hm[kMaxTypes], noise_sd[kMaxTypes], mass[kMaxTypes];   // hm = (dt / 2) / m
     uint32_t cap[kMaxTypes];
+    float rl2[kMaxTypes * kMaxTypes];   // neighbour-list radius^2 of the type pair (list builds only)
 };
 static_assert(sizeof(StepTabs) % 16 == 0, "staged in 16-byte words");
 
@@ -325,6 +328,9 @@ struct Dev {
 };
 
 __device__ __forceinline__ uint32_t type_of(const float4& p) { return __float_as_uint(p.w); }
+__host__ __device__ __forceinline__ uint32_t pair_index(const Params& P, uint32_t ti, uint32_t tj) {
+    return (ti & 0xFFu) * (P.ntypes & 0xFFu) + tj;      // (8-bit factors: one 24-bit multiply-add)
+}
 
 // Cell-slot word: particle index in the low 24 bits, type in the high 8.
 __device__ __forceinline__ uint32_t slot_index(const float4& q) { return __float_as_uint(q.w) & kIdxMask; }

@@ -215,7 +215,8 @@ struct TimerScope {
 // reaches the launch), so the per-kernel times are kernel execution times.
 #define LAUNCH(sys, kern, grid, block, ...) LAUNCH_AS(sys, #kern, kern, grid, block, __VA_ARGS__)
 // kernels built in two variants: the full one for systems with tether bonds
-// or rate modifiers, the lean one otherwise
+// or rate modifiers (for the force kernels tether bonds alone: slip bonds and
+// melting change the sweep only), the lean one otherwise
 #define LAUNCH_EXT(sys, tname, kern, grid, block, ...)                                       \
     do {                                                                                     \
         if ((sys)->P.ext) LAUNCH_AS(sys, tname, (kern<true>), grid, block, __VA_ARGS__);     \
@@ -224,7 +225,7 @@ struct TimerScope {
 #define LAUNCH_EVAL(sys, mode, xin, off, out3)                                                     \
     do {                                                                                           \
         const unsigned ge_ = grid_of((sys)->n);                                                    \
-        if ((sys)->P.ext) LAUNCH_AS(sys, "k_eval", (k_eval<true, mode>), ge_, kBlock, (sys)->P, (sys)->D, xin, off, out3); \
+        if ((sys)->P.ext_force) LAUNCH_AS(sys, "k_eval", (k_eval<true, mode>), ge_, kBlock, (sys)->P, (sys)->D, xin, off, out3); \
         else LAUNCH_AS(sys, "k_eval", (k_eval<false, mode>), ge_, kBlock, (sys)->P, (sys)->D, xin, off, out3);             \
     } while (0)
 // the same, with the name the kernel is timed under given explicitly
@@ -523,11 +524,13 @@ double melt_mix_host(double p_init, double p_melt, double lam, double tm, double
 void fill_tabs(const db_system* s, StepTabs& th) {
     const Params& P = s->P;
     th = StepTabs{};
-    for (int k = 0; k < kMaxTypes * kMaxTypes; ++k) {
-        th.pf[k] = make_float4(P.rc2_pre[k], P.rc2_in[k], P.sig2f[k], P.eps24f[k]);
-        th.rl2[k] = P.rl2[k];
-        th.pair[k] = s->pair_h[k];
-    }
+    for (uint32_t a = 0; a < P.ntypes; ++a)
+        for (uint32_t b = 0; b < P.ntypes; ++b) {
+            const uint32_t k = a * kMaxTypes + b, w = pair_index(P, a, b);
+            th.pf[w] = make_float4(P.rc2_pre[k], P.rc2_in[k], P.sig2f[k], P.eps24f[k]);
+            th.rl2[w] = P.rl2[k];
+            th.pair[w] = s->pair_h[k];
+        }
     for (int k = 0; k < 8; ++k) {
         th.bk[k] = P.bk[k];
         th.br0[k] = P.br0[k];
@@ -561,20 +564,24 @@ void apply_temperature(db_system* s) {
 }
 
 // Automatic launch shapes (threads per particle) of the step kernel and of
-// the proposal kernel, measured on the gel and the sweep replicas (µs per
-// step, shapes given as step / proposal threads):
-//  - below 32 768 particles 8 / 8: 10 500 particles 13.4 against 14.1 at
-//    4 / 4 and 18.0 at 32 / 16 (the earlier rule of at least 2^19 threads
-//    per launch), 20 000 particles 17.8 against 18.7 and 26.2;
-//  - up to 1.5 M particles 4 / 2: 50 000 particles 21.7 against 22.0 at
-//    8 / 8, 200 000 particles 35.9 against 40.3;
-//  - from 1.5 M particles on 1 / 2: once the state no longer sits in the
-//    Infinity Cache, one thread per particle (k_step1, whose loads for a
-//    particle are all in flight together and which needs no LDS reduction)
-//    beats four: 2 M particles 3.7 % faster per step, 4 M 6.6 %, 16 M 7.9 %
-//    (equal at 1 M).
-constexpr uint32_t kStepEightThreadN = 32768u, kStepOneThreadN = 1500000u;
-uint32_t auto_step_tpp(uint32_t n) { return n >= kStepOneThreadN ? 1u : (n < kStepEightThreadN ? 8u : 4u); }
+// the proposal kernel (us per step of the gel unless said otherwise):
+//  - below 32 768 particles 8 / 8, one particle's work on its own threads
+//    (k_step): chains of 10 500 particles 11.9 against 12.7 for k_stepq<4>,
+//    monomers of 8000 11.4 against 12.4; 20 000 particles 16.8 against 17.4,
+//    32 768 20.8 against 20.1;
+//  - from there the work of a workgroup is dealt out evenly (k_stepq), with 4
+//    threads per particle for the loads up to 130 000 particles (40 000: 20.5
+//    against 22.0 with 2; 130 000: 27.1 either way) and 2 up to 3 M (160 000:
+//    29.7 against 31.2 with 4; 1 M: 95 against 105; 2 M: 152.8 against 162.7
+//    for k_step1);
+//  - from 3 M on one thread per particle (k_step1): bytes, not issue, bound
+//    the step there, and it has no queues to fill (3 M: equal; 4 M: 325.8
+//    against 330.5; 16 M: 1221 against 1261).
+// The proposal kernel takes 2 from 32 768 particles on.
+constexpr uint32_t kStepEightThreadN = 32768u, kStepFourThreadN = 130000u, kStepOneThreadN = 3000000u;
+uint32_t auto_step_tpp(uint32_t n) {
+    return n < kStepEightThreadN ? 8u : (n < kStepFourThreadN ? 4u : (n < kStepOneThreadN ? 2u : 1u));
+}
 uint32_t auto_propose_tpp(uint32_t n) { return n < kStepEightThreadN ? 8u : 2u; }
 
 void fill_params(db_system* s) {
@@ -632,7 +639,7 @@ void fill_params(db_system* s) {
         P.blc1[b] = s->bonds[b].lc1;
         P.blc0[b] = s->bonds[b].lc0;
         P.blmax[b] = s->bonds[b].lmax;
-        if (s->bonds[b].kind == DB_BOND_TETHER) P.ext = 1u;
+        if (s->bonds[b].kind == DB_BOND_TETHER) P.ext = P.ext_force = 1u;
     }
     for (size_t a = 0; a < s->rx.size(); ++a) {
         const auto& d = s->rx[a];
@@ -904,33 +911,25 @@ void launch_step(db_system* s) {
     const unsigned gs = (unsigned)(((uint64_t)P.n * P.tpp_step + kBlock - 1) / kBlock);
     const int f3 = (int)(t % 3);
 #define STEP_AS(...) LAUNCH_AS(s, "k_step", (__VA_ARGS__), gs, kBlock, P, s->D, xin, sp, f3, ake)
-    if (P.ext) {
-        switch (P.tpp_step) {
-            case 1: STEP_AS(k_step1<true>); break;
-            case 2: STEP_AS(k_step<2, 0, true>); break;
-            case 4:
-                if (P.qb_step == 2) STEP_AS(k_step<4, 2, true>);
-                else if (P.qb_step == 4) STEP_AS(k_step<4, 4, true>);
-                else STEP_AS(k_step<4, 0, true>);
-                break;
-            case 8: STEP_AS(k_step<8, 0, true>); break;
-            case 16: STEP_AS(k_step<16, 0, true>); break;
-            default: STEP_AS(k_step<32, 0, true>); break;
-        }
-    } else {
-        switch (P.tpp_step) {
-            case 1: STEP_AS(k_step1<false>); break;
-            case 2: STEP_AS(k_step<2, 0, false>); break;
-            case 4:
-                if (P.qb_step == 2) STEP_AS(k_step<4, 2, false>);
-                else if (P.qb_step == 4) STEP_AS(k_step<4, 4, false>);
-                else STEP_AS(k_step<4, 0, false>);
-                break;
-            case 8: STEP_AS(k_step<8, 0, false>); break;
-            case 16: STEP_AS(k_step<16, 0, false>); break;
-            default: STEP_AS(k_step<32, 0, false>); break;
-        }
+#define STEP_SHAPES(EXT)                                          \
+    switch (P.tpp_step) {                                         \
+        case 1: STEP_AS(k_step1<EXT>); break;                     \
+        case 2: STEP_AS(k_stepq<2, 3, EXT>); break;               \
+        case 4:                                                   \
+            if (P.qb_step == 2) STEP_AS(k_stepq<4, 2, EXT>);      \
+            else if (P.qb_step == 4) STEP_AS(k_stepq<4, 4, EXT>); \
+            else STEP_AS(k_stepq<4, 1, EXT>);                     \
+            break;                                                \
+        case 8: STEP_AS(k_step<8, EXT>); break;                   \
+        case 16: STEP_AS(k_step<16, EXT>); break;                 \
+        default: STEP_AS(k_step<32, EXT>); break;                 \
     }
+    if (P.ext_force) {
+        STEP_SHAPES(true)
+    } else {
+        STEP_SHAPES(false)
+    }
+#undef STEP_SHAPES
 #undef STEP_AS
     LAUNCH(s, k_binr, grid_of(P.n), kBlock, P, s->D, xin ^ 1, (int)((t + 1) % 3));
     LAUNCH(s, k_nlist, ntiles(P), kTileThreads, P, s->D, (int)((t + 1) % 3));
@@ -2485,12 +2484,13 @@ db_status db_read_observables(db_system* s, db_observables* out) {
     // and one wait (the sum kernel's answer lands in pinned memory)
     if (s->n <= kObsOneMaxN) {
         const size_t lds = s->n * sizeof(uint32_t);
-        if (P.ext)
+        if (P.ext_force)
             hipLaunchKernelGGL((k_observe_one<true>), dim3(1), dim3(kObsOneThreads), lds, s->stream, P, s->D, s->cur_x, s->obs_h);
         else
             hipLaunchKernelGGL((k_observe_one<false>), dim3(1), dim3(kObsOneThreads), lds, s->stream, P, s->D, s->cur_x, s->obs_h);
     } else {
-        LAUNCH_EXT(s, "k_observe", k_observe, g, kBlock, P, s->D, s->cur_x);
+        if (P.ext_force) LAUNCH_AS(s, "k_observe", (k_observe<true>), g, kBlock, P, s->D, s->cur_x);
+        else LAUNCH_AS(s, "k_observe", (k_observe<false>), g, kBlock, P, s->D, s->cur_x);
         LAUNCH(s, k_cc_union, g, kBlock, P, s->D, s->cur_x);
         LAUNCH(s, k_cc_size, g, kBlock, P, s->D);
         LAUNCH(s, k_observe_sum, 1, 1024, P, s->D, s->obs_h);

@@ -611,11 +611,20 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
 }
 
 // Copy the step tables (built on the host at commit, kept in device memory)
-// into LDS, 16 bytes per thread.
-__device__ __forceinline__ void stage_tabs(const Dev& D, StepTabs& T, uint32_t tid) {
+// into LDS, 16 bytes per thread: the type pairs in use, then the rest (with
+// the list radii where `lists`).  All 8 x 8 pairs were 6 KB a workgroup, 0.7
+// of them for the gel's 3 types.
+__device__ __forceinline__ void stage_tabs(const Params& P, const Dev& D, StepTabs& T, uint32_t tid, bool lists) {
     const uint4* __restrict__ src = reinterpret_cast<const uint4*>(D.tabs);
     uint4* dst = reinterpret_cast<uint4*>(&T);
-    for (uint32_t k = tid; k < sizeof(StepTabs) / 16; k += blockDim.x) dst[k] = src[k];
+    constexpr uint32_t kPair = offsetof(StepTabs, pair) / 16, kRest = offsetof(StepTabs, bk) / 16;
+    constexpr uint32_t kRadii = offsetof(StepTabs, rl2) / 16, kAll = sizeof(StepTabs) / 16;
+    const uint32_t a = P.ntypes * P.ntypes, b = a + a * (uint32_t)(sizeof(PairTab) / 16);
+    const uint32_t c = b + (lists ? kAll : kRadii) - kRest;
+    for (uint32_t k = tid; k < c; k += blockDim.x) {
+        const uint32_t w = k < a ? k : (k < b ? kPair + (k - a) : kRest + (k - b));
+        dst[w] = src[w];
+    }
 }
 
 // WCA force on pi from neighbour pj (type in the w bits), constants from LDS.
@@ -666,7 +675,7 @@ __device__ __forceinline__ float pair_r2_image(const Params& P, float4 pi, float
 __device__ __forceinline__ bool pair_force_f32(const Params& P, const StepTabs& T, uint32_t* err, float4 pi,
                                                float4 pj, uint32_t ti, bool valid, long long& fx, long long& fy,
                                                long long& fz) {
-    const float4 c = T.pf[(int)ti * kMaxTypes + (int)type_of(pj)];
+    const float4 c = T.pf[pair_index(P, ti, type_of(pj))];
     const float dx = pj.x - pi.x, dy = pj.y - pi.y, dz = pj.z - pi.z;
     const bool direct = pair_direct(P, dx, dy, dz);
     float r2 = pair_r2(dx, dy, dz);
@@ -680,7 +689,7 @@ __device__ __forceinline__ bool pair_force_f32(const Params& P, const StepTabs& 
 // inside the cutoff: which evaluation the pair needs, and the FP32 one.
 enum : uint32_t { kPairFar = 0u, kPairNear = 1u, kPairExact = 2u };
 __device__ __forceinline__ uint32_t pair_screen(const Params& P, const StepTabs& T, float4 pi, float4 pj, uint32_t ti) {
-    const float4* c = &T.pf[(int)ti * kMaxTypes + (int)type_of(pj)];
+    const float4* c = &T.pf[pair_index(P, ti, type_of(pj))];
     const float dx = pj.x - pi.x, dy = pj.y - pi.y, dz = pj.z - pi.z;
     const bool direct = pair_direct(P, dx, dy, dz);
     float r2 = pair_r2(dx, dy, dz);
@@ -690,14 +699,14 @@ __device__ __forceinline__ uint32_t pair_screen(const Params& P, const StepTabs&
 __device__ __forceinline__ void pair_force_near(const Params& P, const StepTabs& T, uint32_t* err, float4 pi, float4 pj,
                                                 uint32_t ti, long long& fx, long long& fy, long long& fz) {
     const float dx = pj.x - pi.x, dy = pj.y - pi.y, dz = pj.z - pi.z;
-    near_force(err, T.pf[(int)ti * kMaxTypes + (int)type_of(pj)], dx, dy, dz, pair_r2(dx, dy, dz), true, fx, fy, fz);
+    near_force(err, T.pf[pair_index(P, ti, type_of(pj))], dx, dy, dz, pair_r2(dx, dy, dz), true, fx, fy, fz);
 }
 
 __device__ __forceinline__ void pair_force_f64(const Params& P, const StepTabs& T, uint32_t* err, float4 pi,
                                                float4 pj, uint32_t ti, long long& fx, long long& fy,
                                                long long& fz, double* e = nullptr) {
 #pragma clang fp contract(off)
-    const PairTab& pp = T.pair[(int)ti * kMaxTypes + (int)type_of(pj)];
+    const PairTab& pp = T.pair[pair_index(P, ti, type_of(pj))];
     const double ex = mi_delta(pi.x, pj.x, P.L, P.invL);
     const double ey = mi_delta(pi.y, pj.y, P.L, P.invL);
     const double ez = mi_delta(pi.z, pj.z, P.L, P.invL);
@@ -726,8 +735,8 @@ __device__ __forceinline__ void pair_force_tab(const Params& P, const StepTabs& 
 // Bond force on site i from partner j (bond type bt), FP64 from the exact
 // minimum-image separation, constants from LDS; with `e`, half the bond's
 // energy is added there.
-// EXT: the system has tether bonds or rate modifiers (kernels are built in
-// two variants, so that systems without them keep the lean register budget).
+// EXT: the system has tether bonds (kernels are built in two variants, so that
+// systems without them keep the lean register budget).
 template <bool EXT>
 __device__ __forceinline__ void bond_force_tab(const Params& P, const StepTabs& T, const Dev& D, float4 pi,
                                                float4 pj, uint32_t bt, uint32_t i, uint32_t j,
@@ -804,7 +813,7 @@ __device__ __forceinline__ Force3 force_eval(const Params& P, const StepTabs& T,
             const float dx = mi_delta_f(pi.x, pj[q].x, P);
             const float dy = mi_delta_f(pi.y, pj[q].y, P);
             const float dz = mi_delta_f(pi.z, pj[q].z, P);
-            if (dx * dx + dy * dy + dz * dz < T.pf[(int)ti * kMaxTypes + (int)type_of(pj[q])].x)
+            if (dx * dx + dy * dy + dz * dz < T.pf[pair_index(P, ti, type_of(pj[q]))].x)
                 pair_force_f64(P, T, D.err, pi, pj[q], ti, fx, fy, fz, e);
         }
     }
@@ -832,7 +841,7 @@ template <bool EXT, int MODE>
 __global__ __launch_bounds__(256) void k_eval(const Params P, const Dev D, int xin, uint32_t off,
                                               float* __restrict__ out3) {
     __shared__ StepTabs T;
-    stage_tabs(D, T, threadIdx.x);
+    stage_tabs(P, D, T, threadIdx.x, false);
     __syncthreads();
     const uint32_t i = xcd_block() * blockDim.x + threadIdx.x;
     if (i >= P.n) return;
@@ -856,7 +865,9 @@ __global__ __launch_bounds__(256) void k_eval(const Params P, const Dev D, int x
     out3[3 * (size_t)tag + 2] = f.z;
 }
 
-// One BAOAB step t -> s = t + 1 over 256 / TPP particles per workgroup.
+// One BAOAB step t -> s = t + 1 over 256 / TPP particles per workgroup, for
+// systems too small to fill the chip, whose step is one particle's chain of
+// latencies (below 32 768 particles; k_stepq's queues cost it 0.4 to 0.6 us).
 //
 // Force phase: TPP threads share a particle; each takes every TPP-th entry
 // of the particle's neighbour list and every TPP-th bond slot (static slots,
@@ -875,7 +886,6 @@ __global__ __launch_bounds__(256) void k_eval(const Params P, const Dev D, int x
 // (which bin x_{t+1} and rebuild the lists only then).  The other waves have
 // retired by then, so no lane idles through the integration.
 //   xin = buffer of x_t, sp = t mod 2, f3 = t mod 3.
-//   QB (if not 0) = list entries per thread issued up front.
 // Thread 0 also retires the rebuild flag of step t (consumed by the k_nlist
 // of step t - 1), switching the cell list of the next build when it was set.
 __device__ __forceinline__ void retire_rebuild_flag(const Dev& D, int f3) {
@@ -885,15 +895,14 @@ __device__ __forceinline__ void retire_rebuild_flag(const Dev& D, int f3) {
     }
 }
 
-template <int TPP, int QB = 0, bool EXT = false>
+template <int TPP, bool EXT = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_step(const Params P, const Dev D, int xin, int sp,
                                               int f3, int accum_ke) {
-    static_assert(TPP >= 1 && TPP <= 64, "256 threads per workgroup");
+    static_assert(TPP >= 8 && TPP <= 32, "the first wave integrates the workgroup's particles");
     constexpr int PPB = 256 / TPP;                       // particles per workgroup
-    constexpr uint32_t kIntThreads = PPB > 64 ? PPB : 64;   // whole waves that integrate
-    constexpr int Q = QB ? QB : (4 / TPP > 1 ? 4 / TPP : 1);   // list entries per thread issued up front
-    constexpr int QX = 8 / TPP > 1 ? 8 / TPP : 1;              // further entries per thread, issued with the gathers
-    constexpr int BQ = 8 / TPP > 1 ? 8 / TPP : 1;       // bond slots per thread issued up front
+    constexpr uint32_t kIntThreads = 64;                 // the wave that integrates
+    constexpr int Q = 1, QX = 1, BQ = 1;                 // list entries and bond slots per thread issued up front,
+                                                         // and list entries issued with the gathers
     __shared__ StepTabs T;
     __shared__ unsigned long long fsum[3][PPB];
     const uint32_t tid = threadIdx.x;
@@ -926,7 +935,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
             else if (b < nslot) bw[q] = D.dyn[(b - P.stat_max) * n + i];
         }
     }
-    stage_tabs(D, T, tid);
+    stage_tabs(P, D, T, tid, false);
     if (tid < PPB) fsum[0][tid] = fsum[1][tid] = fsum[2][tid] = 0ull;
     const unsigned long long s = D.stepv[sp] + 1ull;
     if (gtid == 0) {
@@ -1010,12 +1019,218 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
     }
 }
 
+// The same step with its force work dealt out evenly, for systems that fill
+// the chip: 256 / TPP particles per workgroup, TPP threads per particle for
+// the loads (Q list entries and BQ bond words each), then every pair and every
+// bond of the workgroup is an entry of a queue in LDS, and the 256 threads
+// take the entries in turn.  A particle has 1.7 listed pairs and 2.2 bonds on
+// average in the bonded gel but up to 6 bonds and 8 and more pairs; with the
+// work of a particle on its own threads a wave ran every slot and entry that
+// any of its particles had, at 20 to 40 % of its lanes.  Pairs are queued
+// before bonds (a wave holds one kind but for one boundary), and the pairs
+// that need the FP64 evaluation, some 4 %, are queued again and evaluated
+// last, together: nearly every wave has one.  Sums go to the particle's LDS
+// words as 64-bit integers, so the dealing does not change them.  An entry for
+// which a queue has no room is evaluated by the thread that holds it.
+// Arguments as k_step.  Measured against k_step<4> before it (whole step):
+// 200 000 particles 37.2 -> 31.9 us, 1 M 113 -> 95 us, 50 000 23.0 -> 21.3 us.
+template <int TPP, int Q, bool EXT = false>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EXT ? 7 : 8))) void k_stepq(const Params P, const Dev D, int xin,
+                                                                                       int sp, int f3, int accum_ke) {
+    static_assert(TPP == 2 || TPP == 4, "whole waves integrate 256 / TPP particles");
+    constexpr uint32_t PPB = 256 / TPP;
+    constexpr int BQ = TPP == 2 ? 3 : 2;                 // bond words per thread loaded up front
+    constexpr uint32_t kPairs = 7 * PPB, kBonds = BQ * 256, kExact = 2 * PPB;  // queue lengths
+    __shared__ StepTabs T;
+    __shared__ unsigned long long fsum[3][PPB];
+    __shared__ float4 pos[PPB];
+    __shared__ uint32_t pq[kPairs], bq[kBonds];          // owner << 24 | partner index
+    __shared__ uint8_t bqt[kBonds];                      // bond type
+    __shared__ uint32_t queued[3];                       // pairs, bonds
+    __shared__ uint32_t xq[kExact];
+    const uint32_t tid = threadIdx.x;
+    const uint32_t base = xcd_block() * PPB;
+    const uint32_t own = tid / TPP, lane = tid % TPP, i = base + own;
+    const uint32_t gtid = blockIdx.x * blockDim.x + tid;
+    const size_t n = P.n;
+    const float4* __restrict__ X = D.x[xin];
+    const uint32_t nslot = P.stat_max + P.cap_max;
+    const bool live = i < P.n;
+    float4 pi = make_float4(0.f, 0.f, 0.f, 0.f);
+    uint32_t m = 0;
+    uint32_t nb[Q], bw[BQ];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) nb[q] = 0u;
+#pragma unroll
+    for (int q = 0; q < BQ; ++q) bw[q] = kEmpty;
+    auto slot_word = [&](uint32_t b) { return b < P.stat_max ? D.stat[b * n + i] : D.dyn[(b - P.stat_max) * n + i]; };
+    if (live) {
+        pi = X[i];
+        m = D.nl_cnt[i];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const uint32_t k = lane + (uint32_t)q * TPP;
+            if (k < P.nlmax) nb[q] = D.nl[k * n + i];
+        }
+#pragma unroll
+        for (int q = 0; q < BQ; ++q) {
+            const uint32_t b = lane + (uint32_t)q * TPP;
+            if (b < nslot) bw[q] = slot_word(b);
+        }
+    }
+    stage_tabs(P, D, T, tid, false);
+    if (tid < PPB) fsum[0][tid] = fsum[1][tid] = fsum[2][tid] = 0ull;
+    if (tid < 3) queued[tid] = 0u;
+    const unsigned long long s = D.stepv[sp] + 1ull;
+    if (gtid == 0) {
+        D.stepv[sp ^ 1] = s;
+        retire_rebuild_flag(D, f3);
+    }
+    if (lane == 0u) pos[own] = pi;
+    __syncthreads();
+    auto add = [&](uint32_t o, long long fx, long long fy, long long fz) {
+        atomicAdd(&fsum[0][o], (unsigned long long)fx);
+        atomicAdd(&fsum[1][o], (unsigned long long)fy);
+        atomicAdd(&fsum[2][o], (unsigned long long)fz);
+    };
+    auto do_pair = [&](uint32_t o, uint32_t jj, float4 pj) {
+        const float4 p = pos[o];
+        long long fx = 0, fy = 0, fz = 0;
+        if (pair_force_f32(P, T, D.err, p, pj, type_of(p), true, fx, fy, fz)) {
+            const uint32_t e = atomicAdd(&queued[2], 1u);
+            if (e < kExact) xq[e] = (o << 24) | jj;
+            else pair_force_f64(P, T, D.err, p, pj, type_of(p), fx, fy, fz);
+        }
+        add(o, fx, fy, fz);
+    };
+    auto do_bond = [&](uint32_t o, uint32_t j, uint32_t bt, float4 pj) {
+        long long fx = 0, fy = 0, fz = 0;
+        bond_force_tab<EXT>(P, T, D, pos[o], pj, bt, base + o, j, fx, fy, fz);
+        add(o, fx, fy, fz);
+    };
+    const unsigned long long below = (1ull << __lane_id()) - 1ull;
+    // the words in hand into the queues, two LDS atomics per wave
+    {
+        const uint32_t limit = live ? P.stat_max + T.cap[type_of(pi)] : 0u;
+        unsigned long long pm[Q], bm[BQ];
+        uint32_t np = 0, nbd = 0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            pm[q] = __ballot(lane + (uint32_t)q * TPP < m);
+            np += (uint32_t)__popcll(pm[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < BQ; ++q) {
+            bm[q] = __ballot(bw[q] != kEmpty && lane + (uint32_t)q * TPP < limit);
+            nbd += (uint32_t)__popcll(bm[q]);
+        }
+        uint32_t ap = 0, ab = 0;
+        if (__lane_id() == 0) {
+            ap = atomicAdd(&queued[0], np);
+            ab = atomicAdd(&queued[1], nbd);
+        }
+        ap = __builtin_amdgcn_readfirstlane(ap);
+        ab = __builtin_amdgcn_readfirstlane(ab);
+        uint32_t k1 = lane + (uint32_t)Q * TPP;            // this thread's first entry not yet queued
+#pragma unroll
+        for (int q = Q - 1; q >= 0; --q) {
+            uint32_t before = ap;
+#pragma unroll
+            for (int o = 0; o < q; ++o) before += (uint32_t)__popcll(pm[o]);
+            if (lane + (uint32_t)q * TPP < m) {
+                const uint32_t e = before + (uint32_t)__popcll(pm[q] & below);
+                if (e < kPairs) pq[e] = (own << 24) | nb[q];
+                else k1 = lane + (uint32_t)q * TPP;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < BQ; ++q) {
+            const uint32_t b = lane + (uint32_t)q * TPP;
+            if (bw[q] != kEmpty && b < limit) {
+                const uint32_t e = ab + (uint32_t)__popcll(bm[q] & below);
+                const uint32_t bt = b < P.stat_max ? bw[q] >> 24 : T.rbt[(bw[q] >> 24) & 0x7Fu];
+                bq[e] = (own << 24) | (bw[q] & kIdxMask);      // at most BQ per thread: they fit
+                bqt[e] = (uint8_t)bt;
+            }
+            ab += (uint32_t)__popcll(bm[q]);
+        }
+        // longer lists (a few particles per wave; an entry for which the queue
+        // has no room is evaluated here) and further bond slots
+        for (uint32_t k = k1; __any(k < m); k += TPP) {
+            const bool more = k < m;
+            const uint32_t j = more ? D.nl[k * n + i] : 0u;
+            const unsigned long long mask = __ballot(more);
+            uint32_t a0 = 0;
+            if (__lane_id() == 0) a0 = atomicAdd(&queued[0], (uint32_t)__popcll(mask));
+            a0 = __builtin_amdgcn_readfirstlane(a0);
+            if (more) {
+                const uint32_t e = a0 + (uint32_t)__popcll(mask & below);
+                if (e < kPairs) pq[e] = (own << 24) | j;
+                else do_pair(own, j, X[j]);
+            }
+        }
+        for (uint32_t b = lane + (uint32_t)BQ * TPP; b < limit; b += TPP) {
+            const uint32_t w = slot_word(b);
+            if (w != kEmpty)
+                do_bond(own, w & kIdxMask, b < P.stat_max ? w >> 24 : T.rbt[(w >> 24) & 0x7Fu], X[w & kIdxMask]);
+        }
+    }
+    __syncthreads();
+    // the integrating threads' state, on its way during the force work
+    const uint32_t i2 = base + tid;
+    const bool mine = tid < PPB && i2 < P.n;
+    float4 u2 = make_float4(0.f, 0.f, 0.f, 0.f);
+    uint2 r2 = make_uint2(0u, 0u);
+    if (mine) {
+        u2 = D.u[i2];
+        r2 = D.xref[i2];
+    }
+    {
+        const uint32_t np = min(queued[0], kPairs), total = np + queued[1];
+        auto item = [&](uint32_t e) { return e < np ? pq[e] : bq[e - np]; };
+        auto work = [&](uint32_t e, uint32_t w, float4 pj) {
+            if (e < np) do_pair(w >> 24, w & kIdxMask, pj);
+            else do_bond(w >> 24, w & kIdxMask, bqt[e - np], pj);
+        };
+        for (uint32_t e = tid; e < total; e += 512u) {
+            const bool two = e + 256u < total;
+            const uint32_t w0 = item(e), w1 = two ? item(e + 256u) : w0;
+            const float4 p0 = X[w0 & kIdxMask], p1 = X[w1 & kIdxMask];
+            work(e, w0, p0);
+            if (two) work(e + 256u, w1, p1);
+        }
+    }
+    __syncthreads();
+    for (uint32_t e = tid; e < min(queued[2], kExact); e += 256u) {
+        const uint32_t w = xq[e], o = w >> 24;
+        const float4 p = pos[o];
+        long long fx = 0, fy = 0, fz = 0;
+        pair_force_f64(P, T, D.err, p, X[w & kIdxMask], type_of(p), fx, fy, fz);
+        add(o, fx, fy, fz);
+    }
+    __syncthreads();
+    if (tid >= PPB) return;
+    unsigned long long ke = 0ull;
+    if (mine) {
+        const float4 p2 = pos[tid];
+        const Force3 F = fix_to_force(D, (long long)fsum[0][tid], (long long)fsum[1][tid], (long long)fsum[2][tid]);
+        float4 po;
+        ke = advance_particle(P, T, D, xin, i2, p2, type_of(p2), F, u2, __float_as_uint(u2.w), s, accum_ke, po);
+        if (moved_past_skin(P, r2, po)) D.rflag[f3 == 2 ? 0 : f3 + 1] = 1u;
+    }
+    if (accum_ke) {
+        for (int off = 32; off >= 1; off >>= 1) ke += __shfl_xor(ke, off, 64);
+        if (__lane_id() == 0 && ke) atomicAdd(&D.ke_fix[ke_slot(P, s)], ke);
+    }
+}
+
 // One BAOAB step t -> s = t + 1 with one thread per particle (the default
 // for large systems): the thread issues its particle's loads (position,
 // velocity, list position, tag, list length, the first 4 list entries and 2
 // bond words) together, then the 4 neighbour and 2 partner positions
-// together, takes further list entries 4 at a time the same way and further
-// bond slots one by one, and goes on to the integration with its force in
+// together, takes further list entries and bond slots 4 at a time the same
+// way (bond slots one by one, each a load and a gather in turn, took 345
+// instead of 326 us per step at 4 M), and goes on to the integration with its force in
 // registers (no LDS reduction, one barrier).  Same arguments and the same
 // result bit for bit as k_step<TPP>.  Compiled for 6 waves per SIMD (78
 // VGPRs, no spill): with 4 bond words up front it took 88 VGPRs and ran 5,
@@ -1055,7 +1270,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k
             else if (b < nslot) bw[q] = D.dyn[(b - P.stat_max) * n + i];
         }
     }
-    stage_tabs(D, T, tid);
+    stage_tabs(P, D, T, tid, false);
     const unsigned long long s = D.stepv[sp] + 1ull;
     if (gtid == 0) {
         D.stepv[sp ^ 1] = s;
@@ -1083,17 +1298,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k
             for (int q = 0; q < Q; ++q)
                 pair_force_tab(P, T, D.err, pi, pj[q], ti, k0 + (uint32_t)q < m, fx, fy, fz);
         }
+        const uint32_t limit = P.stat_max + T.cap[ti];     // slots beyond the valence stay empty
         auto bond = [&](uint32_t b, uint32_t w, float4 pw) {
             const uint32_t j = w & kIdxMask;
             const uint32_t bt = b < P.stat_max ? w >> 24 : T.rbt[(w >> 24) & 0x7Fu];
-            if (b < P.stat_max + T.cap[ti]) bond_force_tab<EXT>(P, T, D, pi, pw, bt, i, j, fx, fy, fz);
+            if (b < limit) bond_force_tab<EXT>(P, T, D, pi, pw, bt, i, j, fx, fy, fz);
         };
 #pragma unroll
         for (int q = 0; q < BQ; ++q)
             if (bw[q] != kEmpty) bond((uint32_t)q, bw[q], pb[q]);
-        for (uint32_t b = BQ; b < nslot; ++b) {
-            const uint32_t w = b < P.stat_max ? D.stat[b * n + i] : D.dyn[(b - P.stat_max) * n + i];
-            if (w != kEmpty) bond(b, w, X[w & kIdxMask]);
+        for (uint32_t b0 = BQ; b0 < limit; b0 += Q) {
+            uint32_t w[Q];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const uint32_t b = b0 + (uint32_t)q;
+                w[q] = b < limit ? (b < P.stat_max ? D.stat[b * n + i] : D.dyn[(b - P.stat_max) * n + i]) : kEmpty;
+            }
+#pragma unroll
+            for (int q = 0; q < Q; ++q) pj[q] = X[w[q] != kEmpty ? (w[q] & kIdxMask) : i];
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (w[q] != kEmpty) bond(b0 + (uint32_t)q, w[q], pj[q]);
         }
         const Force3 F = fix_to_force(D, fx, fy, fz);
         float4 po;
@@ -2021,7 +2246,7 @@ __global__ __launch_bounds__(1024) void k_observe_one(const Params P, const Dev 
     constexpr int M = __HIP_MEMORY_SCOPE_WORKGROUP;
     constexpr uint32_t kPer = kObsOneMaxN / kObsOneThreads;
     const uint32_t tid = threadIdx.x, n = P.n;
-    stage_tabs(D, T, tid);
+    stage_tabs(P, D, T, tid, false);
     if (tid < kMaxRx) nb[tid] = 0u;
     if (tid < 2) sum[tid] = 0ull;
     if (tid == 0) largest = 0u;
@@ -2069,7 +2294,7 @@ __global__ __launch_bounds__(256) void k_observe(const Params P, const Dev D, in
     __shared__ StepTabs T;
     __shared__ unsigned long long sum[2];
     __shared__ uint32_t nb[kMaxRx];
-    stage_tabs(D, T, threadIdx.x);
+    stage_tabs(P, D, T, threadIdx.x, false);
     if (threadIdx.x < kMaxRx) nb[threadIdx.x] = 0u;
     if (threadIdx.x < 2) sum[threadIdx.x] = 0ull;
     __syncthreads();

@@ -131,7 +131,7 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
         __syncthreads();
         uint32_t m = 0;
         if (live) {
-            const float* rrow = T.rl2 + ti * kMaxTypes;
+            const float* rrow = T.rl2 + pair_index(P, ti, 0u);
             uint16_t* const mine = lst + sub * n + i;
             for (uint32_t r = sub; r < 9u; r += TPP) {
                 const uint32_t rz = r / 3u, ry = r - 3u * rz;
@@ -355,7 +355,7 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
             if (before + q < P.nlmax) D.nl[(size_t)(before + q) * n + i] = L.at(q);
         if (own) D.nl_cnt[i] = min(L.m + m1, P.nlmax);
     } else if (own) {
-        const float* rrow = T.rl2 + ti * kMaxTypes;
+        const float* rrow = T.rl2 + pair_index(P, ti, 0u);
         const float4* const X = xs + (nsteps & 1u) * n;
         uint32_t m = 0;
         for (uint32_t j = 0; j < n; ++j) {
