@@ -2480,14 +2480,15 @@ db_status db_read_observables(db_system* s, db_observables* out) {
     HIPCHK(s, hipSetDevice(s->device));
     const unsigned g = grid_of(s->n);
     const Params& P = s->P;
-    // one workgroup does everything up to kObsOneMaxN particles: one launch
-    // and one wait (the sum kernel's answer lands in pinned memory)
+    // up to kObsOneMaxN particles one launch and one wait (the answer lands in
+    // pinned memory)
     if (s->n <= kObsOneMaxN) {
         const size_t lds = s->n * sizeof(uint32_t);
+        const unsigned gw = 1u + (s->n + kObsSites - 1u) / kObsSites;
         if (P.ext_force)
-            hipLaunchKernelGGL((k_observe_one<true>), dim3(1), dim3(kObsOneThreads), lds, s->stream, P, s->D, s->cur_x, s->obs_h);
+            hipLaunchKernelGGL((k_observe_one<true>), dim3(gw), dim3(kObsOneThreads), lds, s->stream, P, s->D, s->cur_x, s->obs_h);
         else
-            hipLaunchKernelGGL((k_observe_one<false>), dim3(1), dim3(kObsOneThreads), lds, s->stream, P, s->D, s->cur_x, s->obs_h);
+            hipLaunchKernelGGL((k_observe_one<false>), dim3(gw), dim3(kObsOneThreads), lds, s->stream, P, s->D, s->cur_x, s->obs_h);
     } else {
         if (P.ext_force) LAUNCH_AS(s, "k_observe", (k_observe<true>), g, kBlock, P, s->D, s->cur_x);
         else LAUNCH_AS(s, "k_observe", (k_observe<false>), g, kBlock, P, s->D, s->cur_x);

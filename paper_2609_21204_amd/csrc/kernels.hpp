@@ -2160,11 +2160,11 @@ __global__ __launch_bounds__(256) void k_cc_union(const Params P, const Dev D, i
 // workgroups do not queue on one address): PE and KE in 2^-32 fixed point,
 // the bonds of each reaction, the largest component.
 constexpr uint32_t kObsSlots = 64, kObsWords = 16;
-enum : int { kObsPe = 0, kObsKe = 1, kObsBonds = 2, kObsLargest = 2 + kMaxRx };
+enum : int { kObsPe = 0, kObsKe = 1, kObsBonds = 2, kObsLargest = 2 + kMaxRx, kObsDone = kObsLargest + 1 };
 // The answer in pinned host memory: the sums, the device error words, the
 // event counters (3 per reaction).
 constexpr uint32_t kObsErr = kObsWords, kObsCtr = kObsErr + 4, kObsOut = kObsCtr + 3 * kMaxRx;
-static_assert(kObsLargest < (int)kObsWords, "sums fit a slot");
+static_assert(kObsDone < (int)kObsWords, "sums fit a slot");
 
 // Component sizes at the roots (D.scan), the largest one into the sums.
 __global__ __launch_bounds__(256) void k_cc_size(const Params P, const Dev D) {
@@ -2214,11 +2214,12 @@ __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
     return v;
 }
 
-// The spread event counters summed into the answer (whole waves call this
-// together).
-__device__ __forceinline__ void observe_counters(const Params& P, const Dev& D, unsigned long long* out) {
+// The spread event counters summed into the answer (called by whole waves,
+// this one the `wave`th of `waves`).
+__device__ __forceinline__ void observe_counters(const Params& P, const Dev& D, uint32_t wave, uint32_t waves,
+                                                 unsigned long long* out) {
     const uint32_t lane = __lane_id();
-    for (uint32_t c = threadIdx.x >> 6; c < 3 * P.nrx; c += blockDim.x >> 6) {
+    for (uint32_t c = wave; c < 3 * P.nrx; c += waves) {
         unsigned long long v = 0;
 #pragma unroll
         for (uint32_t k = 0; k < kCtrSlots / 64; ++k) v += D.counters[(size_t)c * kCtrSlots + k * 64 + lane];
@@ -2227,63 +2228,87 @@ __device__ __forceinline__ void observe_counters(const Params& P, const Dev& D, 
     }
 }
 
-// Every observable of a small system in one workgroup, the answer written
+// Every observable of a small system in one launch, the answer written
 // straight to pinned host memory: a parameter sweep reads the observables of
-// every replica after each span, and launches, not work, are what that costs
-// (25 launches and 4 to 5 waits per system before, 310 us a call; one and one
-// now, 15 to 30 us of kernel at 256 to 4096 particles).  Components are built
-// in LDS (n parent words, dynamic).  Above kObsOneMaxN particles one CU is
-// slower than four launches over the chip (74 against about 40 us at 8000).
-constexpr uint32_t kObsOneMaxN = 4096;
-constexpr uint32_t kObsOneThreads = 1024;
+// every replica after each span, and launches, not work, are what that costs.
+// Workgroup 0 builds the components in LDS (n parent words, dynamic); the
+// others take kObsSites particles' energies and bonds each, one particle per
+// thread (their further waves sum the event counters, or end).  The last
+// workgroup to be done writes the sums.  Over 256 systems of 256 to 8192
+// particles a call's kernels take 16.8 us on average (27 us at the largest);
+// with everything in one workgroup, whose energies were the long part, and
+// four launches over the chip from 4097 particles on, they took 28 us (45 us
+// at 4096, 35 us in the four), and each launch more cost a call 5 us.
+// Above kObsOneMaxN particles the components of one CU are no faster.
+constexpr uint32_t kObsOneMaxN = 8192;
+constexpr uint32_t kObsOneThreads = 1024, kObsSites = 256;
 template <bool EXT>
 __global__ __launch_bounds__(1024) void k_observe_one(const Params P, const Dev D, int xin,
                                                       unsigned long long* __restrict__ out) {
     __shared__ StepTabs T;
     __shared__ unsigned long long sum[2];
-    __shared__ uint32_t nb[kMaxRx], largest;
+    __shared__ uint32_t nb[kMaxRx], largest, last;
     extern __shared__ uint32_t uf[];
     constexpr int M = __HIP_MEMORY_SCOPE_WORKGROUP;
     constexpr uint32_t kPer = kObsOneMaxN / kObsOneThreads;
     const uint32_t tid = threadIdx.x, n = P.n;
-    stage_tabs(P, D, T, tid, false);
-    if (tid < kMaxRx) nb[tid] = 0u;
-    if (tid < 2) sum[tid] = 0ull;
-    if (tid == 0) largest = 0u;
-    for (uint32_t i = tid; i < n; i += kObsOneThreads) uf[i] = i;
-    __syncthreads();
     const float4* __restrict__ X = D.x[xin];
-    unsigned long long pe = 0, ke = 0;
-    for (uint32_t i = tid; i < n; i += kObsOneThreads) {
-        observe_site<EXT>(P, T, D, X, i, pe, ke, nb);
-        uf_bonds<M>(P, D, uf, i, type_of(X[i]));
-    }
-    pe = wave_sum(pe);
-    ke = wave_sum(ke);
-    if (__lane_id() == 0) {
-        atomicAdd(&sum[0], pe);
-        atomicAdd(&sum[1], ke);
-    }
-    observe_counters(P, D, out);
-    __syncthreads();
-    uint32_t r[kPer];
+    if (blockIdx.x == 0) {
+        if (tid == 0) largest = 0u;
+        for (uint32_t i = tid; i < n; i += kObsOneThreads) uf[i] = i;
+        __syncthreads();
+        for (uint32_t i = tid; i < n; i += kObsOneThreads) uf_bonds<M>(P, D, uf, i, type_of(X[i]));
+        __syncthreads();
+        uint32_t r[kPer];
 #pragma unroll
-    for (uint32_t k = 0; k < kPer; ++k) {
-        const uint32_t i = tid + k * kObsOneThreads;
-        r[k] = i < n ? uf_root<M>(uf, i) : 0u;
-    }
-    __syncthreads();
-    for (uint32_t i = tid; i < n; i += kObsOneThreads) uf[i] = 0u;
-    __syncthreads();
-    uint32_t most = 0;
+        for (uint32_t k = 0; k < kPer; ++k) {
+            const uint32_t i = tid + k * kObsOneThreads;
+            r[k] = i < n ? uf_root<M>(uf, i) : 0u;
+        }
+        __syncthreads();
+        for (uint32_t i = tid; i < n; i += kObsOneThreads) uf[i] = 0u;
+        __syncthreads();
+        uint32_t most = 0;
 #pragma unroll
-    for (uint32_t k = 0; k < kPer; ++k)
-        if (k * kObsOneThreads < n) most = max(most, uf_count<M>(uf, r[k], tid + k * kObsOneThreads < n));
-    atomicMax(&largest, most);
+        for (uint32_t k = 0; k < kPer; ++k)
+            if (k * kObsOneThreads < n) most = max(most, uf_count<M>(uf, r[k], tid + k * kObsOneThreads < n));
+        atomicMax(&largest, most);
+        __syncthreads();
+        if (tid == 0) atomicMax(&D.red[kObsLargest], (unsigned long long)largest);
+    } else {
+        stage_tabs(P, D, T, tid, false);
+        if (tid < kMaxRx) nb[tid] = 0u;
+        if (tid < 2) sum[tid] = 0ull;
+        __syncthreads();
+        if (tid < kObsSites) {
+            const uint32_t i = (blockIdx.x - 1u) * kObsSites + tid;
+            unsigned long long pe = 0, ke = 0;
+            if (i < n) observe_site<EXT>(P, T, D, X, i, pe, ke, nb);
+            pe = wave_sum(pe);
+            ke = wave_sum(ke);
+            if (__lane_id() == 0) {
+                atomicAdd(&sum[0], pe);
+                atomicAdd(&sum[1], ke);
+            }
+        } else if (blockIdx.x == 1) {
+            observe_counters(P, D, (tid - kObsSites) / 64u, (kObsOneThreads - kObsSites) / 64u, out);
+        }
+        __syncthreads();
+        if (tid < 2) atomicAdd(&D.red[tid], sum[tid]);
+        else if (tid < 2 + P.nrx && nb[tid - 2]) atomicAdd(&D.red[tid], (unsigned long long)nb[tid - 2]);
+    }
+    // the sums are complete for the workgroup that arrives last; it leaves
+    // them cleared for the next call
+    static_assert(kObsBonds == 2, "the bond sums follow the two energies");
     __syncthreads();
-    if (tid < 2) out[tid] = sum[tid];
-    if (tid < kMaxRx) out[kObsBonds + tid] = nb[tid];
-    if (tid == 0) out[kObsLargest] = largest;
+    if (tid == 0)
+        last = __hip_atomic_fetch_add(&D.red[kObsDone], 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1u;
+    __syncthreads();
+    if (!last) return;
+    if (tid <= (uint32_t)kObsDone) {
+        const unsigned long long v = __hip_atomic_exchange(&D.red[tid], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid < (uint32_t)kObsDone) out[tid] = v;
+    }
     if (tid < 4) out[kObsErr + tid] = __hip_atomic_load(&D.err[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -2333,7 +2358,7 @@ __global__ __launch_bounds__(1024) void k_observe_sum(const Params P, const Dev 
         v = wave_sum(v);
     }
     if (lane == 0) out[w] = v;
-    observe_counters(P, D, out);
+    observe_counters(P, D, w, blockDim.x >> 6, out);
     if (threadIdx.x < 4) out[kObsErr + threadIdx.x] = D.err[threadIdx.x];
 }
 

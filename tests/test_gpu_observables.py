@@ -1,10 +1,11 @@
-"""Observables at the edges of the one-workgroup kernel (at most 4096
+"""Observables at the edges of the one-launch kernel (at most 8192
 particles) and of its 1024 threads, against values worked out from the
 read-outs: bond counts, bonded fraction, clusters and kinetic energy."""
 
 import numpy as np
 import pytest
 
+from helpers import oracle_from_workload
 from paper_2609_21204_amd import dybond as db
 from paper_2609_21204_amd import inputs
 
@@ -50,3 +51,24 @@ def test_observables_match_the_read_outs(n, kind):
     assert np.array_equal(hist, want) and clusters == sizes[1:].sum()
     for k in o:
         assert np.array_equal(o[k], again[k]), k
+
+
+@pytest.mark.parametrize("n", [64, 256, 257, 2049, 8192, 8193])
+def test_energies_match_the_oracle(n):
+    """Edges of the workgroups that share the energies (256 particles each) and
+    of the one-launch form (8192), twice over the same system: the sums of a
+    call are cleared for the next.  PE: FP32 terms of either sign, so relative
+    to the terms' own sum at most 2^-23 each, within 1e-5 as elsewhere."""
+    w = inputs.replica(7, n, 9.0, 0.3, 3, "mono")
+    with db.System.from_workload(w) as s:
+        o = oracle_from_workload(w)
+        for steps in (20, 80):
+            s.step(steps)
+            bonds = s.bonds()
+            o.set_state(s.step_count, s.positions(), s.velocities(), bonds[:, :2], bonds[:, 2])
+            g, r = s.observables(), o.observables()
+            assert np.array_equal(g["n_bonds"], r["n_bonds"])
+            assert g["largest_cluster_fraction"] == r["largest_cluster_fraction"]
+            assert abs(g["PE"] - r["PE"]) <= 1e-5 * abs(r["PE"])
+            assert abs(g["KE"] - r["KE"]) <= 1e-5 * abs(r["KE"])
+            assert g["forms"][0] - g["breaks"][0] == g["n_bonds"][0]
