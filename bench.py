@@ -226,7 +226,7 @@ def timed_steps(s, torch, k):
 
 def batch_vs_plain(a, db, inputs, torch):
     """Replicas/hour of the parameter-sweep batch run by db_step_batch (one
-    graph, one launch chain per size class) under the plan the autotuner
+    launch chain per size class) under the plan the autotuner
     picks on these replicas (its trials are ordinary steps of the run and
     are timed separately), against the same replicas run one after another
     with db_step.  The plain cost is measured on a sample spread over the
@@ -294,9 +294,7 @@ def batch_vs_plain(a, db, inputs, torch):
 def other_configs(db, inputs, torch, oracle=True):
     """The small and telechelic workloads on their own (absolute numbers
     only): small over its whole 1000-step run from the initial state (one
-    db_step call: for 512 particles its first 200 steps time the grid
-    kernels and a batch of one, 100 steps each, and the rest runs on the
-    faster), telechelic over 2000 steps after 500 (grid kernels,
+    db_step call, in one workgroup), telechelic over 2000 steps after 500 (grid kernels,
     launch-bound).  With `oracle`, the
     FP64 oracle (one thread) on the same starting state: the whole 1000
     small steps, and a 100-step window of telechelic."""
@@ -310,10 +308,9 @@ def other_configs(db, inputs, torch, oracle=True):
             dt = timed_steps(s, torch, steps)
             out[name] = {"n_particles": w.n, "steps": steps, "after_steps": equil,
                          "ms_per_step": 1000.0 * dt / steps, "particle_timesteps_per_s": w.n * steps / dt,
-                         # db_step runs long calls on a system of at most 768 particles
-                         # on whichever of a batch of one (one workgroup) and the grid
-                         # kernels its first long call measured faster
-                         "path": "measured: one workgroup or grid kernels" if w.n <= 768 else "grid kernels"}
+                         # db_step runs a system whose positions and lists one workgroup
+                         # can hold (up to 1024 particles) there for the whole call
+                         "path": "one workgroup" if name == "small" else "grid kernels"}
         if oracle:
             ob = cpu_baseline(w, state, osteps)
             out[name]["oracle_particle_timesteps_per_s"] = ob["value"]

@@ -3,7 +3,9 @@
 // Step structure (three launches per time step, plus the sweep every n
 // steps):
 //
-//   k_step      forces at x_t (neighbour list, WCA on every listed pair,
+//   k_step      (k_stepq and k_step1 on larger systems; systems that one
+//               workgroup can hold take whole runs in k_resident instead)
+//               forces at x_t (neighbour list, WCA on every listed pair,
 //               static and dynamic bonds), closing half kick of the previous
 //               step, then B-A-O-A of BAOAB, wrap, and the test whether some
 //               particle has moved more than half the skin since the last
