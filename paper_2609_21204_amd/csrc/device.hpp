@@ -463,6 +463,30 @@ __device__ __forceinline__ void ev_push(const Params& P, const Dev& D, int k, bo
     if (base + rank < P.evcap[k]) D.ev[k][base + rank] = make_uint2(lo, hi | ((uint32_t)a << 24));
 }
 
+// The same for a whole workgroup at once: at most one entry {lo, hi |
+// reaction << 24} per thread, one atomic per workgroup.  All threads call it.
+__device__ __forceinline__ void ev_push_group(const Params& P, const Dev& D, int k, bool want, uint2 e) {
+    __shared__ uint32_t wave[16], base;
+    const unsigned long long mask = __ballot(want);
+    const uint32_t w = threadIdx.x >> 6;
+    if (__lane_id() == 0) wave[w] = (uint32_t)__popcll(mask);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t total = 0;
+        for (uint32_t q = 0; q < blockDim.x / 64u; ++q) {
+            const uint32_t c = wave[q];
+            wave[q] = total;
+            total += c;
+        }
+        if (total) base = atomicAdd(&D.evc[k], total);
+    }
+    __syncthreads();
+    if (!want) return;
+    const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+    const uint32_t at = base + wave[w] + rank;
+    if (at < P.evcap[k]) D.ev[k][at] = e;
+}
+
 __device__ __forceinline__ void count_add(const Dev& D, int a, int kind, uint32_t v) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);

@@ -860,6 +860,8 @@ db_status check_errors(db_system* s) {
 void launch_sweep(db_system* s, int xcur, int sp) {
     const Params& P = s->P;
     const unsigned g = grid_of(P.n);
+    // one list atomic per workgroup: wide workgroups where there are thousands
+    const unsigned bc = P.n >= kClaimWideN ? kClaimWide : kBlock, gc = (P.n + bc - 1u) / bc;
     for (int slot = 0; slot < (int)P.nrx; ++slot) {
         const unsigned gp = grid_of(P.n);       // 256 sites per workgroup
         switch (P.tpp) {
@@ -870,11 +872,11 @@ void launch_sweep(db_system* s, int xcur, int sp) {
             case 16: LAUNCH(s, k_propose<16>, gp, kBlock, P, s->D, slot, xcur, sp); break;
             default: LAUNCH(s, k_propose<32>, gp, kBlock, P, s->D, slot, xcur, sp); break;
         }
-        LAUNCH_EXT(s, "k_claim", k_claim, g, kBlock, P, s->D, slot, 1, xcur, sp);
+        LAUNCH_EXT(s, "k_claim", k_claim, gc, bc, P, s->D, slot, 1, xcur, sp);
         const int R = (int)s->match_rounds;
         for (int q = 2; q <= R; ++q) {
             LAUNCH(s, k_kill, g, kBlock, P, s->D, q, 0);
-            LAUNCH_EXT(s, "k_claim", k_claim, g, kBlock, P, s->D, slot, q, xcur, sp);
+            LAUNCH_EXT(s, "k_claim", k_claim, gc, bc, P, s->D, slot, q, xcur, sp);
         }
         LAUNCH(s, k_kill, g, kBlock, P, s->D, R + 1, 1);
         LAUNCH_EXT(s, "k_finish", k_finish, 1, 1024, P, s->D, slot, (R + 1) % 3, xcur, sp, s->finish_lds);
