@@ -2136,7 +2136,12 @@ __device__ __forceinline__ void uf_bonds(const Params& P, const Dev& D, uint32_t
 
 // Count each lane's root r (lanes with `valid`) in size[].  Most particles of
 // a network belong to one component, whose counter would take one atomic per
-// particle: the two commonest-first roots of a wave are counted by one lane.
+// particle: one lane counts for all lanes of the wave's smallest root (roots
+// are smallest indices, and the largest component's is nearly always the
+// smallest), and one for those of the first root left.  (With the first lane's
+// root and the next one's instead, a wave whose first two particles lie in
+// other components counted its network particles one by one: k_cc_size took
+// 283 instead of 41 us in a 200 000-particle gel with 61 % in one component.)
 // Returns the largest count this lane has seen (the count after its own
 // addition: the last addition to a counter sees the component's size).
 template <int MEM>
@@ -2145,8 +2150,14 @@ __device__ __forceinline__ uint32_t uf_count(uint32_t* size, uint32_t r, bool va
     for (int k = 0; k < 2; ++k) {
         const unsigned long long todo = __ballot(valid);
         if (!todo) return most;
-        const int leader = __ffsll((long long)todo) - 1;
-        const bool same = valid && r == (uint32_t)__shfl((int)r, leader, 64);
+        uint32_t root = valid ? r : 0xFFFFFFFFu;
+        if (k == 0) {
+            for (int off = 32; off >= 1; off >>= 1) root = min(root, (uint32_t)__shfl_xor((int)root, off, 64));
+        } else {
+            root = (uint32_t)__shfl((int)r, __ffsll((long long)todo) - 1, 64);
+        }
+        const bool same = valid && r == root;
+        const int leader = __ffsll((long long)__ballot(same)) - 1;
         const uint32_t c = (uint32_t)__popcll(__ballot(same));
         if ((int)__lane_id() == leader) most = __hip_atomic_fetch_add(size + r, c, __ATOMIC_RELAXED, MEM) + c;
         valid = valid && !same;
