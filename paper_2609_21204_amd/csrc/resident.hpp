@@ -40,14 +40,21 @@ struct BatchState {
     uint32_t err[4];         // the system's device error words after the launch
 };
 
-// Neighbour entries of one thread: its list in LDS, or, when that overflowed,
-// every particle of the system.
+// Neighbour entries of one thread: the first KL in LDS, further ones in the
+// system's list in memory (slot-major rows of nlmax, not used otherwise
+// during a run): entry q >= KL in row q, or with two threads per particle,
+// for the second of them, in row top - (q - KL), so that the pair's entries
+// meet from both ends and fit together wherever their sum fits nlmax.
+template <int TPP>
 struct ResList {
-    const uint16_t* lst;     // entry q of this thread at lst[q * stride]
-    uint32_t stride, m, sub, tpp;
-    bool all;
-    __device__ __forceinline__ uint32_t count() const { return m; }
-    __device__ __forceinline__ uint32_t at(uint32_t q) const { return all ? q * tpp + sub : lst[q * stride]; }
+    static constexpr uint32_t KL = TPP == 2 ? kResList2 : kResList1;
+    uint16_t* lst;           // entry q < KL at lst[q * stride]
+    uint32_t* far;           // the particle's column of the list in memory
+    uint32_t stride, n, m, sub, top;
+    __device__ __forceinline__ uint32_t row(uint32_t q) const { return TPP == 2 && sub ? top - (q - KL) : q; }
+    __device__ __forceinline__ uint32_t near_at(uint32_t q) const { return lst[q * stride]; }
+    __device__ __forceinline__ uint32_t far_at(uint32_t q) const { return far[(size_t)row(q) * n]; }
+    __device__ __forceinline__ uint32_t at(uint32_t q) const { return q < KL ? near_at(q) : far_at(q); }
 };
 
 template <int TPP>
@@ -65,7 +72,7 @@ template <bool EXT, int TPP>
 __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, const StepTabs& T, unsigned char* lds,
                                                const BatchState& st, uint32_t nsteps, uint32_t* flag, uint32_t* more,
                                                BatchState* out) {
-    constexpr uint32_t KL = TPP == 2 ? kResList2 : kResList1;
+    constexpr uint32_t KL = ResList<TPP>::KL;
     constexpr int BW = 4;                          // bond words held in registers per thread
     const uint32_t tid = threadIdx.x, bs = blockDim.x, n = P.n;
     const uint32_t i = tid / TPP, sub = tid % TPP;
@@ -99,7 +106,8 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
         }
     };
     load_bonds();
-    ResList L{lst + sub * n + (live ? i : 0u), TPP * n, 0u, sub, TPP, false};
+    const uint32_t at = live ? i : 0u;
+    ResList<TPP> L{lst + sub * n + at, D.nl + at, TPP * n, n, 0u, sub, P.nlmax - 1u};
 
     // Lists at the positions X (p: this thread's own): a counting sort of the
     // particles by cell, then each thread scans the 9 (5 and 4 with two
@@ -132,7 +140,6 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
         uint32_t m = 0;
         if (live) {
             const float* rrow = T.rl2 + pair_index(P, ti, 0u);
-            uint16_t* const mine = lst + sub * n + i;
             for (uint32_t r = sub; r < 9u; r += TPP) {
                 const uint32_t rz = r / 3u, ry = r - 3u * rz;
                 const int row = (wrapc(cz + (int)rz - 1, nc) * nc + wrapc(cy + (int)ry - 1, nc)) * nc;
@@ -157,7 +164,8 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
                         const float dx = mi_delta_list(p.x, q[e].x, P), dy = mi_delta_list(p.y, q[e].y, P),
                                     dz = mi_delta_list(p.z, q[e].z, P);
                         if (k0 + e < len && j[e] != i && dx * dx + dy * dy + dz * dz < rrow[type_of(q[e])]) {
-                            if (m < KL) mine[m * TPP * n] = (uint16_t)j[e];
+                            if (m < KL) L.lst[m * L.stride] = (uint16_t)j[e];
+                            else if (L.row(m) < P.nlmax) L.far[(size_t)L.row(m) * n] = j[e];
                             ++m;
                         }
                     }
@@ -166,8 +174,7 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
         }
         const uint32_t both = TPP == 2 ? m + (uint32_t)__shfl_xor((int)m, 1, 64) : m;
         if (own && both > P.nlmax) atomicOr(&D.err[0], kErrNlist);
-        L.all = m > KL;
-        L.m = L.all ? (n - sub + TPP - 1u) / TPP : m;
+        L.m = min(m, max(KL, P.nlmax));            // (beyond it only after that error)
         ref = p;
     };
 
@@ -186,21 +193,24 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
         if (live) {
             // pairs: screen the thread's entries 2 at a time, then evaluate
             // those inside the cutoff, FP32 ones first, so that a wave runs
-            // as many evaluations as its busiest lane needs
-            for (uint32_t q0 = 0; q0 < L.m; q0 += 32u) {
+            // as many evaluations as its busiest lane needs; KL entries per
+            // round, the first round from LDS, further ones from memory (the
+            // same choice for every lane of a round)
+            for (uint32_t q0 = 0; q0 < L.m; q0 += KL) {
+                auto entry = [&](uint32_t q) { return q0 == 0u ? L.near_at(q) : L.far_at(q0 + q); };
                 uint32_t near = 0u, exact = 0u;
-                const uint32_t lim = min(L.m - q0, 32u);
+                const uint32_t lim = min(L.m - q0, KL);
                 for (uint32_t q1 = 0; q1 < lim; q1 += 2) {
                     uint32_t j[2];
                     float4 pj[2];
 #pragma unroll
-                    for (uint32_t e = 0; e < 2; ++e) j[e] = L.at(q0 + min(q1 + e, lim - 1u));
+                    for (uint32_t e = 0; e < 2; ++e) j[e] = entry(min(q1 + e, lim - 1u));
 #pragma unroll
                     for (uint32_t e = 0; e < 2; ++e) pj[e] = X[j[e]];
 #pragma unroll
                     for (uint32_t e = 0; e < 2; ++e) {
                         const uint32_t w = pair_screen(P, T, p, pj[e], ti);
-                        const uint32_t bit = q1 + e < lim && j[e] != i ? 1u << (q1 + e) : 0u;
+                        const uint32_t bit = q1 + e < lim ? 1u << (q1 + e) : 0u;
                         near |= w == kPairNear ? bit : 0u;
                         exact |= w == kPairExact ? bit : 0u;
                     }
@@ -208,12 +218,12 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
                 while (near) {
                     const uint32_t q = (uint32_t)__builtin_ctz(near);
                     near &= near - 1u;
-                    pair_force_near(P, T, D.err, p, X[L.at(q0 + q)], ti, fx, fy, fz);
+                    pair_force_near(P, T, D.err, p, X[entry(q)], ti, fx, fy, fz);
                 }
                 while (exact) {
                     const uint32_t q = (uint32_t)__builtin_ctz(exact);
                     exact &= exact - 1u;
-                    pair_force_f64(P, T, D.err, p, X[L.at(q0 + q)], ti, fx, fy, fz);
+                    pair_force_f64(P, T, D.err, p, X[entry(q)], ti, fx, fy, fz);
                 }
             }
             auto bond = [&](uint32_t b, uint32_t w) {
@@ -282,9 +292,9 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
             if (live && (ti == P.ra[a] || ti == P.rb[a]) && occs[i] < T.cap[ti]) {
                 ProposeScan<TPP> scan;
                 scan.begin(P, D, a, i, p, ti);
-                for (uint32_t q = 0; q < L.count(); ++q) {
+                for (uint32_t q = 0; q < L.m; ++q) {
                     const uint32_t c = L.at(q);
-                    if (c != i) scan.consider(P, D, c, Xn[c], occs[c], scan.avoid ? D.mol[c] : 0u);
+                    scan.consider(P, D, c, Xn[c], occs[c], scan.avoid ? D.mol[c] : 0u);
                 }
                 j = scan.finish(D);
             }
@@ -334,39 +344,25 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
     // hand the state back in the form db_step leaves it: positions, velocities,
     // lists, step slots, no list rebuild pending
     const int xin = xin0 ^ (int)(nsteps & 1u);
-    // A list that overflowed its LDS slots is written from scratch, at fresh
-    // build positions for every particle.
-    if (tid == 0) more[0] = 0u;
-    __syncthreads();
-    if (live && L.all) more[0] = 1u;
-    __syncthreads();
-    const bool some_long = more[0] != 0u;
-    if (some_long) build(xs + (nsteps & 1u) * n);
     if (own) {
         D.x[xin][i] = p;
         D.u[i] = u;
         D.xref[i] = xref_pack(P, ref);
     }
-    const uint32_t m1 = TPP == 2 ? (uint32_t)__shfl_xor((int)L.m, 1, 64) : 0u;
-    const bool either = L.all || (TPP == 2 && __shfl_xor(L.all ? 1 : 0, 1, 64) != 0);
-    if (live && !either) {
-        const uint32_t before = sub ? m1 : 0u;     // the pair's lists one after the other
-        for (uint32_t q = 0; q < L.m; ++q)
-            if (before + q < P.nlmax) D.nl[(size_t)(before + q) * n + i] = L.at(q);
-        if (own) D.nl_cnt[i] = min(L.m + m1, P.nlmax);
-    } else if (own) {
-        const float* rrow = T.rl2 + pair_index(P, ti, 0u);
-        const float4* const X = xs + (nsteps & 1u) * n;
-        uint32_t m = 0;
-        for (uint32_t j = 0; j < n; ++j) {
-            const float dx = mi_delta_list(p.x, X[j].x, P), dy = mi_delta_list(p.y, X[j].y, P),
-                        dz = mi_delta_list(p.z, X[j].z, P);
-            if (j != i && dx * dx + dy * dy + dz * dz < rrow[type_of(X[j])]) {
-                if (m < P.nlmax) D.nl[(size_t)m * n + i] = j;
-                ++m;
+    // the pair's lists one after the other in D.nl: rows from KL on are the
+    // first thread's already, the second's further entries move down from the
+    // end (to rows no higher than their own, lowest first)
+    const uint32_t m_other = TPP == 2 ? (uint32_t)__shfl_xor((int)L.m, 1, 64) : 0u;
+    if (live) {
+        const uint32_t r0 = sub ? m_other : 0u;
+        for (uint32_t q = 0; q < min(L.m, KL); ++q)
+            if (r0 + q < P.nlmax) L.far[(size_t)(r0 + q) * n] = L.near_at(q);
+        if (TPP == 2 && sub && L.m > KL)
+            for (uint32_t e = L.m - KL; e-- > 0u;) {
+                const uint32_t r = r0 + L.m - 1u - e;
+                if (r < P.nlmax) L.far[(size_t)r * n] = L.far_at(KL + e);
             }
-        }
-        D.nl_cnt[i] = min(m, P.nlmax);
+        if (own) D.nl_cnt[i] = min(L.m + m_other, P.nlmax);
     }
     __syncthreads();
     if (tid == 0) {
