@@ -5,7 +5,9 @@
 // velocity, build position and bond words in registers for the whole launch.
 // Positions of all particles live in LDS in two buffers (read one, write the
 // other: one barrier per step), neighbour lists, cell lists and the matching's
-// keys in LDS as well.  A step then touches global memory only for image
+// keys in LDS as well.  A launch takes the lists as they were last built, and
+// builds where the grid kernels would: the same builds are counted, and the
+// same lists and cells checked against their limits.  A step then touches global memory only for image
 // counters (a particle that crosses the box) and in the sweeps, for the bond
 // slots.  What bounds a step here is the latency of one particle's chain of
 // work and, with 16 waves on a CU, the issue of its instructions.
@@ -90,10 +92,14 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
     const unsigned long long t0 = st.t;
     const int xin0 = st.cur_x;
 
-    float4 p = make_float4(0.f, 0.f, 0.f, 0.f), u = p, ref = p;
+    float4 p = make_float4(0.f, 0.f, 0.f, 0.f), u = p;
+    uint2 ref = make_uint2(0u, 0u);                // packed build position
+    uint32_t listed = 0;
     if (live) {
         p = D.x[xin0][i];
         u = D.u[i];
+        ref = D.xref[i];
+        listed = D.nl_cnt[i];
     }
     const uint32_t ti = type_of(p), tag = __float_as_uint(u.w);
     const uint32_t nstat = P.stat_max, nslot = live ? nstat + T.cap[ti] : 0u;
@@ -107,7 +113,22 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
     };
     load_bonds();
     const uint32_t at = live ? i : 0u;
-    ResList<TPP> L{lst + sub * n + at, D.nl + at, TPP * n, n, 0u, sub, P.nlmax - 1u};
+    // the lists as they were last built: the second thread of a pair takes the
+    // last half, from the end
+    ResList<TPP> L{lst + sub * n + at, D.nl + at, TPP * n, n, TPP == 2 ? (listed + 1u - sub) / 2u : listed, sub,
+                   listed - 1u - KL};
+    for (uint32_t q0 = 0, lim = min(L.m, KL); q0 < lim; q0 += 4) {
+        uint32_t j[4];
+#pragma unroll
+        for (uint32_t e = 0; e < 4; ++e) {
+            const uint32_t q = min(q0 + e, lim - 1u);
+            j[e] = L.far[(size_t)(sub ? listed - 1u - q : q) * n];
+        }
+#pragma unroll
+        for (uint32_t e = 0; e < 4; ++e)
+            if (q0 + e < lim) L.lst[(q0 + e) * L.stride] = (uint16_t)j[e];
+    }
+    bool built = false;                            // since the launch began (the same for the whole workgroup)
 
     // Lists at the positions X (p: this thread's own): a counting sort of the
     // particles by cell, then each thread scans the 9 (5 and 4 with two
@@ -138,6 +159,7 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
         if (own) order[cst[c] + slot] = (uint16_t)i;
         __syncthreads();
         uint32_t m = 0;
+        L.top = P.nlmax - 1u;
         if (live) {
             const float* rrow = T.rl2 + pair_index(P, ti, 0u);
             for (uint32_t r = sub; r < 9u; r += TPP) {
@@ -175,12 +197,12 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
         const uint32_t both = TPP == 2 ? m + (uint32_t)__shfl_xor((int)m, 1, 64) : m;
         if (own && both > P.nlmax) atomicOr(&D.err[0], kErrNlist);
         L.m = min(m, max(KL, P.nlmax));            // (beyond it only after that error)
-        ref = p;
+        ref = xref_pack(P, p);
+        built = true;
     };
 
     if (own) xs[i] = p;
     __syncthreads();
-    build(xs);
     for (uint32_t k = 0; k < nsteps; ++k) {
         const unsigned long long s = t0 + k + 1ull;
         const bool sweep = P.nrx > 0 && (s % P.period) == 0;
@@ -254,9 +276,7 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
                     D.img[n + i] += iy;
                     D.img[2 * (size_t)n + i] += iz;
                 }
-                const float dx = mi_delta_list(ref.x, p.x, P), dy = mi_delta_list(ref.y, p.y, P),
-                            dz = mi_delta_list(ref.z, p.z, P);
-                if (dx * dx + dy * dy + dz * dz > P.disp2) flag[k % 3] = 1u;
+                if (moved_past_skin(P, ref, p)) flag[k % 3] = 1u;
             }
         }
         if (ake) {
@@ -267,7 +287,7 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
         }
         __syncthreads();
         if (flag[k % 3]) {
-            if (tid == 0) ++D.rflag[4];            // builds so far, as db_step counts them
+            if (tid == 0) ++D.rflag[4];            // builds so far, on the grid kernels' schedule
             build(Xn);
             __syncthreads();
         }
@@ -347,13 +367,13 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
     if (own) {
         D.x[xin][i] = p;
         D.u[i] = u;
-        D.xref[i] = xref_pack(P, ref);
     }
-    // the pair's lists one after the other in D.nl: rows from KL on are the
-    // first thread's already, the second's further entries move down from the
-    // end (to rows no higher than their own, lowest first)
+    // lists built during the launch: the pair's one after the other in D.nl.
+    // Rows from KL on are the first thread's already, the second's further
+    // entries move down from the end (to rows no higher than their own, lowest
+    // first).
     const uint32_t m_other = TPP == 2 ? (uint32_t)__shfl_xor((int)L.m, 1, 64) : 0u;
-    if (live) {
+    if (live && built) {
         const uint32_t r0 = sub ? m_other : 0u;
         for (uint32_t q = 0; q < min(L.m, KL); ++q)
             if (r0 + q < P.nlmax) L.far[(size_t)(r0 + q) * n] = L.near_at(q);
@@ -362,7 +382,10 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
                 const uint32_t r = r0 + L.m - 1u - e;
                 if (r < P.nlmax) L.far[(size_t)r * n] = L.far_at(KL + e);
             }
-        if (own) D.nl_cnt[i] = min(L.m + m_other, P.nlmax);
+        if (own) {
+            D.nl_cnt[i] = min(L.m + m_other, P.nlmax);
+            D.xref[i] = ref;
+        }
     }
     __syncthreads();
     if (tid == 0) {

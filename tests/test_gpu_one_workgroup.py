@@ -46,3 +46,38 @@ def test_lists_that_overflow_on_one_thread_of_a_pair(n, skin):
     differ, and one of them outgrows its 16 LDS slots where the other does
     not (with one thread per particle: 24 slots, some lists longer)."""
     compare(block(n, 0.05, 1.05, kT=0.2), (1, 9, 25), f"skin {skin}", skin=skin)
+
+
+@pytest.mark.parametrize("n, rho", [(300, 0.3), (384, 0.05), (600, 0.3)])
+def test_short_calls_build_lists_when_the_grid_kernels_do(n, rho):
+    """Both forms build after the same steps and count every build (the one
+    of the grid kernels' renumbering at step 0 is before the first count)."""
+    w = inputs.replica(9, n, 5.0, rho, 2, "mono")
+    with db.System.from_workload(w) as a, grid_of(w) as g:
+        a.step(10)
+        g.step(10)
+        a0, g0 = db.db_read_list_builds(a.h), db.db_read_list_builds(g.h)
+        for _ in range(40):
+            a.step(5)
+            g.step(5)
+        assert db.db_read_list_builds(g.h) > g0 + 2
+        assert db.db_read_list_builds(a.h) - a0 == db.db_read_list_builds(g.h) - g0
+        assert_same(a, g, f"n={n}")
+
+
+def test_a_call_between_two_builds_meets_no_list_limit():
+    """A particle drifts into the list radius of one that already has
+    max_neighbors entries, by less than half the skin: no list is built, so
+    no call may report that the list is full."""
+    w = inputs.Workload(
+        name="three", n=3, L=9.0, types=[(0, 1.0, 1.0, 1.0)],
+        pos=np.array([[0, 0, 0], [1.2, 0, 0], [-1.44, 0, 0]], np.float32),
+        vel=np.array([[0, 0, 0], [0, 0, 0], [1, 0, 0]], np.float32), type_id=np.zeros(3, np.uint32),
+        bond_types=[], static_pairs=np.zeros((0, 2), np.uint32), static_types=np.zeros(0, np.uint32),
+        reactions=[], kT=1e-9)
+    with db.System.from_workload(w, max_neighbors=1) as a, grid_of(w, max_neighbors=1) as g:
+        for _ in range(20):
+            a.step(1)
+            g.step(1)
+        assert np.array_equal(a.positions(), g.positions())
+        assert -1.42 < a.positions()[2, 0] < -1.3
