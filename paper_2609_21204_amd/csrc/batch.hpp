@@ -391,6 +391,9 @@ void k_batch(const BatchItem* __restrict__ items, BatchState* __restrict__ state
             }
             if (tid < 3) more[tid] = 0u;
             if (slot == 0 && tid == 0) {      // a new sweep: its event lists start empty
+                // and the next sweep's energy slot, with barriers between this
+                // and the adds of the next step (a sweep may follow every step)
+                D.ke_fix[ke_slot(P, s) ^ 1u] = 0ull;
                 D.evc[0] = 0u;
                 D.evc[1] = 0u;
                 D.evc[2] = (uint32_t)s;
@@ -450,7 +453,6 @@ void k_batch(const BatchItem* __restrict__ items, BatchState* __restrict__ state
             count_add(D, a, kCtrBreak, broke);
             __syncthreads();
         }
-        if (tid == 0) D.ke_fix[ke_slot(P, s) ^ 1u] = 0ull;   // the next sweep's slot, as db_step leaves it
     }
     // hand the state back in the form db_step leaves it: step slots, no list
     // rebuild pending, the cell list of db_step's next build empty, round-1

@@ -302,6 +302,9 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
             }
             if (tid < 3) more[tid] = 0u;
             if (slot == 0 && tid == 0) {           // a new sweep: its event lists start empty
+                // and the next sweep's energy slot, with barriers between this
+                // and the adds of the next step (a sweep may follow every step)
+                D.ke_fix[ke_slot(P, s) ^ 1u] = 0ull;
                 D.evc[0] = 0u;
                 D.evc[1] = 0u;
                 D.evc[2] = (uint32_t)s;
@@ -359,7 +362,6 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
             __syncthreads();
         }
         load_bonds();
-        if (tid == 0) D.ke_fix[ke_slot(P, s) ^ 1u] = 0ull;   // the next sweep's slot, as db_step leaves it
     }
     // hand the state back in the form db_step leaves it: positions, velocities,
     // lists, step slots, no list rebuild pending

@@ -81,3 +81,13 @@ def test_a_call_between_two_builds_meets_no_list_limit():
             g.step(1)
         assert np.array_equal(a.positions(), g.positions())
         assert -1.42 < a.positions()[2, 0] < -1.3
+
+
+@pytest.mark.parametrize("n", [300, 700, 1500])
+def test_a_sweep_after_every_step_at_the_kinetic_temperature(n):
+    """The energy word of the next sweep is cleared while no step adds to it
+    (1500 particles: the batch kernel's own loop)."""
+    w = inputs.replica(11, n, 3.0, 0.2, 2, "mono")
+    w.period = 1
+    o = compare(w, (1, 2, 40, 61), "period 1", kt_source=db.DB_KT_KINETIC)
+    assert o["forms"].sum() > 0 and o["breaks"].sum() > 0
