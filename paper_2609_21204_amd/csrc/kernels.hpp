@@ -2323,8 +2323,11 @@ __global__ __launch_bounds__(1024) void k_observe_one(const Params P, const Dev 
         else if (tid < 2 + P.nrx && nb[tid - 2]) atomicAdd(&D.red[tid], (unsigned long long)nb[tid - 2]);
     }
     // the sums are complete for the workgroup that arrives last; it leaves
-    // them cleared for the next call
+    // them cleared for the next call.  The arrival of thread 0 waits for its
+    // own wave's memory operations alone: the waves that may have raised an
+    // error (observe_site) wait for theirs here.
     static_assert(kObsBonds == 2, "the bond sums follow the two energies");
+    if (blockIdx.x != 0 && tid < kObsSites) __threadfence();
     __syncthreads();
     if (tid == 0)
         last = __hip_atomic_fetch_add(&D.red[kObsDone], 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1u;

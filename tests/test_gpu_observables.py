@@ -72,3 +72,26 @@ def test_energies_match_the_oracle(n):
             assert abs(g["PE"] - r["PE"]) <= 1e-5 * abs(r["PE"])
             assert abs(g["KE"] - r["KE"]) <= 1e-5 * abs(r["KE"])
             assert g["forms"][0] - g["breaks"][0] == g["n_bonds"][0]
+
+
+@pytest.mark.parametrize("n, pair", [(600, 3), (600, 250), (600, 590), (5000, 4321)])
+def test_an_error_met_by_the_evaluation_is_reported_by_the_call(n, pair):
+    """A bond that the last step has stretched past its range is first
+    evaluated by the read-out: whichever wave meets it, this call reports it."""
+    m = int(np.ceil(n ** (1.0 / 3.0)))
+    g = np.stack(np.meshgrid(*[np.arange(m)] * 3, indexing="ij"), -1).reshape(-1, 3)[:n]
+    w = inputs.Workload(
+        name="stretched", n=n, L=1.2 * m, types=[(0, 1.0, 1.0, 1.0)],
+        pos=((g - 0.5 * (m - 1)) * 1.2).astype(np.float32), vel=np.zeros((n, 3), np.float32),
+        type_id=np.zeros(n, np.uint32), bond_types=[(inputs.FENE, 30.0, 1.5)],
+        static_pairs=np.array([[pair, pair + 1]], np.uint32), static_types=np.zeros(1, np.uint32), reactions=[], kT=1e-9)
+    assert np.isclose(np.linalg.norm(w.pos[pair + 1] - w.pos[pair]), 1.2, atol=1e-5)
+    d = w.pos[pair + 1] - w.pos[pair]
+    w.vel[pair], w.vel[pair + 1] = -35.0 * d, 35.0 * d          # 1.2 -> 1.6 in one step
+    with db.System.from_workload(w) as s:
+        s.step(1)
+        with pytest.raises(db.DybondError) as e:
+            s.observables()
+        assert e.value.name == "DB_EBOND"
+        s.set_state(0, w.pos, 0.0 * w.vel)
+        assert s.observables()["largest_cluster_fraction"] == 2.0 / n
