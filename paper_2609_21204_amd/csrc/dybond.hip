@@ -229,14 +229,16 @@ struct TimerScope {
         else LAUNCH_AS(sys, "k_eval", (k_eval<false, mode>), ge_, kBlock, (sys)->P, (sys)->D, xin, off, out3);             \
     } while (0)
 // the same, with the name the kernel is timed under given explicitly
-#define LAUNCH_AS(sys, tname, kern, grid, block, ...)                                            \
-    do {                                                                                         \
-        TimerScope ts_((sys), tname);                                                            \
-        if (ts_.a)                                                                               \
-            hipExtLaunchKernelGGL(kern, dim3(grid), dim3(block), 0, (sys)->stream, ts_.a, ts_.b, \
-                                  0u, __VA_ARGS__);                                              \
-        else                                                                                     \
-            hipLaunchKernelGGL(kern, dim3(grid), dim3(block), 0, (sys)->stream, __VA_ARGS__);   \
+#define LAUNCH_AS(sys, tname, kern, grid, block, ...) LAUNCH_LDS(sys, tname, kern, grid, block, 0, __VA_ARGS__)
+// the same, with `lds` bytes of dynamic LDS
+#define LAUNCH_LDS(sys, tname, kern, grid, block, lds, ...)                                        \
+    do {                                                                                           \
+        TimerScope ts_((sys), tname);                                                              \
+        if (ts_.a)                                                                                 \
+            hipExtLaunchKernelGGL(kern, dim3(grid), dim3(block), lds, (sys)->stream, ts_.a, ts_.b, \
+                                  0u, __VA_ARGS__);                                                \
+        else                                                                                       \
+            hipLaunchKernelGGL(kern, dim3(grid), dim3(block), lds, (sys)->stream, __VA_ARGS__);    \
     } while (0)
 
 void flush_timing(db_system* s) {
@@ -2487,10 +2489,8 @@ db_status db_read_observables(db_system* s, db_observables* out) {
     if (s->n <= kObsOneMaxN) {
         const size_t lds = s->n * sizeof(uint32_t);
         const unsigned gw = 1u + (s->n + kObsSites - 1u) / kObsSites;
-        if (P.ext_force)
-            hipLaunchKernelGGL((k_observe_one<true>), dim3(gw), dim3(kObsOneThreads), lds, s->stream, P, s->D, s->cur_x, s->obs_h);
-        else
-            hipLaunchKernelGGL((k_observe_one<false>), dim3(gw), dim3(kObsOneThreads), lds, s->stream, P, s->D, s->cur_x, s->obs_h);
+        if (P.ext_force) LAUNCH_LDS(s, "k_observe_one", (k_observe_one<true>), gw, kObsOneThreads, lds, P, s->D, s->cur_x, s->obs_h);
+        else LAUNCH_LDS(s, "k_observe_one", (k_observe_one<false>), gw, kObsOneThreads, lds, P, s->D, s->cur_x, s->obs_h);
     } else {
         if (P.ext_force) LAUNCH_AS(s, "k_observe", (k_observe<true>), g, kBlock, P, s->D, s->cur_x);
         else LAUNCH_AS(s, "k_observe", (k_observe<false>), g, kBlock, P, s->D, s->cur_x);

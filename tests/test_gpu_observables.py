@@ -95,3 +95,16 @@ def test_an_error_met_by_the_evaluation_is_reported_by_the_call(n, pair):
         assert e.value.name == "DB_EBOND"
         s.set_state(0, w.pos, 0.0 * w.vel)
         assert s.observables()["largest_cluster_fraction"] == 2.0 / n
+
+
+@pytest.mark.parametrize("n, kernel", [(600, "k_observe_one"), (9000, "k_observe")])
+def test_kernel_timing_counts_the_observables(n, kernel):
+    with db.System.from_workload(inputs.replica(5, n, 5.0, 0.1, 2, "mono")) as s:
+        db.db_kernel_timing(s.h, 1)
+        plain = s.observables()
+        s.observables()
+        launches, ms = db.db_read_kernel_time(s.h, kernel)
+        assert launches == 2 and 0.0 < ms < 100.0
+        db.db_kernel_timing(s.h, 0)
+        again = s.observables()
+        assert all(np.array_equal(plain[k], again[k]) for k in plain)
