@@ -584,6 +584,16 @@ constexpr uint32_t kStepEightThreadN = 32768u, kStepFourThreadN = 130000u, kStep
 uint32_t auto_step_tpp(uint32_t n) {
     return n < kStepEightThreadN ? 8u : (n < kStepFourThreadN ? 4u : (n < kStepOneThreadN ? 2u : 1u));
 }
+// List entries per thread loaded up front by the step kernel that `tpp_step`
+// selects (launch_step).
+uint32_t step_list_batch(const Params& P) {
+    switch (P.tpp_step) {
+        case 1: return (uint32_t)kStep1List;
+        case 2: return (uint32_t)kStepqList2;
+        case 4: return P.qb_step ? P.qb_step : 1u;
+        default: return 1u;
+    }
+}
 uint32_t auto_propose_tpp(uint32_t n) { return n < kStepEightThreadN ? 8u : 2u; }
 
 void fill_params(db_system* s) {
@@ -918,7 +928,7 @@ void launch_step(db_system* s) {
 #define STEP_SHAPES(EXT)                                          \
     switch (P.tpp_step) {                                         \
         case 1: STEP_AS(k_step1<EXT>); break;                     \
-        case 2: STEP_AS(k_stepq<2, 3, EXT>); break;               \
+        case 2: STEP_AS(k_stepq<2, kStepqList2, EXT>); break;     \
         case 4:                                                   \
             if (P.qb_step == 2) STEP_AS(k_stepq<4, 2, EXT>);      \
             else if (P.qb_step == 4) STEP_AS(k_stepq<4, 4, EXT>); \
@@ -1523,8 +1533,7 @@ db_status db_set_step_shape(db_system* s, uint32_t tpp, uint32_t list_batch) {
 db_status db_get_step_shape(const db_system* s, uint32_t* tpp, uint32_t* list_batch) {
     if (!s || !tpp || !list_batch) return DB_EINVAL;
     *tpp = s->committed ? s->P.tpp_step : s->tpp_user;
-    *list_batch = s->committed ? (s->P.qb_step ? s->P.qb_step : (s->P.tpp_step == 1 ? 4u : std::max(1u, 4u / s->P.tpp_step)))
-                               : s->qb_user;
+    *list_batch = s->committed ? step_list_batch(s->P) : s->qb_user;
     return DB_OK;
 }
 

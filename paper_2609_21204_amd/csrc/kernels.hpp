@@ -1036,6 +1036,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
 // which a queue has no room is evaluated by the thread that holds it.
 // Arguments as k_step.  Measured against k_step<4> before it (whole step):
 // 200 000 particles 37.2 -> 31.9 us, 1 M 113 -> 95 us, 50 000 23.0 -> 21.3 us.
+constexpr int kStepqList2 = 3;    // Q with two threads per particle
 template <int TPP, int Q, bool EXT = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EXT ? 7 : 8))) void k_stepq(const Params P, const Dev D, int xin,
                                                                                        int sp, int f3, int accum_ke) {
@@ -1237,10 +1238,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EXT ? 7 : 8
 // result bit for bit as k_step<TPP>.  Compiled for 6 waves per SIMD (78
 // VGPRs, no spill): with 4 bond words up front it took 88 VGPRs and ran 5,
 // 4 % slower at 4 M and 16 M particles; 8 waves spill.
+constexpr int kStep1List = 4;     // list entries loaded up front
 template <bool EXT = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k_step1(const Params P, const Dev D, int xin, int sp,
                                                                                        int f3, int accum_ke) {
-    constexpr int Q = 4, BQ = 2;
+    constexpr int Q = kStep1List, BQ = 2;
     __shared__ StepTabs T;
     const uint32_t tid = threadIdx.x;
     const uint32_t i = xcd_block() * 256u + tid;

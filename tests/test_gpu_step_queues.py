@@ -52,3 +52,13 @@ def test_full_variant_with_many_bond_slots(shape):
     for r in w.reactions:
         r["slip"] = 0.5
     compare(w, shape, (150, 90))
+
+
+@pytest.mark.parametrize("shape, batch", [((1, 0), 4), ((2, 0), 3), ((2, 4), 3), ((4, 0), 1), ((4, 2), 2), ((4, 4), 4),
+                                          ((8, 0), 1), ((16, 0), 1), ((32, 0), 1)])
+def test_the_shape_in_use_is_the_one_that_is_launched(shape, batch):
+    with db.System.from_workload(inputs.replica(3, 200, 5.0, 0.2, 2, "mono"), commit=False) as s:
+        db.db_set_step_shape(s.h, *shape)
+        assert db.db_get_step_shape(s.h) == shape                # as requested
+        db.db_commit(s.h)
+        assert db.db_get_step_shape(s.h) == (shape[0], batch)    # as resolved
