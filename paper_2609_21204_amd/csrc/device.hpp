@@ -422,6 +422,14 @@ __device__ __forceinline__ uint2 xref_pack(const Params& P, float4 p) {
     return make_uint2((uint32_t)b, (uint32_t)(b >> 32));
 }
 
+// The build position that a packed one stands for: the centre of its grid
+// cell (which packs to the same word again).
+__device__ __forceinline__ float3 xref_point(const Params& P, uint2 r) {
+    const unsigned long long b = (unsigned long long)r.x | ((unsigned long long)r.y << 32);
+    auto c = [&](unsigned long long v) { return ((float)(v & 0x1FFFFFull) + 0.5f) * P.xqinv - P.halfLf; };
+    return make_float3(c(b), c(b >> 21), c(b >> 42));
+}
+
 // Has the particle at p moved farther than skin / 2 from its packed build
 // position r?  The grid point is the centre of r's grid cell, at most
 // sqrt(3) L / 2^22 (plus FP32 rounding) from where the list was built; the
@@ -429,9 +437,8 @@ __device__ __forceinline__ uint2 xref_pack(const Params& P, float4 p) {
 // skin / 2 always triggers (a rebuild may come slightly early, which changes
 // nothing computed: the lists only have to contain every pair in range).
 __device__ __forceinline__ bool moved_past_skin(const Params& P, uint2 r, float4 p) {
-    const unsigned long long b = (unsigned long long)r.x | ((unsigned long long)r.y << 32);
-    auto c = [&](unsigned long long v) { return ((float)(v & 0x1FFFFFull) + 0.5f) * P.xqinv - P.halfLf; };
-    const float dx = mi_delta_f(c(b), p.x, P), dy = mi_delta_f(c(b >> 21), p.y, P), dz = mi_delta_f(c(b >> 42), p.z, P);
+    const float3 c = xref_point(P, r);
+    const float dx = mi_delta_f(c.x, p.x, P), dy = mi_delta_f(c.y, p.y, P), dz = mi_delta_f(c.z, p.z, P);
     return dx * dx + dy * dy + dz * dz > P.disp2;
 }
 

@@ -50,6 +50,7 @@ struct BatchState {
 template <int TPP>
 struct ResList {
     static constexpr uint32_t KL = TPP == 2 ? kResList2 : kResList1;
+    static_assert(KL <= 32, "one bit per entry");
     uint16_t* lst;           // entry q < KL at lst[q * stride]
     uint32_t* far;           // the particle's column of the list in memory
     uint32_t stride, n, m, sub, top;
@@ -93,12 +94,12 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
     const int xin0 = st.cur_x;
 
     float4 p = make_float4(0.f, 0.f, 0.f, 0.f), u = p;
-    uint2 ref = make_uint2(0u, 0u);                // packed build position
+    float3 ref = make_float3(0.f, 0.f, 0.f);       // build position, on the packed grid
     uint32_t listed = 0;
     if (live) {
         p = D.x[xin0][i];
         u = D.u[i];
-        ref = D.xref[i];
+        ref = xref_point(P, D.xref[i]);
         listed = D.nl_cnt[i];
     }
     const uint32_t ti = type_of(p), tag = __float_as_uint(u.w);
@@ -197,7 +198,7 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
         const uint32_t both = TPP == 2 ? m + (uint32_t)__shfl_xor((int)m, 1, 64) : m;
         if (own && both > P.nlmax) atomicOr(&D.err[0], kErrNlist);
         L.m = min(m, max(KL, P.nlmax));            // (beyond it only after that error)
-        ref = xref_pack(P, p);
+        ref = xref_point(P, xref_pack(P, p));
         built = true;
     };
 
@@ -215,24 +216,25 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
         if (live) {
             // pairs: screen the thread's entries 2 at a time, then evaluate
             // those inside the cutoff, FP32 ones first, so that a wave runs
-            // as many evaluations as its busiest lane needs; KL entries per
-            // round, the first round from LDS, further ones from memory (the
-            // same choice for every lane of a round)
-            for (uint32_t q0 = 0; q0 < L.m; q0 += KL) {
-                auto entry = [&](uint32_t q) { return q0 == 0u ? L.near_at(q) : L.far_at(q0 + q); };
+            // as many evaluations as its busiest lane needs.  Entries beyond
+            // the LDS slots follow in rounds, brought into words that only the
+            // sweep uses (a load from either place, chosen per entry, cost
+            // every step 2.5 %, a loop of its own for them 9 %).
+            const uint16_t* cur = L.lst;
+            uint32_t q0 = 0, cnt = min(L.m, KL);
+            for (;;) {
                 uint32_t near = 0u, exact = 0u;
-                const uint32_t lim = min(L.m - q0, KL);
-                for (uint32_t q1 = 0; q1 < lim; q1 += 2) {
+                for (uint32_t q1 = 0; q1 < cnt; q1 += 2) {
                     uint32_t j[2];
                     float4 pj[2];
 #pragma unroll
-                    for (uint32_t e = 0; e < 2; ++e) j[e] = entry(min(q1 + e, lim - 1u));
+                    for (uint32_t e = 0; e < 2; ++e) j[e] = cur[min(q1 + e, cnt - 1u) * L.stride];
 #pragma unroll
                     for (uint32_t e = 0; e < 2; ++e) pj[e] = X[j[e]];
 #pragma unroll
                     for (uint32_t e = 0; e < 2; ++e) {
                         const uint32_t w = pair_screen(P, T, p, pj[e], ti);
-                        const uint32_t bit = q1 + e < lim ? 1u << (q1 + e) : 0u;
+                        const uint32_t bit = q1 + e < cnt ? 1u << (q1 + e) : 0u;
                         near |= w == kPairNear ? bit : 0u;
                         exact |= w == kPairExact ? bit : 0u;
                     }
@@ -240,13 +242,24 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
                 while (near) {
                     const uint32_t q = (uint32_t)__builtin_ctz(near);
                     near &= near - 1u;
-                    pair_force_near(P, T, D.err, p, X[entry(q)], ti, fx, fy, fz);
+                    pair_force_near(P, T, D.err, p, X[cur[q * L.stride]], ti, fx, fy, fz);
                 }
                 while (exact) {
                     const uint32_t q = (uint32_t)__builtin_ctz(exact);
                     exact &= exact - 1u;
-                    pair_force_f64(P, T, D.err, p, X[entry(q)], ti, fx, fy, fz);
+                    pair_force_f64(P, T, D.err, p, X[cur[q * L.stride]], ti, fx, fy, fz);
                 }
+                q0 += cnt;
+                if (q0 >= L.m) break;
+                constexpr uint32_t kRound = 8 / TPP;         // 16 bytes of keys per particle
+                uint16_t* const spare = reinterpret_cast<uint16_t*>(B0) + sub * n + i;
+                uint32_t far[kRound];
+                cnt = min(L.m - q0, kRound);
+#pragma unroll
+                for (uint32_t e = 0; e < kRound; ++e) far[e] = L.far_at(q0 + min(e, cnt - 1u));
+#pragma unroll
+                for (uint32_t e = 0; e < kRound; ++e) spare[e * L.stride] = (uint16_t)far[e];
+                cur = spare;
             }
             auto bond = [&](uint32_t b, uint32_t w) {
                 const uint32_t j = w & kIdxMask;
@@ -276,7 +289,9 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
                     D.img[n + i] += iy;
                     D.img[2 * (size_t)n + i] += iz;
                 }
-                if (moved_past_skin(P, ref, p)) flag[k % 3] = 1u;
+                const float dx = mi_delta_list(ref.x, p.x, P), dy = mi_delta_list(ref.y, p.y, P),
+                            dz = mi_delta_list(ref.z, p.z, P);
+                if (dx * dx + dy * dy + dz * dz > P.disp2) flag[k % 3] = 1u;
             }
         }
         if (ake) {
@@ -386,7 +401,7 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
             }
         if (own) {
             D.nl_cnt[i] = min(L.m + m_other, P.nlmax);
-            D.xref[i] = ref;
+            D.xref[i] = xref_pack(P, make_float4(ref.x, ref.y, ref.z, 0.f));
         }
     }
     __syncthreads();
