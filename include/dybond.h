@@ -285,9 +285,9 @@ DB_API db_status db_commit(db_system* sys);
  * with P_on = P0_on exp(-U_b(r)/kT) and breaks the bonds present at its
  * start with P0_off (Eq. pon, Eq. probs).  Synchronous: returns when the
  * GPU work is done.  A small system (up to 1024 particles, fewer where they
- * have many neighbours) with the automatic launch shape runs in one workgroup
- * that keeps its state on the chip, instead of the grid kernels, with the same
- * result bit for bit.  Errors: DB_ESTATE (not committed, invalid state),
+ * have many neighbours or bonds) with the automatic launch shape runs in one
+ * workgroup that keeps its state on the chip, instead of the grid kernels, with
+ * the same result bit for bit.  Errors: DB_ESTATE (not committed, invalid state),
  * DB_EDEVICE, DB_ENOMEM; DB_EBOND / DB_EOVERFLOW leave the state invalid
  * (DB_ESTATE) until db_set_state. */
 DB_API db_status db_step(db_system* sys, uint64_t n_steps);

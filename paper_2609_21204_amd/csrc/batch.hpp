@@ -470,6 +470,7 @@ void k_batch(const BatchItem* __restrict__ items, BatchState* __restrict__ state
         st.t = t0 + nsteps;
         st.cur_x = xin;
         st.cur_list = lcur;
+        st.listed = st0.listed;
         for (int w = 0; w < 4; ++w) st.err[w] = __hip_atomic_load(&D.err[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         state[blockIdx.x] = st;
     }

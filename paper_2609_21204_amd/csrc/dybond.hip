@@ -68,6 +68,8 @@ constexpr double kDefaultSkin = 0.3;
 // steps, 37.7 every 240, 37.5 every 480 (4 M particles: 504, 492, 494 us).
 constexpr uint64_t kSortPeriod = 480;
 
+constexpr uint32_t kBatchChunk = 2000;     // steps per launch of a one-workgroup run
+
 // Workspace of db_step_batch, kept by the first system of the batch: the
 // batch's items on the device (and in pinned memory on their way there), the
 // systems' states in pinned memory, which the kernels read and write in place,
@@ -132,7 +134,9 @@ struct db_system {
     uint32_t* err_h = nullptr;      // pinned host memory: the device error words, then `obs_h` and `one_h`
     unsigned long long* obs_h = nullptr;   // pinned answers of the observables and histograms
     std::vector<double> val_sum;           // per type: valence x particles
-    double mean_nb = 0.0;                  // neighbours within the list radius at the mean density
+    double ends = 0.0;                     // bond ends that a particle may have, on average (static, and its valence)
+    uint32_t listed = 0;                   // entries of all neighbour lists when they were last counted (small systems)
+    uint64_t listed_due = 0;               // step from which the grid kernels' lists are counted again
     uint64_t step = 0;
     int cur_x = 0, cur_list = 0;
     std::vector<uint32_t> tag_h, rtag_h;   // host mirrors of tag / rtag
@@ -721,7 +725,6 @@ void fill_params(db_system* s) {
     // neighbour slots: room for 2.5x the mean count of an ideal gas at this
     // density plus 32, at least 64 (or exactly what the caller asked for)
     const double mean_nb = 4.18879020478639 * rlist * rlist * rlist * (double)s->n / (s->L * s->L * s->L);
-    s->mean_nb = mean_nb;
     const uint32_t auto_nl = (std::max<uint32_t>(64u, (uint32_t)std::ceil(2.5 * mean_nb + 32.0)) + 7u) & ~7u;
     P.nlmax = s->nlmax_user ? s->nlmax_user : auto_nl;
 
@@ -821,6 +824,12 @@ db_status upload_state(db_system* s, const float* pos3, const float* vel3, const
     if (err[0] & kErrForce) { s->invalid = true; return fail(s, DB_EBOND, "force out of range"); }
     if (err[0] & kErrNlist) { s->invalid = true; return fail(s, DB_EOVERFLOW, "more than %u neighbours of one particle", s->P.nlmax); }
     s->invalid = false;
+    if (n <= kResMaxN) {
+        std::vector<uint32_t> cnt(n);
+        HIPCHK(s, hipMemcpy(cnt.data(), s->D.nl_cnt, n * sizeof(uint32_t), hipMemcpyDeviceToHost));
+        s->listed = std::accumulate(cnt.begin(), cnt.end(), 0u);
+        s->listed_due = s->step + kBatchChunk;
+    }
     return DB_OK;
 }
 
@@ -1069,8 +1078,6 @@ db_status prepare_graphs(db_system* s) {
     return DB_OK;
 }
 
-constexpr uint32_t kBatchChunk = 2000;     // steps per launch of a one-workgroup run
-
 // Threads per particle of the resident form (resident_steps) in a workgroup
 // of `threads`, 0 where the system has more particles or list cells than it
 // holds.  Two threads share a particle's pairs and bonds, and both integrate
@@ -1092,23 +1099,36 @@ void allow_lds(const void* kernel) {
         (void)hipGetLastError();
 }
 
-// db_step runs a small system in one workgroup that keeps its state on the
-// chip (k_resident) instead of the grid kernels, whatever the number of steps
-// (a launch costs no set-up).  One CU is limited by instruction issue, which
-// grows with the particles and their listed neighbours (m on average), the
-// grid kernels by launches, 11 to 13 us per step at any of these sizes:
-// 256, 512 and 1000 particles at density 0.1 (m = 1.7) take 5.8, 6.8 and 9.0
-// us, at density 0.3 (m = 5.1) 7.3, 9.5 and 12.4 us, 1000 at density 0.4 (m =
-// 6.9) 15.3 us.  The line n (2 + m) = 7000 runs between these.  A
-// caller-chosen launch shape, graphs off or kernel timing take the grid
-// kernels.
-constexpr double kOneGroupWork = 7000.0;
-bool one_group(const db_system* s) {
-    if (!s->use_graphs || s->timing.on || s->tpp_user != 0) return false;
-    return resident_tpp(s, kBatchMaxThreads) != 0u && s->n * (2.0 + s->mean_nb) <= kOneGroupWork;
+// db_step may run a small system in one workgroup that keeps its state on the
+// chip (k_resident) instead of the grid kernels.  A caller-chosen launch
+// shape, graphs off or kernel timing take the grid kernels.
+bool may_one_group(const db_system* s) {
+    return s->use_graphs && !s->timing.on && s->tpp_user == 0 && resident_tpp(s, kBatchMaxThreads) != 0u;
 }
 
-db_status run_one_group(db_system* s, uint64_t nsteps) {
+// Whether it does.  One CU is limited by instruction issue, which grows with
+// the particles, their listed neighbours (m on average, counted in the lists
+// themselves: a collapsed network in a large box has long lists at a low mean
+// density) and the bonds they may have (b ends on average); the grid kernels
+// by launches, 10 to 13 us per step at any of these sizes.  Per step, one
+// workgroup against the grid kernels, with n (1 + m + b):
+//  - two threads per particle (up to 384 particles): 9.6 against 11.2 us at
+//    4700, 10.0 / 11.6 at 7200, 12.4 / 13.0 at 7300 (a collapsed network of
+//    384), 12.8 / 12.5 at 8900, 15.5 / 13.1 at 13 300;
+//  - one thread: 1000 monomers at density 0.1 10.0 / 13.0 (4100), 850 at 0.2
+//    10.8 / 11.4 (4300), 512 in chains at 0.3 11.0 / 10.7 (3600), 700 in chains
+//    at 0.2 11.1 / 11.0 (4600) and at 0.3 12.1 / 10.9 (4800), 700 monomers at
+//    0.4 11.9 / 11.3 (5200), 850 at 0.3 12.3 / 11.2 (5300), 850 in chains at 0.3
+//    14.0 / 11.0 (5800), 1000 in a collapsed network 22.9 / 13.2 (19 800).
+constexpr double kOneGroupWork1 = 4800.0, kOneGroupWork2 = 8000.0;
+bool one_group(const db_system* s) {
+    if (!may_one_group(s)) return false;
+    const double work = s->n * (1.0 + s->ends) + s->listed;
+    return work <= (resident_tpp(s, kBatchMaxThreads) == 2u ? kOneGroupWork2 : kOneGroupWork1);
+}
+
+// One launch of at most kBatchChunk steps.
+db_status run_one_group(db_system* s, uint32_t nsteps) {
     const uint32_t tpp = resident_tpp(s, kBatchMaxThreads);
     const uint32_t threads = (s->n * tpp + 63u) & ~63u;
     const size_t lds = res_lds_bytes(s->n, s->P.ncell, tpp);
@@ -1117,21 +1137,20 @@ db_status run_one_group(db_system* s, uint64_t nsteps) {
                                     : (tpp == 2u ? reinterpret_cast<const void*>(&k_resident<false, 2>)
                                                  : reinterpret_cast<const void*>(&k_resident<false, 1>));
     if (lds > 64u * 1024u) allow_lds(fn);
-    while (nsteps) {
-        uint32_t chunk = (uint32_t)std::min<uint64_t>(kBatchChunk, nsteps);
-        BatchState st{};
-        st.t = s->step;
-        st.cur_x = s->cur_x;
-        st.cur_list = s->cur_list;
-        BatchState* out = s->one_h;
-        void* args[] = {&s->P, &s->D, &st, &chunk, &out};
-        HIPCHK(s, hipLaunchKernel(fn, dim3(1), dim3(threads), args, lds, s->stream));
-        s->step += chunk;
-        s->cur_x ^= (int)(chunk & 1u);
-        s->cur_list = (int)((s->cur_list + chunk) % 3u);
-        nsteps -= chunk;
-    }
-    return DB_OK;
+    BatchState st{};
+    st.t = s->step;
+    st.cur_x = s->cur_x;
+    st.cur_list = s->cur_list;
+    BatchState* out = s->one_h;
+    void* args[] = {&s->P, &s->D, &st, &nsteps, &out};
+    HIPCHK(s, hipLaunchKernel(fn, dim3(1), dim3(threads), args, lds, s->stream));
+    s->step += nsteps;
+    s->cur_x ^= (int)(nsteps & 1u);
+    s->cur_list = (int)((s->cur_list + nsteps) % 3u);
+    HIPCHK(s, hipStreamSynchronize(s->stream));
+    s->tail = false;
+    s->listed = s->one_h->listed;
+    return report_errors(s, s->one_h->err);
 }
 
 db_status run_grid(db_system* s, uint64_t nsteps) {
@@ -1664,6 +1683,7 @@ static db_status commit_impl(db_system* s) {
     }
     s->val_sum.assign(s->ntypes, 0.0);
     for (uint32_t i = 0; i < n; ++i) s->val_sum[s->type[i]] += s->types[s->type[i]].valence;
+    s->ends = (2.0 * (double)s->stat_bt.size() + std::accumulate(s->val_sum.begin(), s->val_sum.end(), 0.0)) / n;
     // static topology, molecule ids, tags
     std::vector<uint32_t> stat((size_t)std::max(P.stat_max, 1u) * n, kEmpty), fillc(n, 0);
     for (size_t k = 0; k < s->stat_bt.size(); ++k) {
@@ -1698,16 +1718,31 @@ db_status db_step(db_system* s, uint64_t nsteps) {
     db_status st = ready(s);
     if (st != DB_OK) return st;
     HIPCHK(s, hipSetDevice(s->device));
-    if (nsteps && one_group(s)) {
-        st = run_one_group(s, nsteps);
+    do {
+        if (nsteps && one_group(s)) {
+            const uint32_t k = (uint32_t)std::min<uint64_t>(kBatchChunk, nsteps);
+            st = run_one_group(s, k);
+            if (st != DB_OK) return st;
+            nsteps -= k;
+            continue;
+        }
+        // where one workgroup may become the faster form, the lists are
+        // counted every kBatchChunk steps (whole sweep periods)
+        uint64_t k = nsteps;
+        if (may_one_group(s)) k = std::min<uint64_t>(k, (kBatchChunk / s->period + 1) * s->period);
+        st = run_grid(s, k);
         if (st != DB_OK) return st;
-        HIPCHK(s, hipStreamSynchronize(s->stream));
-        s->tail = false;
-        return report_errors(s, s->one_h->err);
-    }
-    st = run_grid(s, nsteps);
-    if (st != DB_OK) return st;
-    return check_errors(s);
+        const bool count = may_one_group(s) && s->step >= s->listed_due;
+        if (count) LAUNCH(s, k_list_total, 1, 1024, s->P, s->D, &s->one_h->listed);
+        st = check_errors(s);
+        if (st != DB_OK) return st;
+        if (count) {
+            s->listed = s->one_h->listed;
+            s->listed_due = s->step + kBatchChunk;
+        }
+        nsteps -= k;
+    } while (nsteps);
+    return DB_OK;
 }
 
 }  // extern "C"
@@ -1848,6 +1883,7 @@ db_status run_batch(db_system* const* systems, uint32_t count, uint64_t nsteps, 
         W.state[k].t = s->step;
         W.state[k].cur_x = s->cur_x;
         W.state[k].cur_list = s->cur_list;
+        W.state[k].listed = s->listed;
     }
     // Positions in LDS (the LX variant of k_batch) wherever the largest
     // system of a group fits in the LDS share its workgroup has anyway: the
@@ -1925,6 +1961,7 @@ db_status run_batch(db_system* const* systems, uint32_t count, uint64_t nsteps, 
         s->step += nsteps;
         s->cur_x ^= (int)(nsteps & 1u);
         s->cur_list = (int)((s->cur_list + nsteps) % 3);
+        s->listed = W.state[k].listed;
         if (!W.items_h[k].resident) s->tags_dirty = true;          // renumbered by k_batch_sort
     }
     // the first error in list order, every system's message in its own handle

@@ -173,6 +173,19 @@ __global__ void k_binr(const Params P, const Dev D, int xin, int f3) {
     bin_wave(P, D, (int)D.rflag[3], i, valid, valid ? D.x[xin][i] : make_float4(0.f, 0.f, 0.f, 0.f));
 }
 
+// Entries of all neighbour lists of a small system (one workgroup).
+__global__ __launch_bounds__(1024) void k_list_total(const Params P, const Dev D, uint32_t* __restrict__ out) {
+    __shared__ uint32_t total;
+    if (threadIdx.x == 0) total = 0u;
+    __syncthreads();
+    uint32_t v = 0;
+    for (uint32_t i = threadIdx.x; i < P.n; i += blockDim.x) v += D.nl_cnt[i];
+    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+    if (__lane_id() == 0) atomicAdd(&total, v);
+    __syncthreads();
+    if (threadIdx.x == 0) *out = total;
+}
+
 // u = v - h F / m (turn full-step velocities into the stored form).
 __global__ void k_init_u(const Params P, const Dev D, int xin, uint32_t off) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;

@@ -40,6 +40,7 @@ struct BatchState {
     unsigned long long t;    // step of the system
     int cur_x, cur_list;     // current position buffer and cell list
     uint32_t err[4];         // the system's device error words after the launch
+    uint32_t listed;         // entries of all its neighbour lists
 };
 
 // Neighbour entries of one thread: the first KL in LDS, further ones in the
@@ -385,6 +386,11 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
         D.x[xin][i] = p;
         D.u[i] = u;
     }
+    uint32_t entries = live ? L.m : 0u;
+    for (int off = 32; off >= 1; off >>= 1) entries += __shfl_xor(entries, off, 64);
+    if (tid == 0) more[0] = 0u;
+    __syncthreads();
+    if (__lane_id() == 0) atomicAdd(&more[0], entries);
     // lists built during the launch: the pair's one after the other in D.nl.
     // Rows from KL on are the first thread's already, the second's further
     // entries move down from the end (to rows no higher than their own, lowest
@@ -416,6 +422,7 @@ __device__ __forceinline__ void resident_steps(const Params& P, const Dev& D, co
         e.cur_x = xin;
         e.cur_list = (int)((unsigned)(st.cur_list + nsteps % 3u) % 3u);
         for (int w = 0; w < 4; ++w) e.err[w] = __hip_atomic_load(&D.err[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        e.listed = more[0];
         *out = e;
     }
 }

@@ -1,6 +1,8 @@
 """Small systems in one workgroup (state and lists on the chip), through
 db_step and db_step_batch, against the grid kernels bit for bit."""
 
+import math
+
 import numpy as np
 import pytest
 
@@ -91,3 +93,30 @@ def test_a_sweep_after_every_step_at_the_kinetic_temperature(n):
     w.period = 1
     o = compare(w, (1, 2, 40, 61), "period 1", kt_source=db.DB_KT_KINETIC)
     assert o["forms"].sum() > 0 and o["breaks"].sum() > 0
+
+
+@pytest.mark.parametrize("n, rho, spacing, grid", [(700, 0.05, 1.13, True), (700, 0.05, 1.8, False), (300, 0.05, 1.13, False),
+                                                   (1000, 0.1, 2.0, False), (1000, 0.05, 1.13, True)])
+def test_the_form_is_chosen_by_the_lists_not_the_mean_density(n, rho, spacing, grid):
+    """A dense block in a large box has long lists: it takes the grid kernels
+    (seen by the list build of their renumbering: nothing moves here)."""
+    w = block(n, rho, spacing, kT=1e-12)
+    w.vel[:] = 0.0
+    w.reactions = [dict(w.reactions[0], epsilon=math.nan, k_on=1e-9, k_off=1e-9, p_on0=math.nan)]
+    with db.System.from_workload(w) as s:
+        b0 = db.db_read_list_builds(s.h)
+        s.step(10)
+        assert db.db_read_list_builds(s.h) - b0 == (1 if grid else 0)
+
+
+def test_a_block_that_dissolves_changes_form_within_a_call():
+    """Dense at first (grid kernels), dilute later (one workgroup): the same
+    trajectory through the changes, with the step counter and the errors of
+    one long call."""
+    w = block(700, 0.05, 1.05)
+    with db.System.from_workload(w) as a, grid_of(w) as g:
+        for steps in (3, 6000, 2500, 17):
+            a.step(steps)
+            g.step(steps)
+            assert a.step_count == g.step_count
+            assert_same(a, g, f"{steps} steps")
