@@ -120,3 +120,46 @@ def test_a_block_that_dissolves_changes_form_within_a_call():
             g.step(steps)
             assert a.step_count == g.step_count
             assert_same(a, g, f"{steps} steps")
+
+
+def three_reactions(seed, n):
+    """Telechelic chains whose ends (valence 2) bind crosslinkers and, not
+    within their own molecule, each other; crosslinkers bind each other too."""
+    w = inputs.replica(seed, n, 4.0, 0.3, 4, "chains")
+    w.types[0] = (2,) + tuple(w.types[0][1:])
+    w.bond_types = list(w.bond_types) + [(inputs.HARMONIC, 80.0, 1.0), (inputs.HARMONIC, 60.0, 1.05)]
+    r = w.reactions[0]
+    w.reactions = [dict(r, epsilon=2.0), dict(r, type_a=0, type_b=0, bond_type=2, epsilon=1.5, p_on0=0.8, self_avoid=1),
+                   dict(r, type_a=2, type_b=2, bond_type=3, epsilon=1.0, p_on0=0.5)]
+    return w
+
+
+@pytest.mark.parametrize("n", [300, 600])
+def test_several_reactions_in_one_sweep(n):
+    o = compare(three_reactions(21, n), (9, 1, 60, 130), "three reactions")
+    assert (o["forms"] > 0).all() and (o["breaks"] > 0).all(), o
+
+
+@pytest.mark.parametrize("n", [300, 600])
+def test_more_bond_slots_than_words_in_registers(n):
+    o = compare(inputs.gel_lattice(seed=4, n=n, eps_ab=3.0, eps_ac=2.0), (50, 3, 150), "gel", kt_source=db.DB_KT_KINETIC)
+    assert (o["forms"] > 0).all() and (o["breaks"] > 0).all(), o
+
+
+@pytest.mark.parametrize("n", [200, 384, 500])
+@pytest.mark.parametrize("kind", ["slip", "slip+tether", "melt+kinetic"])
+def test_full_variant(kind, n):
+    """Rate modifiers and tether bonds with one and two threads per particle."""
+    w = inputs.replica(13, n, 3.0, 0.25, 2, "mono")
+    r, kt = w.reactions[0], db.DB_KT_SETPOINT
+    if "slip" in kind:
+        r["slip"] = 0.5
+    if "tether" in kind:
+        w.bond_types = [(db.DB_BOND_TETHER, 2.0, 0.5, 0.8, 1.2, 1.6)]
+        r.update(r_min=0.6, r_max=1.5)
+    if "melt" in kind:
+        from test_gpu_modifiers import _melt_half_bound
+        r.update(epsilon=5.0, melt=_melt_half_bound())
+        kt = db.DB_KT_KINETIC
+    o = compare(w, (31, 9, 160), kind, kt_source=kt)
+    assert o["forms"].sum() > 0 and o["breaks"].sum() > 0
