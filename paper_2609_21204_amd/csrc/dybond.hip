@@ -728,7 +728,10 @@ void fill_params(db_system* s) {
     const uint32_t auto_nl = (std::max<uint32_t>(64u, (uint32_t)std::ceil(2.5 * mean_nb + 32.0)) + 7u) & ~7u;
     P.nlmax = s->nlmax_user ? s->nlmax_user : auto_nl;
 
-    P.nc = (uint32_t)std::floor(s->L / (rlist * (1.0 + 1e-5)));
+    // at least 3, which effective_skin leaves room for (where it shrinks the
+    // skin to exactly that, the quotient may round to just below 3): with 2 a
+    // 3 x 3 x 3 stencil would visit cells twice
+    P.nc = std::max(3u, (uint32_t)std::floor(s->L / (rlist * (1.0 + 1e-5))));
     P.ncell = P.nc * P.nc * P.nc;
     P.cell_scale = (float)((double)P.nc / s->L);
     P.cellcap = cell_capacity(s, P);

@@ -163,3 +163,14 @@ def test_full_variant(kind, n):
         kt = db.DB_KT_KINETIC
     o = compare(w, (31, 9, 160), kind, kt_source=kt)
     assert o["forms"].sum() > 0 and o["breaks"].sum() > 0
+
+
+@pytest.mark.parametrize("n, rho, skin", [(30, 0.4, None), (31, 0.4, None), (46, 0.45, None), (49, 0.4, 0.9), (50, 0.4, 0.9),
+                                          (99, 0.4, 0.9), (114, 0.45, 0.9)])
+def test_boxes_of_three_cells(n, rho, skin):
+    """Boxes that shrink the skin to what three cells leave it, in which L
+    over the cell side rounds to just below 3."""
+    w = inputs.replica(2, n, 4.0, rho, 2, "mono")
+    room = w.L / (3.0 * (1.0 + 1e-5)) - 1.3
+    assert 0.0 < room and w.L / ((1.3 + min(0.3 if skin is None else skin, room)) * (1.0 + 1e-5)) < 3.0
+    compare(w, (1, 20, 60), f"skin {skin}", skin=skin)
