@@ -2286,6 +2286,10 @@ db_status db_read_positions(db_system* s, float* pos3, int32_t* image3) {
     return DB_OK;
 }
 
+// Vectors of up to this many bytes are read out with one wait: 64 to 1024
+// particles 34 to 36 us against 44 with a wait before the copy, 1500 (18 KB,
+// which the runtime copies in another way) 45 against 41.
+constexpr size_t kOneWaitBytes = 16384;
 static db_status read_vec(db_system* s, float* out3, int mode) {
     db_status st = ready(s);
     if (st != DB_OK) return st;
@@ -2293,9 +2297,18 @@ static db_status read_vec(db_system* s, float* out3, int mode) {
     HIPCHK(s, hipSetDevice(s->device));
     if (mode == 1) LAUNCH_EVAL(s, 1, s->cur_x, 0u, s->stage);
     else LAUNCH_EVAL(s, 2, s->cur_x, 0u, s->stage);
+    // out3 is written only where the evaluation met no error: on small systems
+    // through a buffer of the call, with one wait instead of two
+    const size_t words = 3 * (size_t)s->n;
+    std::vector<float> small(words * sizeof(float) <= kOneWaitBytes ? words : 0);
+    if (!small.empty()) HIPCHK(s, hipMemcpyAsync(small.data(), s->stage, words * sizeof(float), hipMemcpyDeviceToHost, s->stream));
     st = check_errors(s);
     if (st != DB_OK) return st;
-    HIPCHK(s, hipMemcpyAsync(out3, s->stage, 3 * (size_t)s->n * sizeof(float), hipMemcpyDeviceToHost, s->stream));
+    if (!small.empty()) {
+        std::copy(small.begin(), small.end(), out3);
+        return DB_OK;
+    }
+    HIPCHK(s, hipMemcpyAsync(out3, s->stage, words * sizeof(float), hipMemcpyDeviceToHost, s->stream));
     HIPCHK(s, hipStreamSynchronize(s->stream));
     return DB_OK;
 }

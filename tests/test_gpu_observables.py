@@ -4,6 +4,7 @@ read-outs: bond counts, bonded fraction, clusters and kinetic energy."""
 
 import numpy as np
 import pytest
+import torch
 
 from helpers import oracle_from_workload
 from paper_2609_21204_amd import dybond as db
@@ -108,3 +109,28 @@ def test_kernel_timing_counts_the_observables(n, kernel):
         db.db_kernel_timing(s.h, 0)
         again = s.observables()
         assert all(np.array_equal(plain[k], again[k]) for k in plain)
+
+
+@pytest.mark.parametrize("n", [1365, 1366])
+def test_vectors_on_both_sides_of_the_one_wait_limit(n):
+    """16 KB of velocities or forces go out with one wait, more with two; an
+    error of the evaluation leaves the caller's array as it was."""
+    w = inputs.replica(4, n, 5.0, 0.2, 2, "mono")
+    with db.System.from_workload(w) as s:
+        s.step(30)
+        q = torch.cuda.current_stream().cuda_stream
+        for host, device in ((s.velocities, db.db_read_velocities_device), (s.forces, db.db_read_forces_device)):
+            out = torch.empty(n, 3, device="cuda")
+            device(s.h, out.data_ptr(), q)
+            torch.cuda.synchronize()
+            assert np.array_equal(host(), out.cpu().numpy())
+    w.bond_types = list(w.bond_types) + [(inputs.FENE, 30.0, 1.5)]
+    i, j = 0, int(np.argsort(np.linalg.norm(w.pos - w.pos[0], axis=1))[1])
+    d = w.pos[j] - w.pos[i]
+    w.vel[i], w.vel[j] = -80.0 * d, 80.0 * d
+    w.static_pairs, w.static_types = np.array([[i, j]], np.uint32), np.ones(1, np.uint32)
+    with db.System.from_workload(w) as s:
+        s.step(1)
+        out = np.full((n, 3), 7.0, np.float32)
+        assert db.load().db_read_forces(s.h, out.ctypes.data) == db.DB_EBOND
+        assert (out == 7.0).all()
