@@ -225,12 +225,7 @@ struct Params {
     float noise_sd[kMaxTypes];         // sqrt(1 - c1^2) sqrt(kT / m)
     float mass[kMaxTypes];
     uint32_t cap[kMaxTypes];
-    float rc2_pre[kMaxTypes * kMaxTypes];  // FP32 prefilter: (2^(1/6) sigma_ij)^2 (1 + 1e-3) + 1e-4; 0 = no WCA
-    float rc2_in[kMaxTypes * kMaxTypes];   // (0.98 rc)^2: below it the FP32 force has no cancellation
     float rl2[kMaxTypes * kMaxTypes];      // neighbour-list radius^2 of the type pair: (max(rc, r_max) + skin)^2 (1 + 1e-4)
-    float sig2f[kMaxTypes * kMaxTypes];    // sigma_ij^2
-    float eps24f[kMaxTypes * kMaxTypes];   // 24 eps_ij
-
     uint32_t bkind[kMaxBondTypes];     // 0 harmonic, 1 FENE, 2 tether
     double bk[kMaxBondTypes], br0[kMaxBondTypes], bR02[kMaxBondTypes], binvR02[kMaxBondTypes];
     double blmin[kMaxBondTypes], blc1[kMaxBondTypes], blc0[kMaxBondTypes], blmax[kMaxBondTypes];  // tether
@@ -263,7 +258,10 @@ struct PairTab {
 // Type pair (ti, tj) sits at pair_index of the arrays, so that the pairs in
 // use are the first ntypes^2 entries and only those are staged.
 struct alignas(16) StepTabs {
-    float4 pf[kMaxTypes * kMaxTypes];   // what the FP32 pair force reads: rc2_pre, rc2_in, sig2f, eps24f of Params
+    // what the FP32 pair force reads: x its prefilter, (2^(1/6) sigma_ij)^2
+    // (1 + 1e-3) + 1e-4 (0: no WCA), y (0.98 rc)^2, below which it has no
+    // cancellation, z sigma_ij^2, w 24 eps_ij
+    float4 pf[kMaxTypes * kMaxTypes];
     PairTab pair[kMaxTypes * kMaxTypes];
     double bk[kMaxBondTypes], br0[kMaxBondTypes], binvR02[kMaxBondTypes];
     double blmin[kMaxBondTypes], blc1[kMaxBondTypes], blc0[kMaxBondTypes], blmax[kMaxBondTypes];

@@ -140,7 +140,8 @@ struct db_system {
     uint64_t step = 0;
     int cur_x = 0, cur_list = 0;
     std::vector<uint32_t> tag_h, rtag_h;   // host mirrors of tag / rtag
-    std::vector<PairTab> pair_h;           // WCA table uploaded to D.pair
+    std::vector<PairTab> pair_h;           // WCA table by type pair, FP64
+    std::vector<float4> near_h;            // the same for the FP32 force (StepTabs::pf)
     Timing timing;
     std::map<uint64_t, hipGraphExec_t> graphs;   // captured step graphs, by kind and phase (graph_key)
     hipEvent_t ev_out = nullptr, ev_back = nullptr;   // ordering of device-side read-outs
@@ -533,7 +534,7 @@ void fill_tabs(const db_system* s, StepTabs& th) {
     for (uint32_t a = 0; a < P.ntypes; ++a)
         for (uint32_t b = 0; b < P.ntypes; ++b) {
             const uint32_t k = a * kMaxTypes + b, w = pair_index(P, a, b);
-            th.pf[w] = make_float4(P.rc2_pre[k], P.rc2_in[k], P.sig2f[k], P.eps24f[k]);
+            th.pf[w] = s->near_h[k];
             th.rl2[w] = P.rl2[k];
             th.pair[w] = s->pair_h[k];
         }
@@ -629,6 +630,7 @@ void fill_params(db_system* s) {
     P.cap_max = std::max(capmax, 1u);
     double rc = 0.0, rmax_all = 0.0;
     s->pair_h.assign(kMaxTypes * kMaxTypes, PairTab{0.0, 0.0, 0.0, -1.0, -1.0, 0.0, 0.0, 0.0});
+    s->near_h.assign(kMaxTypes * kMaxTypes, make_float4(0.f, 0.f, 0.f, 0.f));
     for (uint32_t a = 0; a < s->ntypes; ++a)
         for (uint32_t b = 0; b < s->ntypes; ++b) {
             const double sig = 0.5 * (s->types[a].sigma + s->types[b].sigma);
@@ -638,10 +640,8 @@ void fill_params(db_system* s) {
                 const double c = wca_cut(sig);
                 s->pair_h[k] = PairTab{sig * sig, 24.0 * eps, c, c * c * (1.0 - 1e-14), c * c * (1.0 + 1e-14),
                                        eps, 0.0, 0.0};
-                P.rc2_pre[k] = (float)(c * c * (1.0 + 1e-3) + 1e-4);
-                P.rc2_in[k] = (float)(0.98 * 0.98 * c * c);
-                P.sig2f[k] = (float)(sig * sig);
-                P.eps24f[k] = (float)(24.0 * eps);
+                s->near_h[k] = make_float4((float)(c * c * (1.0 + 1e-3) + 1e-4), (float)(0.98 * 0.98 * c * c),
+                                           (float)(sig * sig), (float)(24.0 * eps));
                 rc = std::max(rc, c);
             }
         }
