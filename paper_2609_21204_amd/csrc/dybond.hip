@@ -1123,7 +1123,9 @@ bool may_one_group(const db_system* s) {
 //    at 0.2 11.1 / 11.0 (4600) and at 0.3 12.1 / 10.9 (4800), 700 monomers at
 //    0.4 11.9 / 11.3 (5200), 850 at 0.3 12.3 / 11.2 (5300), 850 in chains at 0.3
 //    14.0 / 11.0 (5800), 1000 in a collapsed network 22.9 / 13.2 (19 800).
-constexpr double kOneGroupWork1 = 4800.0, kOneGroupWork2 = 8000.0;
+// The lines lie somewhat above break-even, because the first call on the grid
+// kernels also captures their graphs (3.3 ms).
+constexpr double kOneGroupWork1 = 5200.0, kOneGroupWork2 = 8000.0;
 bool one_group(const db_system* s) {
     if (!may_one_group(s)) return false;
     const double work = s->n * (1.0 + s->ends) + s->listed;
