@@ -524,9 +524,9 @@ DB_API db_status db_read_forces_device(db_system* sys, float* dev_force3, void* 
 
 /* Number of neighbour-list builds the system's steps have made since
  * db_commit (its initial build included; a build runs after every step that
- * moved some particle by more than half the skin, and after every spatial
- * renumbering; batched steps are not counted): the rebuild rate that the
- * list's cost is spread over.  Synchronous.  Errors: DB_EINVAL (builds
+ * moved some particle by more than half the skin, in batched steps too, and
+ * after every spatial renumbering of the grid kernels): the rebuild rate that
+ * the list's cost is spread over.  Synchronous.  Errors: DB_EINVAL (builds
  * NULL), DB_ESTATE, DB_EDEVICE. */
 DB_API db_status db_read_list_builds(db_system* sys, uint64_t* builds);
 

@@ -308,7 +308,7 @@ struct Dev {
     uint2* xref;           // positions at the last neighbour-list build, 21 bits per axis (xref_pack)
     uint32_t* rflag;       // neighbour-list rebuild flags of steps t, t+1, t+2 (index step mod 3);
                            // [3]: the cell list (0 or 1) the next build bins into;
-                           // [4]: neighbour-list builds by db_step since commit
+                           // [4]: neighbour-list builds since commit
     uint32_t* corder;      // cells in Morton order (the renumbering's cell sequence)
     // spatial reordering (counting sort by cell): new index of every particle,
     // cell offsets, and second copies of every per-particle array

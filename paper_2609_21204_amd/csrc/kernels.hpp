@@ -1248,7 +1248,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EXT ? 7 : 8
 // way (bond slots one by one, each a load and a gather in turn, took 345
 // instead of 326 us per step at 4 M), and goes on to the integration with its force in
 // registers (no LDS reduction, one barrier).  Same arguments and the same
-// result bit for bit as k_step<TPP>.  Compiled for 6 waves per SIMD (78
+// result bit for bit as k_step<TPP>.  Compiled for 6 waves per SIMD (80
 // VGPRs, no spill): with 4 bond words up front it took 88 VGPRs and ran 5,
 // 4 % slower at 4 M and 16 M particles; 8 waves spill.
 constexpr int kStep1List = 4;     // list entries loaded up front
@@ -2279,7 +2279,9 @@ __device__ __forceinline__ void observe_counters(const Params& P, const Dev& D, 
 // with everything in one workgroup, whose energies were the long part, and
 // four launches over the chip from 4097 particles on, they took 28 us (45 us
 // at 4096, 35 us in the four), and each launch more cost a call 5 us.
-// Above kObsOneMaxN particles the components of one CU are no faster.
+// kObsOneMaxN is where both forms meet (calls, monomers / chains): 36.5 / 44.7
+// us at 6000 particles against 41.7 / 53.7 in four launches, 42.2 / 53.6
+// against 42.3 / 54.6 at 8192, 46.7 / 60.1 against 42.4 / 55.9 at 10 000.
 constexpr uint32_t kObsOneMaxN = 8192;
 constexpr uint32_t kObsOneThreads = 1024, kObsSites = 256;
 template <bool EXT>

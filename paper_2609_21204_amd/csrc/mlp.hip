@@ -463,7 +463,9 @@ inline unsigned blocks(uint64_t n, unsigned bs) { return (unsigned)((n + bs - 1)
 
 // Minibatch orders on their way to the device, and rows of a prediction, go
 // through pinned buffers (allocated on first use: 2 x 1 MiB, or 2 x 4 B a row
-// up to 2 x 16 MiB, and at most 1.5 MiB).
+// up to 2 x 16 MiB, and at most 1.5 MiB).  Predictions of more than
+// kPredictRows rows take turns through the buffer at the same rate: 65 536 rows
+// 109 us, 300 000 509 us (1.66 and 1.70 us per 1000).
 constexpr uint64_t kIdxSlot = 262144, kIdxPinnedMax = 16 * kIdxSlot, kPredictRows = 65536;
 // Workgroups of the forward pass over many rows: two per CU; each keeps its
 // weights over its tiles.
