@@ -818,6 +818,7 @@ db_status upload_state(db_system* s, const float* pos3, const float* vel3, const
     LAUNCH(s, k_nlist, ntiles(P), kTileThreads, s->P, s->D, (int)(s->step % 3));
     LAUNCH_EVAL(s, 0, s->cur_x, 0u, (float*)nullptr);
     if (!vel_is_u) LAUNCH(s, k_init_u, grid_of(n), kBlock, s->P, s->D, s->cur_x, 0u);
+    if (n <= kResMaxN) LAUNCH(s, k_list_total, 1, 1024, s->P, s->D, &s->one_h->listed);
     HIPCHK(s, hipGetLastError());
     HIPCHK(s, hipStreamSynchronize(s->stream));
     uint32_t err[4];
@@ -828,9 +829,7 @@ db_status upload_state(db_system* s, const float* pos3, const float* vel3, const
     if (err[0] & kErrNlist) { s->invalid = true; return fail(s, DB_EOVERFLOW, "more than %u neighbours of one particle", s->P.nlmax); }
     s->invalid = false;
     if (n <= kResMaxN) {
-        std::vector<uint32_t> cnt(n);
-        HIPCHK(s, hipMemcpy(cnt.data(), s->D.nl_cnt, n * sizeof(uint32_t), hipMemcpyDeviceToHost));
-        s->listed = std::accumulate(cnt.begin(), cnt.end(), 0u);
+        s->listed = s->one_h->listed;
         s->listed_due = s->step + kBatchChunk;
     }
     return DB_OK;
@@ -1124,7 +1123,7 @@ bool may_one_group(const db_system* s) {
 //    0.4 11.9 / 11.3 (5200), 850 at 0.3 12.3 / 11.2 (5300), 850 in chains at 0.3
 //    14.0 / 11.0 (5800), 1000 in a collapsed network 22.9 / 13.2 (19 800).
 // The lines lie somewhat above break-even, because the first call on the grid
-// kernels also captures their graphs (3.3 ms).
+// kernels also captures their graphs (3.4 to 3.9 ms).
 constexpr double kOneGroupWork1 = 5200.0, kOneGroupWork2 = 8000.0;
 bool one_group(const db_system* s) {
     if (!may_one_group(s)) return false;
